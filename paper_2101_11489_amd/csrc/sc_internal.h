@@ -35,13 +35,18 @@ struct EventResult {
 
 // Device-resident calibration, derived once per context.
 struct DeviceCalib {
-    const float* noise;   // per strip: noise, or +inf when the strip is unusable
-    const float* gain;    // per APV
+    const float* noise;   // per strip: noise, or +inf when the strip is unusable (kNoisePad more
+                          // bytes may be read past the last one)
+    const float* gain;    // per APV: gain, 1 / gain
     const uint32_t* joins;   // module rows: [n_fed * 4] words, bit c of word c / 32 of FED f set
                              // when channel c reads the same module as channel c - 1; NULL: none
     uint32_t n_fed;
     float t_seed, t_channel, t_cluster;
+    float t2_hi, t2_lo;      // t_cluster^2 (1 +- 2^-19); NaN where the squares decide nothing
+    uint32_t regular_gains;  // every usable gain lies in [2^-60, 2^60]
 };
+// The last window of a FED loads the noise of up to 255 strips past its last digi, unused.
+constexpr size_t kNoisePad = 1024;
 
 // Tile ticket counters, one per 128-byte line: counter 0 (orders 0 and 1) or one per XCD
 // (order 2, at most 8).
@@ -71,7 +76,8 @@ hipError_t static_scratch_address(void** ptr);
 
 // Launch helpers (sc_kernels.hip). All enqueue on `stream` and return the launch error.
 hipError_t launch_derive_calib(const float* noise, const float* gain, const uint8_t* bad,
-                               uint32_t n_fed, float* noise_out, hipStream_t stream);
+                               uint32_t n_fed, float* noise_out, float* gain_pairs,
+                               hipStream_t stream);
 // Clears n_state look-back words (n_ev x n_fed), the queue and the results.
 hipError_t launch_reset(const FusedArgs& a, uint32_t n_state, hipStream_t stream);
 // stage: the LDS stage size in bytes of the tuning (0: the small one)

@@ -13,17 +13,16 @@
 //  * the FED's bytes and gains are staged into LDS with all 16-byte loads in flight at once; wave
 //    0 walks the 96 length fields in LDS (the channel map the paper builds on the CPU); then each
 //    wave takes a group of 96/W channels on its own: one lane per channel validates the records
-//    and marks where each begins in the wave's digi list in LDS, and one lane per digi fills it;
-//  * cluster forming runs digi-parallel, 128 digis per step (two per lane), with the calibration
-//    gathers of several steps in flight: the active/seed tests use one FP32 effective noise per
-//    strip (+inf for unusable strips, which never passes ADC > T*noise); a run is a chain of
-//    active digis on adjacent strips, and its sums (noise squares, charge, seeds) come from a
-//    segmented DPP scan over the lanes; the noise-square sum, in tree order, only steers the
-//    cluster threshold, whose few undecidable runs are settled with the sequential sum;
+//    and marks where each begins in the wave's digi list in LDS, from which forming takes the digis;
+//  * cluster forming runs digi-parallel, in windows of 256 digis (four per lane), with the next
+//    window's calibration gathers in flight: the active/seed tests use one FP32 effective noise
+//    per strip (+inf for unusable strips, which never passes ADC > T*noise); a run is a chain of
+//    active digis on adjacent strips, found with wave masks, and its sums (noise squares, charge,
+//    seeds) go along the four digis of a lane and from lane to lane, in the definition's order;
 //  * the waves exchange their groups' counts in LDS; the tile publishes the FED's counts and looks
 //    back over the earlier FEDs of its event, 64 per load (decoupled look-back), for its output
 //    offsets; records are written by the lane of each cluster's last strip, member ADCs
-//    (gain-corrected here) one lane per digi, again 128 digis per step.
+//    (gain-corrected here) by the lane of their digi, again in windows of 256.
 // No MFMA: nothing here is a dense contraction.
 
 #include <atomic>
@@ -47,7 +46,7 @@ constexpr uint32_t kSpinLimit = 1u << 22;   // look-back wait bound (seconds of 
 constexpr uint32_t kXcds = 8;               // XCDs of the device (queues of tile order 2)
 constexpr int kNch = kChannelsPerFed;
 constexpr int kStripsPerFed = kChannelsPerFed * kStripsPerChannel;
-constexpr uint32_t kGainVecs = 2 * kNch / 4;   // a FED's APV gains as 16-byte vectors
+constexpr uint32_t kGainVecs = 2 * kNch / 4;   // half a FED's APV gain pairs as 16-byte vectors
 
 // ---- global-address-space views (plain global loads/stores, no flat addressing) ------------
 #ifndef SC_GLOBAL_AS
@@ -89,32 +88,10 @@ __device__ __forceinline__ uint32_t from_next_lane(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x130, 0xf, 0xf, false);
 }
 
-// Sums along the runs of a 64-digi step: lane i adds the values of the r lanes just below it
-// (the part of its run that lies in the step; r = 0 outside runs), whatever the run lengths, in
-// six DPP steps: Hillis-Steele inside rows of 16 lanes (row_shr 1, 2, 4, 8; lanes whose source
-// lies in the row before read 0), then the carries across rows (row_bcast:15 into rows 1 and 3,
-// row_bcast:31 into rows 2 and 3), each taken only by lanes whose run began before the row.
 template <int Ctrl, int RowMask>
 __device__ __forceinline__ uint32_t dpp_in(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, Ctrl, RowMask, 0xf, true);
 }
-template <int Ctrl, int RowMask>
-__device__ __forceinline__ void run_sum_step(float& a, bool c) {
-    const float y = __uint_as_float(dpp_in<Ctrl, RowMask>(__float_as_uint(a)));
-    a = c ? a + y : a;
-}
-
-// (tree order: the noise sums of the cluster threshold)
-__device__ __forceinline__ void run_sums(float& a, uint32_t r) {
-    const uint32_t l = lane(), lr = l & 15u;
-    run_sum_step<0x111, 0xf>(a, r >= 1u);
-    run_sum_step<0x112, 0xf>(a, r >= 2u);
-    run_sum_step<0x114, 0xf>(a, r >= 4u);
-    run_sum_step<0x118, 0xf>(a, r >= 8u);
-    run_sum_step<0x142, 0xa>(a, (l & 16u) != 0u && r > lr);
-    run_sum_step<0x143, 0xc>(a, l >= 32u && r + 32u > l);
-}
-
 // Inclusive sum over the wavefront in six DPP steps: row_shr 1, 2, 4, 8 inside rows of 16 lanes,
 // then row_bcast:15 into rows 1 and 3 and row_bcast:31 into rows 2 and 3.
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
@@ -136,27 +113,6 @@ __device__ __forceinline__ uint32_t wave_incl_max(uint32_t x) {
     x = __builtin_elementwise_max(x, dpp_in<0x142, 0xa>(x));
     x = __builtin_elementwise_max(x, dpp_in<0x143, 0xc>(x));
     return x;
-}
-
-// run_sums for integers: the plain inclusive scan minus its value at the lane just below the
-// run's first lane (read with ds_bpermute; 0 when the run starts at lane 0). Modulo 2^32 these
-// are the conditional adds' sums exactly, so wherever a run's sum fits 32 bits they are equal.
-__device__ __forceinline__ uint32_t scan_below(uint32_t p, uint32_t first) {
-    const uint32_t y = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((first - 1u) << 2), (int)p);
-    return first ? y : 0u;
-}
-__device__ __forceinline__ void run_sums_int(uint32_t& a, uint32_t& b, uint32_t r) {
-    const uint32_t first = lane() - r;
-    const uint32_t pa = wave_incl_scan(a), pb = wave_incl_scan(b);
-    a = pa - scan_below(pa, first);
-    b = pb - scan_below(pb, first);
-}
-__device__ __forceinline__ void run_sums_int3(uint32_t& a, uint32_t& b, uint32_t& c, uint32_t r) {
-    const uint32_t first = lane() - r;
-    const uint32_t pa = wave_incl_scan(a), pb = wave_incl_scan(b), pc = wave_incl_scan(c);
-    a = pa - scan_below(pa, first);
-    b = pb - scan_below(pb, first);
-    c = pc - scan_below(pc, first);
 }
 
 __device__ __forceinline__ uint32_t wave_excl_scan(uint32_t v, uint32_t& total) {
@@ -193,16 +149,23 @@ __device__ __forceinline__ unsigned long long pack_state(uint64_t flag, uint32_t
     return (flag << 62) | ((uint64_t)(ncl & 0x7fffffffu) << 31) | (uint64_t)(nadc & 0x7fffffffu);
 }
 
-// Digi word in the list: adc(8) | strip(8) | channel-in-FED(7), and after forming the flags
-// active | continues-previous | accepted | undecided (the last two on the first digi of a run:
-// accepted, or left to the sequential noise sum). Seeds are counted while forming, not kept.
-constexpr uint32_t kActBit = 1u << 23, kContBit = 1u << 25, kAccBit = 1u << 26,
-                   kRedoBit = 1u << 27;
-constexpr uint32_t kNoKey = 0xffffffffu;
+// The digi list of a wave holds, while a channel group is built and formed,
+//  * markers, in the slot of each ZS record's first digi: bit 31, and
+//      (source << 17 | position << 2) - slot * kSlotStep   (+ kMaybeBit),
+//    source = the stage offset of the digi's ADC byte, position = channel-in-FED * 256 + strip.
+//    Adding slot' * kSlotStep gives source and position of any later digi of the record, at slot';
+//  * digi words: position << 10 | ADC, and once formed kMemberBit (a member of an accepted cluster)
+//    and kContBit (active, as the digi before it on the adjacent strip: both in one run).
+constexpr uint32_t kSlotStep = 1u << 17 | 4u, kMarker = 1u << 31, kMaybeBit = 1u;
+constexpr uint32_t kMemberBit = 1u << 30, kContBit = 1u << 29;
+constexpr uint32_t kNoStrip = 0xffffffffu;
+constexpr uint32_t kNoiseMask = 0x1fffcu;   // position << 2: byte offset in the FED's noise table
 __device__ __forceinline__ uint32_t d_adc(uint32_t d) { return d & 255u; }
-__device__ __forceinline__ uint32_t d_strip(uint32_t d) { return (d >> 8) & 255u; }
-__device__ __forceinline__ uint32_t d_ch(uint32_t d) { return (d >> 16) & 127u; }
-__device__ __forceinline__ uint32_t d_pos(uint32_t d) { return (d >> 8) & 0x7fffu; }
+__device__ __forceinline__ uint32_t d_strip(uint32_t d) { return (d >> 10) & 255u; }
+__device__ __forceinline__ uint32_t d_ch(uint32_t d) { return (d >> 18) & 127u; }
+__device__ __forceinline__ uint32_t d_pos(uint32_t d) { return (d >> 10) & 0x7fffu; }
+// a lane's bit of a wave mask, as a select condition
+__device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
 // Module rows (tiles instantiated with kMod): bit c of the FED's join words is set when channel c
 // reads the same module as channel c - 1, whose strips then continue into it (strip 255 of c - 1
@@ -232,21 +195,25 @@ __device__ __forceinline__ uint32_t lds_u16(const uint8_t* buf, uint32_t o) {
 // large one (fewer resident tiles) a FED of the 6 %, long-cluster stress events.
 constexpr int kStageSmall = 6656, kStageLarge = 10240;
 
+// A wave's list is read four words at a time from any slot below its end: three words of pad.
+constexpr int kListPad = 3;
+
 template <int W, int DW, int S = kStageSmall>
 struct TileSmem {
     static constexpr int kStageBytes = S;
     static constexpr int kStageData = kStageBytes - 16;   // FED bytes that fit (alignment slack)
-    alignas(16) uint8_t stage[kStageBytes + 16];         // the FED's bytes (+ readable pad)
-    uint32_t digi[W * DW];                               // wave w: [w*DW, (w+1)*DW)
-    alignas(16) float gain[2 * kNch];                    // the FED's APV gains
-    uint32_t ch_pos[2 * kWave];   // 96 used; 128 so that two full-wave stores fit
-    uint16_t ch_len[2 * kWave];
-    uint32_t ch_base[kNch + W];   // channel c of wave w at index c + w: digi offset in the group
-    uint8_t ch_st[kNch];
-    uint8_t chunk_first[W][kNch + 1];
-    uint32_t walk[4];             // bad_from, trailing, delta (from wave 0)
+    static constexpr int kList = DW + kListPad;
+    alignas(16) float gain[4 * kNch];                    // the FED's APV gains and reciprocals, in pairs
+    alignas(16) uint8_t stage[kStageBytes + 4];          // the FED's bytes (+ readable pad)
+    uint32_t digi[W * kList];                            // wave w: [w * kList, w * kList + DW)
+    uint32_t ch_pos[kNch + 2];    // payload offsets; [96]: past the last record, + 2; [97]: unused
+    uint16_t ch_base[kNch + W];   // channel c of wave w at index c + w: digi offset in the group,
+                                  // and kChBad if its record is malformed
+    uint8_t chunk_first[W][kNch / W + 1];
+    uint32_t walk[4];             // bad_from, trailing, delta (from wave 0), the next tile
     uint32_t grp_cnt[W + 1][3];   // per group: clusters, member ADCs; [W]: the FED's offsets
 };
+constexpr uint32_t kChBad = 0x8000u;
 
 // Two-wave tiles of 2880 digis fit eight to a CU (160 KiB of LDS).
 static_assert(sizeof(TileSmem<2, 1440>) <= 160 * 1024 / 8, "eight two-wave tiles per CU");
@@ -264,15 +231,22 @@ __device__ __forceinline__ uint32_t wave_index() {
     else return uni(threadIdx.x >> 6);
 }
 
-// The FED's 192 APV gains as 48 16-byte vectors (lanes past the 48th repeat the last one).
-__device__ __forceinline__ u32x4 load_gain_vec(const float* gains) {
+// The FED's 192 pairs of APV gain and reciprocal as 96 16-byte vectors, two per lane (lanes past
+// the 48th repeat the last ones).
+struct GainVecs {
+    u32x4 a, b;
+};
+__device__ __forceinline__ GainVecs load_gain_vecs(const float* gains) {
     const uint32_t i = lane() < kGainVecs ? lane() : kGainVecs - 1u;
-    return gc(reinterpret_cast<const u32x4*>(gains))[i];
+    gconst<u32x4>* g = gc(reinterpret_cast<const u32x4*>(gains));
+    return GainVecs{g[i], g[i + kGainVecs]};
 }
 template <int W, int DW, int S>
-__device__ __forceinline__ void store_gain_vec(TileSmem<W, DW, S>& sm, u32x4 v) {
+__device__ __forceinline__ void store_gain_vecs(TileSmem<W, DW, S>& sm, const GainVecs& v) {
     const uint32_t i = lane() < kGainVecs ? lane() : kGainVecs - 1u;
-    reinterpret_cast<u32x4*>(sm.gain)[i] = v;
+    u32x4* g = reinterpret_cast<u32x4*>(sm.gain);
+    g[i] = v.a;
+    g[i + kGainVecs] = v.b;
 }
 
 // ---- staging -----------------------------------------------------------------------------
@@ -293,8 +267,8 @@ __device__ __forceinline__ uint32_t stage_bytes(TileSmem<W, DW, S>& sm, uint32_t
     gconst<u32x4>* s4 = gc(reinterpret_cast<const u32x4*>(a0));
     u32x4* d4 = reinterpret_cast<u32x4*>(sm.stage);
     const bool lead = wave_index<W>() == 0u;
-    u32x4 gv = {0u, 0u, 0u, 0u};
-    if (gains && lead) gv = load_gain_vec(gains);
+    GainVecs gv = {};
+    if (gains && lead) gv = load_gain_vecs(gains);
     if (nchunks) {
         // every thread loads K pieces (indices past the end repeat the last piece), then stores
         // the ones that exist
@@ -311,7 +285,7 @@ __device__ __forceinline__ uint32_t stage_bytes(TileSmem<W, DW, S>& sm, uint32_t
             if (c < nchunks) d4[c] = r[k];
         }
     }
-    if (gains && lead) store_gain_vec(sm, gv);
+    if (gains && lead) store_gain_vecs(sm, gv);
     return delta;
 }
 
@@ -370,12 +344,11 @@ __device__ WalkResult stage_and_walk(TileSmem<W, DW, S>& sm, const uint8_t* g, u
             const uint32_t nx0 = from_next_lane(vpos0), nx1 = from_next_lane(vpos1);
             const uint32_t end0 = (l == 63u ? next1 : nx0) - 2u;
             const uint32_t end1 = l == kLast ? pos : nx1 - 2u;
-            const uint32_t vlen0 = end0 - vpos0, vlen1 = end1 - vpos1;
             const uint32_t good = popc(__ballot(end0 <= L)) + popc(__ballot(l <= kLast && end1 <= L));
-            sm.ch_pos[lane()] = vpos0;
-            sm.ch_len[lane()] = (uint16_t)vlen0;
-            sm.ch_pos[64 + lane()] = vpos1;   // entries 96..127 are never read
-            sm.ch_len[64 + lane()] = (uint16_t)vlen1;
+            sm.ch_pos[l] = vpos0;
+            // lane 32: where record 95 ends; the lanes past it write the unused entry
+            vpos1 = l == kLast + 1u ? pos + 2u : vpos1;
+            sm.ch_pos[l <= kLast + 1u ? 64u + l : (uint32_t)kNch + 1u] = vpos1;
             sm.walk[0] = good;
             sm.walk[1] = (good == (uint32_t)kNch && pos < L) ? 1u : 0u;
             sm.walk[2] = delta;
@@ -385,7 +358,7 @@ __device__ WalkResult stage_and_walk(TileSmem<W, DW, S>& sm, const uint8_t* g, u
         // larger than the stage: wave 0 stages windows of the FED in turn and walks them; the
         // records are then read from global memory
         if (gains) {
-            if (wave_index<W>() == 0u) store_gain_vec(sm, load_gain_vec(gains));
+            if (wave_index<W>() == 0u) store_gain_vecs(sm, load_gain_vecs(gains));
         }
         if (wave_index<W>() == 0u) {
             uint32_t pos = 0, bad_from = kNch, win = 0, win_n = 0, delta = 0;
@@ -403,9 +376,9 @@ __device__ WalkResult stage_and_walk(TileSmem<W, DW, S>& sm, const uint8_t* g, u
                     uni((uint32_t)sm.stage[o] | ((uint32_t)sm.stage[o + 1] << 8));
                 if (pos + 2 + P > L) { bad_from = k; break; }
                 sm.ch_pos[k] = pos + 2;   // the same values from every lane
-                sm.ch_len[k] = (uint16_t)P;
                 pos += 2 + P;
             }
+            sm.ch_pos[bad_from] = pos + 2;   // where record bad_from - 1 ends
             sm.walk[0] = bad_from;
             sm.walk[1] = (bad_from == (uint32_t)kNch && pos < L) ? 1u : 0u;
             sm.walk[2] = 0u;
@@ -420,36 +393,41 @@ __device__ WalkResult stage_and_walk(TileSmem<W, DW, S>& sm, const uint8_t* g, u
     return w;
 }
 
+// Payload bytes of channel ch (below the walk's bad_from): its record ends where the next begins.
+template <int W, int DW, int S>
+__device__ __forceinline__ uint32_t payload_len(const TileSmem<W, DW, S>& sm, uint32_t ch) {
+    return sm.ch_pos[ch + 1] - 2u - sm.ch_pos[ch];
+}
+
 // ---- record validation, one lane per channel ----------------------------------------------
-// Returns the channel's digi count (0 if malformed) and writes its status into ch_st.
+// Returns the channel's digi count, or kChBad if it is malformed.
 template <class P, int W, int DW, int S>
 __device__ __forceinline__ uint32_t check_channel(TileSmem<W, DW, S>& sm, P src, uint32_t ch,
                                                   const WalkResult& w) {
-    uint32_t st = w.trailing ? (uint32_t)SC_CH_FED_TRAILING : 0u;
-    uint32_t nd = 0;
-    if (ch >= w.bad_from) {
-        st |= SC_CH_MALFORMED;
-    } else {
-        const uint32_t p = sm.ch_pos[ch];
-        const uint32_t len = sm.ch_len[ch];
-        uint32_t q = 0, next_free = 0;
-        bool ok = true;
-        while (q < len) {
-            if (q + 2 > len) { ok = false; break; }
-            // both header bytes are read before any test, and the tests are combined without
-            // short-circuit branches, so a record costs one LDS round trip
-            const uint32_t first = src[p + q], cnt = src[p + q + 1];
-            const bool bad = (cnt == 0u) | (first + cnt > (uint32_t)kStripsPerChannel) |
-                             (first < next_free) | (q + 2 + cnt > len);
-            if (bad) { ok = false; break; }
-            nd += cnt;
-            next_free = first + cnt;
-            q += 2 + cnt;
-        }
-        if (!ok) { st |= SC_CH_MALFORMED; nd = 0; }
+    if (ch >= w.bad_from) return kChBad;
+    const uint32_t p = sm.ch_pos[ch];
+    const uint32_t len = payload_len(sm, ch);
+    uint32_t q = 0, next_free = 0, nd = 0;
+    bool ok = true;
+    while (q < len) {
+        if (q + 2 > len) { ok = false; break; }
+        // both header bytes are read before any test, and the tests are combined without
+        // short-circuit branches, so a record costs one LDS round trip
+        const uint32_t first = src[p + q], cnt = src[p + q + 1];
+        const bool bad = (cnt == 0u) | (first + cnt > (uint32_t)kStripsPerChannel) |
+                         (first < next_free) | (q + 2 + cnt > len);
+        if (bad) { ok = false; break; }
+        nd += cnt;
+        next_free = first + cnt;
+        q += 2 + cnt;
     }
-    sm.ch_st[ch] = (uint8_t)st;
-    return nd;
+    return ok ? nd : kChBad;
+}
+
+// Digi offset of entry i of the channel table (channel c of wave w: c + w) in its group.
+template <int W, int DW, int S>
+__device__ __forceinline__ uint32_t digi_base(const TileSmem<W, DW, S>& sm, uint32_t i) {
+    return sm.ch_base[i] & ~kChBad;
 }
 
 // The channel group [c_lo, c_hi) of wave w: digi counts -> offsets in the group (ch_base) and
@@ -460,14 +438,14 @@ __device__ uint32_t plan_chunks(TileSmem<W, DW, S>& sm, uint32_t w, uint32_t c_l
     uint32_t carry = 0;
     for (uint32_t base = c_lo; base < c_hi; base += kWave) {
         const uint32_t ch = base + lane();
-        const uint32_t nd = ch < c_hi ? count(ch) : 0u;
+        const uint32_t nd = ch < c_hi ? count(ch) : 0u;   // kChBad: malformed, no digis
         uint32_t tot;
-        const uint32_t ex = wave_excl_scan(nd, tot);
-        if (ch < c_hi) sm.ch_base[ch + w] = carry + ex;
+        const uint32_t ex = wave_excl_scan(nd & ~kChBad, tot);
+        if (ch < c_hi) sm.ch_base[ch + w] = (uint16_t)((carry + ex) | (nd & kChBad));
         carry += tot;
     }
     total = carry;
-    sm.ch_base[c_hi + w] = carry;   // uniform stores from every lane
+    sm.ch_base[c_hi + w] = (uint16_t)carry;   // uniform stores from every lane
     uint8_t* cf = sm.chunk_first[w];
     uint32_t n_chunks = 1;
     wave_sync();
@@ -479,7 +457,7 @@ __device__ uint32_t plan_chunks(TileSmem<W, DW, S>& sm, uint32_t w, uint32_t c_l
         uint32_t c = c_lo, n = 0;
         cf[0] = (uint8_t)c_lo;
         while (c < c_hi) {
-            const uint32_t start = uni(sm.ch_base[c + w]);
+            const uint32_t start = uni(digi_base(sm, c + w));
             if constexpr (kMod) {
                 // whole rows only: a row holds <= 768 <= DW digis (the host keeps DW >= 768)
                 uint32_t c1 = c + 1;
@@ -487,14 +465,14 @@ __device__ uint32_t plan_chunks(TileSmem<W, DW, S>& sm, uint32_t w, uint32_t c_l
                 while (c1 < c_hi) {
                     uint32_t c2 = c1 + 1;
                     while (c2 < c_hi && joined(J, c2)) ++c2;
-                    if (uni(sm.ch_base[c2 + w]) - start > (uint32_t)DW) break;
+                    if (uni(digi_base(sm, c2 + w)) - start > (uint32_t)DW) break;
                     c1 = c2;
                 }
                 cf[++n] = (uint8_t)c1;
                 c = c1;
             } else {
                 uint32_t c1 = c + 1;   // one channel holds <= 256 <= DW digis
-                while (c1 < c_hi && uni(sm.ch_base[c1 + 1 + w]) - start <= (uint32_t)DW) ++c1;
+                while (c1 < c_hi && uni(digi_base(sm, c1 + 1 + w)) - start <= (uint32_t)DW) ++c1;
                 cf[++n] = (uint8_t)c1;
                 c = c1;
             }
@@ -505,95 +483,87 @@ __device__ uint32_t plan_chunks(TileSmem<W, DW, S>& sm, uint32_t w, uint32_t c_l
     return n_chunks;
 }
 
-// Expand the records of channels [c0, c1) into the digi list dl.
-// From the staged FED (LDS) in two passes: one lane per channel writes, at the first digi slot
-// o of each of its records, a marker (bit 31 | (source offset of the ADC bytes - o) << 15 |
-// channel << 8 | (first strip - o) mod 256); then one lane per digi, at slot j, takes the last
-// marker at or before it and writes its digi word: ADC byte at (its source field) + j, strip
-// (its low byte + j) mod 256. Records take their slots in the order of their bytes in the FED,
-// and between two records the source offset grows by at least the first one's digis plus the
-// next one's 2-byte header, so the source field grows with every marker and the last marker at
-// or before a slot is the largest: a running maximum over the lanes, carried across steps. The
-// list's other slots never carry bit 31 (the digi words use bits 0-27, and the kernel clears the
-// list before its first tile), and slot 0 holds a marker. From global memory (a FED larger than
-// the stage): one lane per channel expands its runs, four ADC bytes per iteration.
-template <bool kStaged, class P, int W, int DW, int S>
-__device__ __forceinline__ void build_zs(TileSmem<W, DW, S>& sm, uint32_t w, uint32_t* dl, P src,
-                                         uint32_t c0, uint32_t c1) {
-    const uint32_t b0 = sm.ch_base[c0 + w];
-    if constexpr (kStaged) {
-        static_assert(TileSmem<W, DW, S>::kStageBytes + 16 <= (1 << 16), "marker source offsets are 16 bits");
-        __builtin_amdgcn_s_setprio(2);   // a serial pass that the digi pass waits for
-        for (uint32_t ch = c0 + lane(); ch < c1; ch += kWave) {
-            if (sm.ch_st[ch] & SC_CH_MALFORMED) continue;
-            const uint32_t p = sm.ch_pos[ch];
-            const uint32_t len = sm.ch_len[ch];
-            uint32_t o = sm.ch_base[ch + w] - b0;
-            uint32_t q = 0;
-            while (q < len) {
-                const uint32_t first = src[p + q], cnt = src[p + q + 1];
-                // every digi before slot o has its ADC byte before p + q + 2: no underflow
-                dl[o] = 0x80000000u | ((p + q + 2 - o) << 15) | (ch << 8) | ((first - o) & 0xffu);
-                o += cnt;
-                q += 2 + cnt;
-            }
+// The records of channels [c0, c1) of a staged FED, as markers in the digi list dl (one lane per
+// channel). Returns whether any record may go on from the record before it: its first strip follows
+// the last one of the record before (runs of more than 255 strips are written so) or, in a module
+// row, it starts at strip 0 of a joined channel.
+// Records take their slots in the order of their bytes, and from one record to the next the source
+// grows by the first one's digis plus a 2-byte header, the slot by the digis alone: the source
+// field, and with it the marker, grows, and the last marker at or before a slot is the largest.
+template <bool kMod, int W, int DW, int S>
+__device__ __forceinline__ bool build_markers(TileSmem<W, DW, S>& sm, uint32_t w, uint32_t* dl,
+                                              uint32_t delta, Joins J, uint32_t c0, uint32_t c1) {
+    static_assert(TileSmem<W, DW, S>::kStageBytes + 16 < (1 << 14), "marker sources are 14 bits");
+    static_assert(DW * 4 < (1 << 18), "position - slot must not borrow past one source step");
+    const uint32_t b0 = digi_base(sm, c0 + w);
+    const uint8_t* src = sm.stage + delta;
+    bool maybe = false;
+    __builtin_amdgcn_s_setprio(2);   // a serial pass that the digi pass waits for
+    for (uint32_t ch = c0 + lane(); ch < c1; ch += kWave) {
+        const uint32_t bw = sm.ch_base[ch + w];
+        if (bw & kChBad) continue;
+        const uint32_t p = sm.ch_pos[ch];
+        const uint32_t len = payload_len(sm, ch);
+        uint32_t o = bw - b0;
+        uint32_t q = 0;
+        // the strip a record starts on if it goes on from what is before it
+        uint32_t next = kMod && joined(J, ch) ? 0u : kNoStrip;
+        while (q < len) {
+            const uint32_t first = src[p + q], cnt = src[p + q + 1];
+            const bool on = first == next;
+            maybe |= on;
+            dl[o] = (kMarker | (on ? kMaybeBit : 0u)) +
+                    (((delta + p + q + 2u) << 17 | (ch << 10) | (first << 2)) - o * kSlotStep);
+            o += cnt;
+            q += 2 + cnt;
+            next = first + cnt;
         }
-        __builtin_amdgcn_s_setprio(0);
-        wave_sync();
-        const uint32_t n = uni(sm.ch_base[c1 + w] - b0);
-        // two steps of 64 slots per iteration, both loads first (each lane reads and writes
-        // only its own slots); a slot at or past n reads slot 0 and is neither used nor written
-        uint32_t carry = 0u;   // the last marker of the steps before (uniform)
-        for (uint32_t j0 = 0; j0 < n; j0 += 2u * kWave) {
-            const uint32_t ja = j0 + lane(), jb = ja + kWave;
-            const uint32_t va = dl[ja < n ? ja : 0u], vb = dl[jb < n ? jb : 0u];
-            const uint32_t ma = __builtin_elementwise_max(wave_incl_max(ja < n ? va : 0u), carry);
-            const uint32_t mb = __builtin_elementwise_max(wave_incl_max(jb < n ? vb : 0u),
-                                                          last_lane(ma));
-            carry = last_lane(mb);
-            if (ja < n) {
-                const uint32_t so = ((ma >> 15) & 0xffffu) + ja, ch = (ma >> 8) & 0x7fu;
-                dl[ja] = (ch << 16) | (((ma + ja) & 0xffu) << 8) | src[so];
+    }
+    __builtin_amdgcn_s_setprio(0);
+    const bool any = __ballot(maybe) != 0ull;
+    wave_sync();
+    return any;
+}
+
+// The same channels from global memory (a FED larger than the stage), as digi words: one lane per
+// channel expands its runs, four ADC bytes per iteration.
+template <int W, int DW, int S>
+__device__ __forceinline__ void build_words(TileSmem<W, DW, S>& sm, uint32_t w, uint32_t* dl,
+                                            gconst<uint8_t>* src, uint32_t c0, uint32_t c1) {
+    const uint32_t b0 = digi_base(sm, c0 + w);
+    for (uint32_t ch = c0 + lane(); ch < c1; ch += kWave) {
+        const uint32_t bw = sm.ch_base[ch + w];
+        if (bw & kChBad) continue;
+        const uint32_t p = sm.ch_pos[ch];
+        const uint32_t len = payload_len(sm, ch);
+        uint32_t o = bw - b0;
+        uint32_t q = 0;
+        while (q < len) {
+            const uint32_t first = src[p + q], cnt = src[p + q + 1];
+            const uint32_t base = (ch << 18) | (first << 10);
+            const uint32_t s = p + q + 2;
+            uint32_t i = 0;
+            for (; i + 4 <= cnt; i += 4) {
+                const uint32_t a0 = src[s + i], a1 = src[s + i + 1], a2 = src[s + i + 2],
+                               a3 = src[s + i + 3];
+                dl[o + i] = base + (i << 10) + a0;
+                dl[o + i + 1] = base + ((i + 1) << 10) + a1;
+                dl[o + i + 2] = base + ((i + 2) << 10) + a2;
+                dl[o + i + 3] = base + ((i + 3) << 10) + a3;
             }
-            if (jb < n) {
-                const uint32_t so = ((mb >> 15) & 0xffffu) + jb, ch = (mb >> 8) & 0x7fu;
-                dl[jb] = (ch << 16) | (((mb + jb) & 0xffu) << 8) | src[so];
-            }
-        }
-    } else {
-        for (uint32_t ch = c0 + lane(); ch < c1; ch += kWave) {
-            if (sm.ch_st[ch] & SC_CH_MALFORMED) continue;
-            const uint32_t p = sm.ch_pos[ch];
-            const uint32_t len = sm.ch_len[ch];
-            uint32_t o = sm.ch_base[ch + w] - b0;
-            uint32_t q = 0;
-            while (q < len) {
-                const uint32_t first = src[p + q], cnt = src[p + q + 1];
-                const uint32_t base = (ch << 16) | (first << 8);
-                const uint32_t s = p + q + 2;
-                uint32_t i = 0;
-                for (; i + 4 <= cnt; i += 4) {
-                    const uint32_t a0 = src[s + i], a1 = src[s + i + 1], a2 = src[s + i + 2],
-                                   a3 = src[s + i + 3];
-                    dl[o + i] = base + (i << 8) + a0;
-                    dl[o + i + 1] = base + ((i + 1) << 8) + a1;
-                    dl[o + i + 2] = base + ((i + 2) << 8) + a2;
-                    dl[o + i + 3] = base + ((i + 3) << 8) + a3;
-                }
-                for (; i < cnt; ++i) dl[o + i] = base + (i << 8) + src[s + i];
-                o += cnt;
-                q += 2 + cnt;
-            }
+            for (; i < cnt; ++i) dl[o + i] = base + (i << 10) + src[s + i];
+            o += cnt;
+            q += 2 + cnt;
         }
     }
     wave_sync();
 }
 
-// Dense rows of channels [c0, c1) -> digi list; 4 channels per wave step, 16 lanes x 16 strips.
+// Dense rows of channels [c0, c1) -> digi words; 4 channels per wave step, 16 lanes x 16 strips.
 template <int W, int DW, int S>
 __device__ __forceinline__ void build_dense(TileSmem<W, DW, S>& sm, uint32_t w, uint32_t* dl,
                                             const uint8_t* rows, uint32_t c0, uint32_t c1) {
-    const uint32_t b0 = sm.ch_base[c0 + w];
+    const uint32_t b0 = digi_base(sm, c0 + w);
     for (uint32_t cb = c0; cb < c1; cb += 4) {
         const uint32_t ch = cb + (lane() >> 4);
         const uint32_t s0 = (lane() & 15) * 16;
@@ -606,12 +576,12 @@ __device__ __forceinline__ void build_dense(TileSmem<W, DW, S>& sm, uint32_t w, 
         uint32_t tot;
         uint32_t o = seg16_excl_scan(cnt, tot);
         if (ch < c1) {
-            o += sm.ch_base[ch + w] - b0;
-            const uint32_t base = (ch << 16) | (s0 << 8);
+            o += digi_base(sm, ch + w) - b0;
+            const uint32_t base = (ch << 18) | (s0 << 10);
 #pragma unroll
             for (int k = 0; k < 16; ++k) {
                 const uint32_t a = (wds[k >> 2] >> ((k & 3) * 8)) & 255u;
-                if (a) dl[o++] = base + ((uint32_t)k << 8) + a;
+                if (a) dl[o++] = base + ((uint32_t)k << 10) + a;
             }
         }
     }
@@ -637,280 +607,323 @@ __device__ __forceinline__ uint32_t count_dense_row(const uint8_t* row) {
     return cnt;
 }
 
-// ---- cluster forming, digi-parallel -------------------------------------------------------
-// Uniform state of the run still open at the last digi of the previous step.
-struct OpenRun {
-    uint32_t key;   // position + 1 of its last digi (kNoKey: no open run)
-    uint32_t head;  // digi index of its first digi
-    uint32_t rp;    // run position of its last digi
-    float S;        // noise sum so far in tree order (steers the cluster-threshold filter)
-    uint32_t Q;     // raw ADC sum | seed count << 16
-    uint32_t mark;  // its threshold decision as it stands (valid if it ends here): a head bit
-};
+// ---- windows of the digi list ---------------------------------------------------------------
+// Forming and writing take the list in windows of up to 256 digis, four consecutive ones per lane
+// (lane l: slots 4 l .. 4 l + 3 of the window). A window begins where a run can begin and is cut
+// where the last run of its 256 slots may begin, so that no run crosses from one window to the
+// next; a channel has 256 strips, so a window always holds the run it begins with (in a module
+// row, whose runs may have 768 strips, a run that fills its window is taken one digi at a time).
+// What a run is follows from wave masks, one per slot of a lane: they are combined by scalar
+// instructions, which cost the vector units nothing. Sums go along the four digis of a lane in
+// order, then from lane to lane, once per further lane of the longest run (mostly once).
+// Bound by vector instruction issue. Two digis per lane with six-step lane scans of every sum, as
+// before, took 8758 vector instructions per tile of a 64-event batch (440 FEDs, 0.5 to 5 %
+// occupancy) and 0.471 ms for the launch; this takes 5551 and 0.376 ms. Four per lane rather than
+// more: a wave's share of a FED is 370 to 1700 digis, and a window costs the same however few it holds.
+constexpr uint32_t kWindow = 4 * kWave;
 
-// Cluster threshold of the runs ending at their lanes (§2: charge against the cluster
-// threshold): accepted when seeded and (float)Q >= t * sqrtf(S), S summed by fmaf from the run's
-// first strip. St, the same sum taken in tree order by run_sums, is within (L + 35) roundings of
-// the exact sum for a run of at most 256 strips, and within (L + 70) for a module row's run of at
-// most 768 (a path through the tree has at most about 10 roundings per 128-digi step, and such
-// runs span at most 3 and 7 steps); the sequential sum is within L (L = rp + 1 strips). Half of
-// that in the square root plus the roundings of the root and the product stay below
-// e = (L + 64) * 2^-24 by more than 2 roundings, so wherever q - r >= r e or q - r < -r e,
-// r = t * sqrt(St) (the difference and r e each rounded once), the sequential sum decides the
-// same way. Returns the head bit: kAccBit (accepted), kRedoBit (too close to call: settle_runs
-// decides from the sequential sum) or 0.
-template <bool kMod>
-__device__ __forceinline__ uint32_t cluster_mark(bool end, uint32_t rp, uint32_t Q, float St,
-                                                 float t) {
-    const bool seeded = end && (Q >> kQShift<kMod>) != 0u;
-    const float q = (float)(Q & ((1u << kQShift<kMod>) - 1u));
-    const float r = t * __builtin_amdgcn_sqrtf(St);
-    const float re = r * ((float)(rp + 65u) * 0x1p-24f);   // (L + 64) fits a float exactly
-    const float d = q - r;
-    const bool in_range = St >= 0x1p-60f && St <= 0x1p100f;   // false for NaN
-    const bool yes = in_range && d >= re;
-    const bool no = in_range && d < -re;
-    return !seeded ? 0u : yes ? kAccBit : no ? 0u : kRedoBit;
+// The last slot whose mask bit is set (at least one is).
+__device__ __forceinline__ uint32_t last_slot(const uint64_t (&m)[4]) {
+    const uint64_t any = m[0] | m[1] | m[2] | m[3];
+    const uint32_t l = 63u - (uint32_t)__builtin_clzll(any);
+    const uint64_t bit = 1ull << l;
+    return 4u * l + ((m[3] & bit) ? 3u : (m[2] & bit) ? 2u : (m[1] & bit) ? 1u : 0u);
 }
 
-// The runs marked kRedoBit in dl[0, nd): their threshold from the sequential fmaf sum of the
-// noise squares from the first strip, as the definition has it (rare; one lane per run).
-__device__ void settle_runs(uint32_t* dl, uint32_t nd, gconst<float>* noise, float t,
-                            uint32_t& n_cl, uint32_t& my_adc) {
-    for (uint32_t base = 0; base < nd; base += kWave) {
-        const uint32_t j = base + lane();
-        const uint32_t d = j < nd ? dl[j] : 0u;
-        bool acc = false;
-        uint32_t width = 0;
-        if (d & kRedoBit) {
-            float S = 0.0f;
-            uint32_t Q = 0, i = j, w = d;
-            for (;;) {
-                const float ni = noise[d_pos(w)];
-                S = __builtin_fmaf(ni, ni, S);
-                Q += d_adc(w);
-                if (++i >= nd) break;
-                w = dl[i];
-                if (!(w & kContBit)) break;
+// Slots [0, n) of a window, as masks.
+__device__ __forceinline__ uint64_t slots_below(uint32_t k, uint32_t n) {
+    return __ballot(4u * lane() + k < n);
+}
+
+// The four words of each lane from slot base on; past nd they read as 0. (Reads at most three
+// words past nd: the list's pad.)
+__device__ __forceinline__ void read_words(const uint32_t* dl, uint32_t base, uint32_t nd,
+                                           uint32_t (&v)[4]) {
+    const uint32_t l4 = 4u * lane(), m = nd - base;
+    const uint32_t* at = dl + base + (l4 < m ? l4 : m - 1u);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = at[k];
+    if (m < kWindow) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = l4 + k < m ? v[k] : 0u;
+    }
+}
+
+struct Window {
+    uint32_t base, n;     // first slot and digis taken; n = 0: a module-row chain longer than this
+    uint32_t raw[4];      // the list's words
+    uint32_t pos4[4];     // position << 2
+    uint32_t adc[4];
+    float noise[4];
+    uint64_t head[4];     // digis that do not follow the one before them on the adjacent strip
+};
+
+// Whether the digi at pos4 goes on from one at prev4 on the strip before it, in the same channel
+// or module row.
+template <bool kMod>
+__device__ __forceinline__ bool follows(uint32_t pos4, uint32_t prev4, Joins J) {
+    bool in_row = (pos4 & (255u << 2)) != 0u;
+    if constexpr (kMod) in_row = in_row || joined(J, pos4 >> 10);
+    return in_row && pos4 == prev4 + 4u;
+}
+
+// The window at base: markers become positions and ADCs (kMarkers; else the list holds words), the
+// window is cut, and its noise loads are issued.
+template <bool kMod, bool kMarkers>
+__device__ __forceinline__ Window load_window(const uint32_t* dl, uint32_t base, uint32_t nd,
+                                              const uint8_t* stage, gconst<float>* noise, Joins J,
+                                              bool maybe) {
+    Window x;
+    x.base = base;
+    read_words(dl, base, nd, x.raw);
+    const uint32_t m = nd - base;
+    if constexpr (kMarkers) {
+        // the largest marker at or before each slot (digi words are below every marker)
+        uint32_t s[4];
+        s[0] = x.raw[0];
+#pragma unroll
+        for (int k = 1; k < 4; ++k) s[k] = __builtin_elementwise_max(s[k - 1], x.raw[k]);
+        const uint32_t before = from_prev_lane(wave_incl_max(s[3]));
+        const uint32_t j0 = (base + 4u * lane()) * kSlotStep;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t t = __builtin_elementwise_max(s[k], before) + j0 + (uint32_t)k * kSlotStep;
+            x.pos4[k] = t & kNoiseMask;
+            x.adc[k] = stage[(t >> 17) & 0x3fffu];
+            x.head[k] = __ballot((int32_t)x.raw[k] < 0);
+        }
+        if (maybe) {   // uniform
+            const uint32_t prev = from_prev_lane(x.pos4[3]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                bool on = (x.raw[k] & kMaybeBit) != 0u;
+                if constexpr (kMod) on = on && follows<kMod>(x.pos4[k], k ? x.pos4[k ? k - 1 : 0] : prev, J);
+                x.head[k] &= ~__ballot(on);
             }
-            width = i - j;
-            acc = (float)Q >= t * __builtin_sqrtf(S);
-            if (acc) dl[j] = d | kAccBit;
         }
-        if (acc) my_adc += width;
-        n_cl += popc(__ballot(acc));
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            x.pos4[k] = (x.raw[k] >> 8) & kNoiseMask;
+            x.adc[k] = x.raw[k] & 255u;
+        }
+        const uint32_t prev = from_prev_lane(x.pos4[3]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            x.head[k] = __ballot(!follows<kMod>(x.pos4[k], k ? x.pos4[k ? k - 1 : 0] : prev, J));
     }
+    x.head[0] |= 1ull;   // where a window begins, a run can begin
+    x.n = m;
+    if (m > kWindow) {
+        x.n = last_slot(x.head);
+        if (x.n == 0u) x.n = kMod ? 0u : kWindow;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        x.noise[k] = *reinterpret_cast<gconst<float>*>(reinterpret_cast<gconst<uint8_t>*>(noise) + x.pos4[k]);
+    return x;
 }
 
-// Runs of a step of 128 digis, two per lane: digi A of lane l sits at position 2l, B at 2l + 1.
-// Digi A of lane 0 heads the part of its run that lies in the step. Run positions count from the
-// run's first digi, across steps too (carry: run position + 1 of the previous step's last digi).
-// Each head may carry a tag bit (tagA, tagB: read only where the digi heads its part of a run),
-// which every digi of the part learns.
-struct PairRuns {
-    uint32_t rpA, rpB;   // run positions of A and B
-    bool fromA;          // A's run began in an earlier step
-    uint32_t lanes;      // lanes back to where the run of B starts (0 when B is inactive)
-    bool tagA, tagB;     // the tags of the heads of A's and B's runs (where active)
-};
-__device__ __forceinline__ PairRuns pair_runs(bool actA, bool contA, bool actB, bool contB,
-                                              bool cont0, uint32_t carry, bool tagA = false,
-                                              bool tagB = false) {
-    const uint32_t l = lane();
-    const bool hA = actA && (!contA || l == 0u);
-    const bool hB = actB && !contB;
-    // 2 (1 + the position of the last head at or below each lane's digi B) + that head's tag
-    // (0: none), by a running maximum over the lanes; A's is this lane's A if it heads a run,
-    // else the previous lane's
-    const uint32_t ownA = (2u * l + 1u) * 2u + (tagA ? 1u : 0u);
-    const uint32_t own = hB ? (2u * l + 2u) * 2u + (tagB ? 1u : 0u) : hA ? ownA : 0u;
-    const uint32_t upto_b = wave_incl_max(own);
-    const uint32_t before = from_prev_lane(upto_b);
-    const uint32_t atA = hA ? ownA : before;
-    const uint32_t headA = (atA >> 1) - 1u;
-    const uint32_t lrpA = actA ? 2u * l - headA : 0u;
-    const uint32_t lrpB = contB ? lrpA + 1u : 0u;
-    PairRuns r;
-    r.fromA = actA && cont0 && headA == 0u;
-    r.rpA = lrpA + (r.fromA ? carry : 0u);
-    r.rpB = lrpB + ((contB && r.fromA) ? carry : 0u);
-    // the run of an active B starts in the lane of the last head at or below B
-    r.lanes = actB ? l - (((upto_b >> 1) - 1u) >> 1) : 0u;
-    r.tagA = (atA & 1u) != 0u;
-    r.tagB = (upto_b & 1u) != 0u;
-    return r;
+// ---- cluster forming --------------------------------------------------------------------------
+// The cluster threshold, exactly (§2: charge against the cluster threshold): (float)Q >= t *
+// sqrtf(S), S = fmaf(n, n, S) from the run's first strip, both roots and products rounded once.
+__device__ __forceinline__ bool passes_exactly(float q, float S, float t) {
+    return q >= t * __builtin_sqrtf(S);
 }
 
-// One step of 128 digis [base, base+128) of the list dl, two per lane: lane l holds digis
-// A = base + 2l and B = A + 1. Flags, runs, cluster threshold; every lane takes part (no divergent
-// cross-lane work). Adds the flag bits to the digi words, marks accepted run heads and counts
-// clusters / member ADCs.
+// Flags and runs of one window; adds the flag bits to its words and counts its clusters and
+// member ADCs (uniform).
+//  * cluster threshold: the sums S and Q are the definition's own (S in strip order), and the test
+//    q >= t sqrt(S) is taken on squares first: q q >= S t2_hi passes and q q < S t2_lo fails, with
+//    t2_hi and t2_lo = t^2 (1 +- 2^-19). Every rounding on either way is 2^-24 or less relative
+//    (three here, twice two in the definition's own test), so what the squares decide the
+//    definition decides the same; the few runs in between, and any with a NaN, take it exactly.
+//    (The host makes the factors NaN where t^2 could leave the normal range.) No root is taken:
+//    v_sqrt_f32 runs at a quarter rate, and four slots would need it per lane.
+//  * members: a run's digis learn its acceptance from its last one, backwards: through the four
+//    slots of a lane mask by mask, and through lanes that one run fills by a carry chain (an
+//    addition on the bit-reversed masks).
 template <bool kMod>
-__device__ __forceinline__ void form_step(uint32_t* dl, uint32_t base, uint32_t nd, uint32_t dA,
-                                          uint32_t dB, float nA, float nB, const DeviceCalib& cal,
-                                          Joins J, OpenRun& open, uint32_t& n_cl,
-                                          uint32_t& my_adc, uint32_t& pending) {
-    const uint32_t l = lane();
-    const uint32_t jA = base + 2u * l, jB = jA + 1u;
-    const bool vA = jA < nd, vB = jB < nd;
-    const uint32_t aA = d_adc(dA), aB = d_adc(dB);
-    const uint32_t pA = d_pos(dA), pB = d_pos(dB);
-    const float afA = (float)aA, afB = (float)aB;
-    const bool actA = vA && afA > cal.t_channel * nA;
-    const bool actB = vB && afB > cal.t_channel * nB;
-    const bool sdA = actA && afA > cal.t_seed * nA;
-    const bool sdB = actB && afB > cal.t_seed * nB;
-    // continues the previous digi: both active, same channel, adjacent strips (B follows A in
-    // the lane, A follows the previous lane's B); in a module row also strip 0 after strip 255 of
-    // the channel before, when the two are joined
-    const uint32_t keyA = actA ? pA + 1u : kNoKey;
-    const uint32_t keyB = actB ? pB + 1u : kNoKey;
-    bool edgeA = d_strip(dA) != 0u, edgeB = d_strip(dB) != 0u;
-    if constexpr (kMod) {
-        edgeA = edgeA || joined(J, d_ch(dA));
-        edgeB = edgeB || joined(J, d_ch(dB));
+__device__ __forceinline__ void form_window(uint32_t* dl, const Window& x, const DeviceCalib& cal,
+                                            uint32_t& n_cl, uint32_t& n_adc) {
+    const uint32_t l4 = 4u * lane();
+    uint64_t valid[4], act[4], K[5];   // K: continues the digi before it (both active)
+    uint32_t Q[4];                     // raw ADC sum | seed count << kQShift, along the run so far
+    float S[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const float a = (float)x.adc[k];
+        valid[k] = slots_below(k, x.n);
+        act[k] = __ballot(a > cal.t_channel * x.noise[k]) & valid[k];
+        const bool seed = a > cal.t_seed * x.noise[k];
+        Q[k] = seed ? x.adc[k] | 1u << kQShift<kMod> : x.adc[k];
     }
-    const bool contB = actB && edgeB && keyA == pB;
-    uint32_t pk = from_prev_lane(keyB);
-    pk = l == 0u ? open.key : pk;
-    const bool contA = actA && edgeA && pk == pA;
-    const bool cont0 = (__ballot(contA) & 1ull) != 0ull;
-    // the run open at the end of the previous step ends before this step
-    if (open.key != kNoKey && !cont0 && open.mark) {
-        dl[open.head] |= open.mark;   // same word, same value from every lane
-        if (open.mark == kAccBit) {
-            n_cl += 1;
-            my_adc += l == 0u ? open.rp + 1u : 0u;
+    K[0] = act[0] & (act[3] << 1) & ~x.head[0];
+#pragma unroll
+    for (int k = 1; k < 4; ++k) K[k] = act[k] & act[k - 1] & ~x.head[k];
+    K[4] = K[0] >> 1;   // the next lane's first digi continues slot 3
+    S[0] = x.noise[0] * x.noise[0];
+#pragma unroll
+    for (int k = 1; k < 4; ++k) {
+        S[k] = __builtin_fmaf(x.noise[k], x.noise[k], in_mask(K[k]) ? S[k - 1] : 0.0f);
+        Q[k] += in_mask(K[k]) ? Q[k - 1] : 0u;
+    }
+    if (K[0]) {   // runs that go on from the lane before
+        const uint64_t through = K[0] & K[1] & K[2] & K[3];
+        uint64_t deep = K[0];   // lanes whose run began at least so many lanes before
+        uint32_t cq = 0u, out = Q[3];
+        do {
+            const float cs = __uint_as_float(from_prev_lane(__float_as_uint(S[3])));
+            S[0] = __builtin_fmaf(x.noise[0], x.noise[0], in_mask(K[0]) ? cs : 0.0f);
+#pragma unroll
+            for (int k = 1; k < 4; ++k)
+                S[k] = __builtin_fmaf(x.noise[k], x.noise[k], in_mask(K[k]) ? S[k - 1] : 0.0f);
+            const uint32_t prev = from_prev_lane(out);
+            cq = in_mask(K[0]) ? prev : 0u;
+            out = Q[3] + (in_mask(through) ? cq : 0u);
+            deep = K[0] & ((through & deep) << 1);
+        } while (deep);
+        Q[0] += cq;
+        Q[1] += in_mask(K[1]) ? cq : 0u;
+        Q[2] += in_mask(K[1] & K[2]) ? cq : 0u;
+        Q[3] += in_mask(K[1] & K[2] & K[3]) ? cq : 0u;
+    }
+    uint64_t yes[4], open[4];
+    float q[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        q[k] = (float)(Q[k] & ((1u << kQShift<kMod>) - 1u));
+        const float q2 = q[k] * q[k];
+        const uint64_t ends = act[k] & ~K[k + 1] & __ballot(Q[k] >= 1u << kQShift<kMod>);
+        const uint64_t above = __ballot(q2 >= S[k] * cal.t2_hi);
+        yes[k] = ends & above;
+        open[k] = ends & ~above & ~__ballot(q2 < S[k] * cal.t2_lo);
+    }
+    if (open[0] | open[1] | open[2] | open[3]) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            yes[k] |= open[k] & __ballot(passes_exactly(q[k], S[k], cal.t_cluster));
+    }
+    // slot 0 of each lane: accepted if its run ends in the lane and was accepted there, or goes
+    // through it to an accepted one
+    const uint64_t past = K[1] & K[2] & K[3] & K[4];
+    uint64_t first = yes[0] | (K[1] & (yes[1] | (K[2] & (yes[2] | (K[3] & yes[3])))));
+    if (past) {
+        const uint64_t p = __builtin_bitreverse64(past), r = __builtin_bitreverse64(first);
+        const uint64_t s = (r << 1) & p;
+        first = __builtin_bitreverse64(r | (p & (~(p + s) | s)));
+    }
+    uint64_t mem[4];
+    mem[3] = yes[3] | (K[4] & (first >> 1));
+    mem[2] = yes[2] | (K[3] & mem[3]);
+    mem[1] = yes[1] | (K[2] & mem[2]);
+    mem[0] = yes[0] | (K[1] & mem[1]);
+    uint32_t v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        n_cl += popc(yes[k]);
+        n_adc += popc(mem[k]);
+        const uint32_t word = x.pos4[k] << 8 | x.adc[k] | (in_mask(mem[k]) ? kMemberBit : 0u) |
+                              (in_mask(K[k]) ? kContBit : 0u);
+        v[k] = in_mask(valid[k]) ? word : x.raw[k];   // the slots past the cut stay as they are
+    }
+    if (l4 < x.n) {
+        uint32_t* at = dl + x.base + l4;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) at[k] = v[k];
+    }
+}
+
+// A chain of adjacent digis that fills the window at base (module rows only), one digi at a time,
+// the same in every lane; returns the slot after it.
+template <bool kMarkers>
+__device__ uint32_t form_long_chain(uint32_t* dl, uint32_t base, uint32_t nd, const uint8_t* stage,
+                                    gconst<float>* noise, Joins J, const DeviceCalib& cal,
+                                    uint32_t& n_cl, uint32_t& n_adc) {
+    uint32_t marker = 0u, prev4 = 0u, j = base, head = base, Q = 0u, seeds = 0u;
+    float S = 0.0f;
+    bool open = false;
+    auto close = [&](uint32_t end) {   // the run [head, end)
+        if (open && seeds && passes_exactly((float)Q, S, cal.t_cluster)) {
+            n_cl += 1u;
+            n_adc += end - head;
+            for (uint32_t i = head; i < end; ++i)
+                dl[i] = uni(dl[i]) | kMemberBit | (i > head ? kContBit : 0u);
+        }
+        open = false;
+    };
+    for (; j < nd; ++j) {
+        const uint32_t raw = uni(dl[j]);
+        uint32_t pos4, adc;
+        if constexpr (kMarkers) {
+            if (raw & kMarker) marker = raw;
+            const uint32_t t = marker + j * kSlotStep;
+            pos4 = t & kNoiseMask;
+            adc = uni(stage[(t >> 17) & 0x3fffu]);
         } else {
-            pending += 1;
+            pos4 = (raw >> 8) & kNoiseMask;
+            adc = raw & 255u;
         }
+        if (j > base && !follows<true>(pos4, prev4, J)) break;
+        prev4 = pos4;
+        const float n = __uint_as_float(uni(__float_as_uint(noise[pos4 >> 2])));
+        const float a = (float)adc;
+        if (a > cal.t_channel * n) {
+            if (!open) {
+                open = true;
+                head = j;
+                Q = seeds = 0u;
+                S = 0.0f;
+            }
+            Q += adc;
+            seeds += a > cal.t_seed * n ? 1u : 0u;
+            S = __builtin_fmaf(n, n, S);
+        } else {
+            close(j);
+        }
+        dl[j] = pos4 << 8 | adc;
     }
-    const PairRuns pr = pair_runs(actA, contA, actB, contB, cont0, open.rp + 1u);
-    const uint32_t rpA = pr.rpA, rpB = pr.rpB;
-    // sums along the runs: noise squares (tree order), raw charge, seeds. Each lane's share of
-    // the run of its digi B is summed across lanes; digi A takes the previous lane's total.
-    float SA = actA ? nA * nA : 0.0f, SB = actB ? nB * nB : 0.0f;
-    uint32_t QA = actA ? aA + (sdA ? 1u << kQShift<kMod> : 0u) : 0u;
-    uint32_t QB = actB ? aB + (sdB ? 1u << kQShift<kMod> : 0u) : 0u;
-    if (cont0) {
-        const bool l0 = l == 0u;
-        SA = l0 ? SA + open.S : SA;
-        QA = l0 ? QA + open.Q : QA;
-    }
-    SB = contB ? SB + SA : SB;
-    QB = contB ? QB + QA : QB;
-    run_sums(SB, pr.lanes);
-    {
-        const uint32_t pq = wave_incl_scan(QB);
-        QB = pq - scan_below(pq, l - pr.lanes);
-    }
-    {
-        const float Sp = __uint_as_float(from_prev_lane(__float_as_uint(SB)));
-        const uint32_t Qp = from_prev_lane(QB);
-        const bool in = contA && l != 0u;
-        SA = in ? SA + Sp : SA;
-        QA = in ? QA + Qp : QA;
-    }
-    if (vA) dl[jA] = dA | (actA ? kActBit : 0u) | (contA ? kContBit : 0u);
-    if (vB) dl[jB] = dB | (actB ? kActBit : 0u) | (contB ? kContBit : 0u);
-    // runs that end inside this step; the run at digi B of lane 63 may go on, so it stays open
-    // with its threshold decision as it stands
-    const bool next_contA = from_next_lane(contA ? 1u : 0u) != 0u;
-    const bool endA = actA && !contB;
-    const bool endB = actB && !next_contA;
-    // Where A's run ends at A, B does not continue it, so B's run, where it ends here (or as it
-    // stands at lane 63), is B alone. The threshold of a one-strip run needs no sum: the square
-    // root of the rounded square of a float is that float (radix 2, round to nearest, the square
-    // neither underflowing nor overflowing), so it is (float)a >= t * n exactly; outside that
-    // range it is left to settle_runs. The tree-sum test then serves A's run, else B's.
-    const uint32_t mark1 = cluster_mark<kMod>(endA || endB, endA ? rpA : rpB, endA ? QA : QB,
-                                              endA ? SA : SB, cal.t_cluster);
-    const bool n_ok = nB >= 0x1p-60f && nB <= 0x1p60f;
-    const uint32_t single = !(endB && sdB) ? 0u
-                            : !n_ok ? kRedoBit
-                            : afB >= cal.t_cluster * nB ? kAccBit : 0u;
-    const uint32_t markA = endA ? mark1 : 0u;
-    const uint32_t markB = endA ? single : mark1;
-    const bool eB = markB != 0u && l != 63u;
-    // (LDS atomic ORs: no read back; each run has one end, so the words differ)
-    if (markA) __hip_atomic_fetch_or(&dl[jA - rpA], markA, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-    if (eB) __hip_atomic_fetch_or(&dl[jB - rpB], markB, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-    const bool accA = markA == kAccBit, accB = eB && markB == kAccBit;
-    my_adc += (accA ? rpA + 1u : 0u) + (accB ? rpB + 1u : 0u);
-    n_cl += popc(__ballot(accA)) + popc(__ballot(accB));
-    pending += popc(__ballot(markA == kRedoBit)) + popc(__ballot(eB && markB == kRedoBit));
-    open.key = last_lane(keyB);
-    open.rp = last_lane(rpB);
-    open.head = base + 127u - open.rp;
-    open.S = __uint_as_float(last_lane(__float_as_uint(SB)));
-    open.Q = last_lane(QB);
-    open.mark = last_lane(markB);
+    close(j);
+    return j;
 }
 
-// Forming over the digi list dl[0, nd): steps of 128 digis, the loads of kBatch steps in flight.
-template <bool kMod>
-__device__ __forceinline__ void form_pass(uint32_t* dl, uint32_t nd, const DeviceCalib& cal,
-                                          uint32_t fed, Joins J, uint32_t& n_cl,
-                                          uint32_t& n_adc) {
-    constexpr int kBatch = 4;
-    constexpr uint32_t kStep = 2 * kWave;
+// Forming over the digi list dl[0, nd) of a FED, the next window's loads in flight.
+template <bool kMod, bool kMarkers>
+__device__ __forceinline__ void form_pass(uint32_t* dl, uint32_t nd, const uint8_t* stage,
+                                          const DeviceCalib& cal, uint32_t fed, Joins J, bool maybe,
+                                          uint32_t& n_cl, uint32_t& n_adc) {
     gconst<float>* noise = gc(cal.noise) + fed * kStripsPerFed;
-    OpenRun open{kNoKey, 0u, 0u, 0.0f, 0u, 0u};
-    uint32_t ncl = 0, my_adc = 0, pending = 0;
-    for (uint32_t b = 0; b < nd; b += kBatch * kStep) {
-        uint32_t dA[kBatch], dB[kBatch];
-        float nA[kBatch], nB[kBatch];
-        // every lane loads (no branch): past nd the index is clamped and the digi reads as 0, whose
-        // noise load (strip 0 of the FED) is unused
-#pragma unroll
-        for (int k = 0; k < kBatch; ++k) {
-            const uint32_t j = b + (uint32_t)k * kStep + 2u * lane();
-            // j even, nd <= the list's even length: dl + j + 1 is inside the list
-            const u32x2 w = *reinterpret_cast<const u32x2*>(dl + (j < nd ? j : 0u));
-            dA[k] = j < nd ? w.x : 0u;
-            dB[k] = j + 1u < nd ? w.y : 0u;
+    uint32_t ncl = 0, nadc = 0, base = 0;
+    auto load = [&](uint32_t at) {
+        return load_window<kMod, kMarkers>(dl, at, nd, stage, noise, J, maybe);
+    };
+    if (nd) {
+        Window x = load(0u);
+        for (;;) {
+            if constexpr (kMod) {
+                if (x.n == 0u) {
+                    base = form_long_chain<kMarkers>(dl, x.base, nd, stage, noise, J, cal, ncl, nadc);
+                    if (base >= nd) break;
+                    x = load(base);
+                    continue;
+                }
+            }
+            base = x.base + x.n;
+            if (base >= nd) {
+                form_window<kMod>(dl, x, cal, ncl, nadc);
+                break;
+            }
+            const Window next = load(base);
+            form_window<kMod>(dl, x, cal, ncl, nadc);
+            x = next;
         }
-#pragma unroll
-        for (int k = 0; k < kBatch; ++k) {
-            nA[k] = noise[d_pos(dA[k])];
-            nB[k] = noise[d_pos(dB[k])];
-        }
-#pragma unroll
-        for (int k = 0; k < kBatch; ++k) {
-            const uint32_t base = b + (uint32_t)k * kStep;
-            if (base < nd)
-                form_step<kMod>(dl, base, nd, dA[k], dB[k], nA[k], nB[k], cal, J, open, ncl,
-                                my_adc, pending);
-        }
-    }
-    if (open.key != kNoKey && open.mark) {
-        dl[open.head] |= open.mark;
-        if (open.mark == kAccBit) {
-            ncl += 1;
-            my_adc += lane() == 0u ? open.rp + 1u : 0u;
-        } else {
-            pending += 1;
-        }
-    }
-    if (pending) {
-        wave_sync();
-        settle_runs(dl, nd, noise, cal.t_cluster, ncl, my_adc);
     }
     n_cl = ncl;
-    n_adc = wave_sum(my_adc);
+    n_adc = nadc;
     wave_sync();
 }
 
 // ---- outputs ------------------------------------------------------------------------------
-// Uniform state of the member run still open at the last digi of the previous write step.
-struct OpenCluster {
-    uint32_t open;   // 1: the last digi of the previous step was a member (so its run, which
-                     // the digis that continue it share, was accepted)
-    uint32_t rp;     // run position of that digi
-    uint32_t C, M;   // sums of c and strip*c so far (module rows: of the low 16 bits of pos*c)
-    uint32_t Mh;     // module rows: sum of the high bits of pos*c
-};
-
 // The float nearest to N / D for integers 0 <= N < 2^53 and 0 < D < 2^27, the same float as
 // (float)(N / D) with the double quotient. One Newton step takes the hardware reciprocal
 // estimate (good to 2^-14 or better) to y within 2^-28 of 1/D. The remainder r = N - D q1 of
@@ -927,11 +940,11 @@ __device__ __forceinline__ float quotient_to_float(double N, double D) {
     return (float)__builtin_fma(r, y, q1);
 }
 
-// Record of the cluster whose last digi is dw, rp positions after its first. Channel runs: M is
-// the sum of strip * c. Module rows: the cluster may start in an earlier channel of the row, so
-// its channel and first strip come from the position of its first digi (d_pos(dw) - rp), and the
-// strip moment from that channel's strip 0 is sum(pos * c) - 256 ch C, with sum(pos * c) =
-// 65536 Mh + M (pos * c < 2^31, summed in two halves so that 768 strips cannot overflow).
+// A cluster's record from its last digi dw: rp = its width - 1, C the charge, M the sum of strip * c.
+// Module rows: the cluster may start in an earlier channel of the row, so its channel and first
+// strip come from the position of its first digi (d_pos(dw) - rp), and the strip moment from that
+// channel's strip 0 is sum(pos * c) - 256 ch C, with sum(pos * c) = 65536 Mh + M (pos * c < 2^31,
+// summed in two halves so that 768 strips cannot overflow).
 template <bool kMod>
 __device__ __forceinline__ u32x4 make_record(uint32_t fed, uint32_t dw, uint32_t rp, uint32_t C,
                                              uint32_t M, uint32_t Mh) {
@@ -950,144 +963,207 @@ __device__ __forceinline__ u32x4 make_record(uint32_t fed, uint32_t dw, uint32_t
     const uint32_t width = rp + 1u;
     // barycenter: sum (s+1/2) c / sum c = (2M + C) / (2C), numerator and denominator exact
     // integers (2C < 2^27: C <= 768 x 65535). Both forms are computed, so that no branch splits
-    // the step; the quotient is not used when C = 0.
+    // the window; the quotient is not used when C = 0.
     const float q = quotient_to_float(2.0 * m + (double)C, 2.0 * (double)C);
     const float mid = (float)first + (float)width * 0.5f;
     const float bary = C ? q : mid;
     return u32x4{fed * kNch + ch, first | (width << 16), C, __float_as_uint(bary)};
 }
 
-// Gain-corrected ADC of a member digi: min(rint(adc / gain), 65535) with the FP32 quotient.
-__device__ __forceinline__ uint32_t corrected_adc(uint32_t d, float g) {
-    const float q = __builtin_rintf((float)d_adc(d) / g);
-    return q > 65535.0f ? 65535u : (uint32_t)q;
+// Gain-corrected ADC min(rint(a / g), 65535) with the FP32 quotient, g and r = its reciprocal
+// rounded to nearest. regular: every usable gain of the detector lies in [2^-60, 2^60]; then a r
+// is within an ulp of a / g, the remainder of one fmaf is exact, and the corrected quotient is
+// the correctly rounded one (Markstein, "Computation of elementary functions on the IBM RISC
+// System/6000 processor", 1990): three instructions for the division's ten.
+__device__ __forceinline__ uint32_t corrected_adc(uint32_t adc, float g, float r, bool regular) {
+    const float a = (float)adc;
+    const float q0 = a * r;
+    float q = __builtin_fmaf(__builtin_fmaf(-q0, g, a), r, q0);
+    if (!regular) q = a / g;   // uniform
+    return (uint32_t)__builtin_fminf(__builtin_rintf(q), 65535.0f);
 }
 
-// Records and member ADCs of the digi list dl[0, nd) at their final positions, 128 digis per
-// step, two per lane (A = base + 2l, B = A + 1) as in forming. The member ADCs are
-// gain-corrected here.
+// The sums of a run, carried from lane to lane: v[i][k] holds the sums along the digis of the lane
+// up to slot k, and gets what the lanes before hold of slot 0's run. K as in form_window.
+template <int N>
+__device__ __forceinline__ void carry_sums(uint32_t (&v)[N][4], const uint64_t (&K)[5]) {
+    if (!K[0]) return;
+    const uint64_t through = K[0] & K[1] & K[2] & K[3];
+    uint64_t deep = K[0];
+    uint32_t c[N], out[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) out[i] = v[i][3];
+    do {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const uint32_t prev = from_prev_lane(out[i]);
+            c[i] = in_mask(K[0]) ? prev : 0u;
+            out[i] = v[i][3] + (in_mask(through) ? c[i] : 0u);
+        }
+        deep = K[0] & ((through & deep) << 1);
+    } while (deep);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        v[i][0] += c[i];
+        v[i][1] += in_mask(K[1]) ? c[i] : 0u;
+        v[i][2] += in_mask(K[1] & K[2]) ? c[i] : 0u;
+        v[i][3] += in_mask(K[1] & K[2] & K[3]) ? c[i] : 0u;
+    }
+}
+
+// A cluster that fills its window (module rows only), one member at a time, the same in every
+// lane; returns the slot after it.
+template <int W, int DW, int S>
+__device__ uint32_t write_long_cluster(const TileSmem<W, DW, S>& sm, const uint32_t* dl,
+                                       uint32_t base, uint32_t nd, uint32_t fed,
+                                       const EventDesc& ev, bool regular, uint32_t& rc,
+                                       uint32_t& pa) {
+    gmut<uint16_t>* adc_out = gm(ev.adc);
+    uint32_t C = 0u, M = 0u, Mh = 0u, last = 0u, j = base;
+    for (; j < nd; ++j) {
+        const uint32_t d = uni(dl[j]);
+        if (j > base && d < (kMemberBit | kContBit)) break;
+        const float* gr = sm.gain + 2u * (d_pos(d) >> 7);
+        const uint32_t c = uni(corrected_adc(d_adc(d), gr[0], gr[1], regular));
+        const uint32_t m = d_pos(d) * c;
+        C += c;
+        M += m & 0xffffu;
+        Mh += m >> 16;
+        if (pa < ev.cap_adc) adc_out[pa] = (uint16_t)c;
+        ++pa;
+        last = d;
+    }
+    const u32x4 rec = make_record<true>(fed, last, j - base - 1u, C, M, Mh);
+    if (rc < ev.cap_cl) gm(reinterpret_cast<u32x4*>(ev.cl))[rc] = rec;
+    ++rc;
+    return j;
+}
+
+// Records and member ADCs of the digi list dl[0, nd) at their final positions, by windows as in
+// forming (here cut at the last digi that continues no cluster). The member ADCs are
+// gain-corrected here. Straight-line windows: every value of a window is formed first and the
+// stores come last, so that no lane mask has to live across a branch.
 template <bool kMod, int W, int DW, int S>
 __device__ __forceinline__ void write_pass(const TileSmem<W, DW, S>& sm, const uint32_t* dl,
                                            uint32_t nd, uint32_t fed, const EventDesc& ev,
-                                           uint32_t base_cl, uint32_t base_adc) {
-    constexpr uint32_t kStep = 2 * kWave;
+                                           bool regular, uint32_t base_cl, uint32_t base_adc) {
     gmut<uint16_t>* adc_out = gm(ev.adc);
     gmut<u32x4>* cl_out = gm(reinterpret_cast<u32x4*>(ev.cl));
-    OpenCluster oc{0u, 0u, 0u, 0u, 0u};
     uint32_t rc = base_cl, pa = base_adc;
-    const uint32_t l = lane();
-    // the digi words and APV gains of the next step are read while this step runs
-    auto gain_of = [&](uint32_t d) { return sm.gain[2 * d_ch(d) + (d_strip(d) >> 7)]; };
-    // (the index is clamped so that the read stays inside the list; digis past nd read as 0)
-    auto load = [&](uint32_t j, uint32_t& dA, uint32_t& dB) {
-        const u32x2 w = *reinterpret_cast<const u32x2*>(dl + (j < nd ? j : 0u));
-        dA = j < nd ? w.x : 0u;
-        dB = j + 1u < nd ? w.y : 0u;   // j even, nd <= the list's even length: dl + j + 1 is inside
-    };
-    uint32_t nA, nB;
-    load(2u * l, nA, nB);
-    float gnA = gain_of(nA), gnB = gain_of(nB);
-    // Straight-line steps: every value of a step is formed first and the stores come last, so
-    // that no lane mask has to live across a branch.
-    for (uint32_t base = 0; base < nd; base += kStep) {
-        const uint32_t dA = nA, dB = nB;
-        const float gA = gnA, gB = gnB;
-        load(base + kStep + 2u * l, nA, nB);
-        gnA = gain_of(nA);
-        gnB = gain_of(nB);
-        const bool actA = (dA & kActBit) != 0u, actB = (dB & kActBit) != 0u;
-        const bool contA = (dA & kContBit) != 0u, contB = (dB & kContBit) != 0u;
-        const bool cont0 = (__ballot(contA) & 1ull) != 0ull;
-        // the cluster open at the end of the previous step is complete unless lane 0 continues
-        // it: its record, already in its slot, is counted
-        rc += (oc.open != 0u && !cont0) ? 1u : 0u;
-        // members: active digis whose run head carries the accepted bit. The heads tag their
-        // runs with it; lane 0's A, when it continues a run of the previous step, tags with that
-        // run's acceptance (a member ended that step).
-        const bool tA = (dA & kAccBit) != 0u || (l == 0u && contA && oc.open != 0u);
-        const bool tB = (dB & kAccBit) != 0u;
-        const PairRuns pr = pair_runs(actA, contA, actB, contB, cont0, oc.rp + 1u, tA, tB);
-        const uint32_t rpA = pr.rpA, rpB = pr.rpB;
-        const bool memA = actA && pr.tagA;
-        const bool memB = actB && pr.tagB;
-        // every lane divides (no branch): non-members take 0
-        const uint32_t qA = corrected_adc(dA, gA), qB = corrected_adc(dB, gB);
-        const uint32_t cA = memA ? qA : 0u, cB = memB ? qB : 0u;
-        const uint64_t mbA = __ballot(memA), mbB = __ballot(memB);
-        const uint32_t padc = count_below(mbB, count_below(mbA, pa));
-        const uint32_t padcB = padc + (memA ? 1u : 0u);
-        pa += popc(mbA) + popc(mbB);
-        // charge and strip-weighted charge along member runs: each lane's share of the run of
-        // its digi B is summed across lanes; digi A takes the previous lane's total
-        uint32_t CA = cA, MA, MhA = 0u, MB, MhB = 0u;
-        if constexpr (kMod) {
-            const uint32_t mA = d_pos(dA) * cA, mB = d_pos(dB) * cB;
-            MA = mA & 0xffffu;
-            MhA = mA >> 16;
-            MB = mB & 0xffffu;
-            MhB = mB >> 16;
-        } else {
-            MA = d_strip(dA) * cA;
-            MB = d_strip(dB) * cB;
+    for (uint32_t base = 0; base < nd;) {
+        uint32_t d[4];
+        read_words(dl, base, nd, d);
+        uint64_t mem[4], K[5];   // members, and those that continue the cluster of the one before
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            mem[k] = __ballot(d[k] >= kMemberBit);
+            K[k] = __ballot(d[k] >= (kMemberBit | kContBit));
         }
-        if (cont0 && oc.open) {
-            const bool l0 = l == 0u;
-            CA = l0 ? CA + oc.C : CA;
-            MA = l0 ? MA + oc.M : MA;
-            if constexpr (kMod) MhA = l0 ? MhA + oc.Mh : MhA;
-        }
-        uint32_t CB = cB + (contB ? CA : 0u);
-        MB += contB ? MA : 0u;
-        if constexpr (kMod) {
-            MhB += contB ? MhA : 0u;
-            run_sums_int3(CB, MB, MhB, pr.lanes);
-        } else {
-            run_sums_int(CB, MB, pr.lanes);
-        }
-        {
-            const uint32_t Cp = from_prev_lane(CB), Mp = from_prev_lane(MB);
-            const bool in = contA && l != 0u;
-            CA = in ? CA + Cp : CA;
-            MA = in ? MA + Mp : MA;
-            if constexpr (kMod) {
-                const uint32_t Mhp = from_prev_lane(MhB);
-                MhA = in ? MhA + Mhp : MhA;
+        uint32_t n = nd - base;
+        if (n > kWindow) {
+            const uint64_t heads[4] = {~K[0] | 1ull, ~K[1], ~K[2], ~K[3]};
+            n = last_slot(heads);
+            if (n == 0u) {
+                if constexpr (kMod) {
+                    base = write_long_cluster(sm, dl, base, nd, fed, ev, regular, rc, pa);
+                    continue;
+                }
+                n = kWindow;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint64_t valid = slots_below(k, n);
+                mem[k] &= valid;
+                K[k] &= valid;
             }
         }
-        // records of the clusters ending in this step (A before B in a lane); the record of
-        // digi B of lane 63 as it stands is kept for the next step, which stores it if the
-        // cluster does not go on
-        const bool next_contA = from_next_lane(contA ? 1u : 0u) != 0u;
-        const bool endA = memA && !contB;
-        const bool endB = memB && !next_contA;
-        const bool eB = endB && l != 63u;
-        // rec1: the record of A's cluster where it ends here, else of B's (the division runs for
-        // the whole wavefront in any case). rec2 serves B where A's cluster ended at A: B then
-        // does not continue it and heads its own run, so where it is stored (B's cluster ends
-        // here, or lane 63 keeps it open as it stands) it is a one-strip record: first = its
-        // strip, width 1, barycenter strip + 1/2 exactly (the quotient (2 s c + c) / (2 c), and
-        // the midpoint when c = 0), in a module row too (its channel is its own)
-        const u32x4 rec1 = make_record<kMod>(fed, endA ? dA : dB, endA ? rpA : rpB,
-                                             endA ? CA : CB, endA ? MA : MB, endA ? MhA : MhB);
-        const u32x4 rec2 = u32x4{fed * kNch + d_ch(dB), d_strip(dB) | (1u << 16), CB,
-                                 __float_as_uint((float)d_strip(dB) + 0.5f)};
-        const u32x4 recB = endA ? rec2 : rec1;
-        const uint64_t ebA = __ballot(endA), ebB = __ballot(eB);
-        const uint32_t prec = count_below(ebB, count_below(ebA, rc));
-        const uint32_t precB = prec + (endA ? 1u : 0u);
-        rc += popc(ebA) + popc(ebB);
-        oc.open = (uint32_t)(mbB >> 63);
-        oc.rp = last_lane(rpB);
-        oc.C = last_lane(CB);
-        oc.M = last_lane(MB);
-        if constexpr (kMod) oc.Mh = last_lane(MhB);
-        // stores. The cluster open at digi B of lane 63 takes the next slot: its record as it
-        // stands goes there now, and a step that extends the cluster stores it there again.
-        if (memA && padc < ev.cap_adc) adc_out[padc] = (uint16_t)cA;
-        if (memB && padcB < ev.cap_adc) adc_out[padcB] = (uint16_t)cB;
-        if (endA && prec < ev.cap_cl) cl_out[prec] = rec1;
-        if (eB && precB < ev.cap_cl) cl_out[precB] = recB;
-        if (memB && l == 63u && rc < ev.cap_cl) cl_out[rc] = recB;
+        base += n;
+        K[4] = K[0] >> 1;
+        // corrected ADCs, and the sums along clusters: charge, strip moment and width
+        uint32_t c[4], s[4];
+        constexpr int kSums = kMod ? 4 : 2;   // C | width << 24, M; module rows: C, M, Mh, width
+        uint32_t v[kSums][4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float* gr = sm.gain + ((d[k] >> 16) & 0x1feu);   // 2 x (position / 128)
+            c[k] = corrected_adc(d_adc(d[k]), gr[0], gr[1], regular);
+            s[k] = d_strip(d[k]);
+            const bool on = k && in_mask(K[k]);
+            if constexpr (kMod) {
+                const uint32_t m = d_pos(d[k]) * c[k];
+                v[0][k] = c[k] + (on ? v[0][k ? k - 1 : 0] : 0u);
+                v[1][k] = (m & 0xffffu) + (on ? v[1][k ? k - 1 : 0] : 0u);
+                v[2][k] = (m >> 16) + (on ? v[2][k ? k - 1 : 0] : 0u);
+                v[3][k] = 1u + (on ? v[3][k ? k - 1 : 0] : 0u);
+            } else {
+                // at most 256 x 65535 < 2^24; a width of 256 reads as 0
+                v[0][k] = c[k] + (1u << 24) + (on ? v[0][k ? k - 1 : 0] : 0u);
+                v[1][k] = s[k] * c[k] + (on ? v[1][k ? k - 1 : 0] : 0u);
+            }
+        }
+        carry_sums(v, K);
+        // positions: members in list order, records by their cluster's last digi
+        uint64_t end[4];
+        uint32_t ra[4], rr[4];
+        ra[0] = pa;
+        rr[0] = rc;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            end[k] = mem[k] & ~K[k + 1];
+            ra[0] = count_below(mem[k], ra[0]);
+            rr[0] = count_below(end[k], rr[0]);
+            pa += popc(mem[k]);
+            rc += popc(end[k]);
+        }
+#pragma unroll
+        for (int k = 1; k < 4; ++k) {
+            ra[k] = ra[k - 1] + (in_mask(mem[k - 1]) ? 1u : 0u);
+            rr[k] = rr[k - 1] + (in_mask(end[k - 1]) ? 1u : 0u);
+        }
+        // Records by pairs of digis A and B: at most one cluster of the pair has more than one
+        // member, and rec1 is A's where it ends at A, else B's. Where A's cluster ends at A, one
+        // that ends at B is B alone: first = its strip, width 1, barycenter strip + 1/2 exactly
+        // (the quotient (2 s c + c) / (2 c), and the midpoint when c = 0), in a module row too
+        // (its channel is its own); that record is formed without the division.
+        u32x4 rec1[2], rec2[2];
+        uint64_t any[2], both[2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const int A = 2 * p, B = A + 1;
+            const bool eA = in_mask(end[A]);
+            const uint32_t dw = eA ? d[A] : d[B];
+            const uint32_t v0 = eA ? v[0][A] : v[0][B], v1 = eA ? v[1][A] : v[1][B];
+            if constexpr (kMod) {
+                const uint32_t v2 = eA ? v[2][A] : v[2][B], v3 = eA ? v[3][A] : v[3][B];
+                rec1[p] = make_record<true>(fed, dw, v3 - 1u, v0, v1, v2);
+            } else {
+                rec1[p] = make_record<false>(fed, dw, ((v0 >> 24) - 1u) & 255u, v0 & 0xffffffu, v1, 0u);
+            }
+            rec2[p] = u32x4{fed * kNch + d_ch(d[B]), s[B] | (1u << 16), c[B],
+                            __float_as_uint((float)s[B] + 0.5f)};
+            any[p] = end[A] | end[B];
+            both[p] = end[A] & end[B];
+        }
+        // (uniform: mostly the whole window fits)
+        if (pa > ev.cap_adc) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) mem[k] &= __ballot(ra[k] < ev.cap_adc);
+        }
+        if (rc > ev.cap_cl) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                any[p] &= __ballot(rr[2 * p] < ev.cap_cl);
+                both[p] &= __ballot(rr[2 * p + 1] < ev.cap_cl);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (in_mask(mem[k])) adc_out[ra[k]] = (uint16_t)c[k];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            if (in_mask(any[p])) cl_out[rr[2 * p]] = rec1[p];
+            if (in_mask(both[p])) cl_out[rr[2 * p + 1]] = rec2[p];
+        }
     }
     wave_sync();
 }
@@ -1139,43 +1215,43 @@ __device__ __forceinline__ void publish_and_lookback(unsigned long long* row, ui
     err = e;
 }
 
-// Status bits of channels [c_lo, c_hi) -> optional per-channel output and the event's flags.
+// Status bits of channels [c_lo, c_hi) of wave w -> optional per-channel output and the event's
+// flags.
 template <int W, int DW, int S>
-__device__ __forceinline__ void emit_status(TileSmem<W, DW, S>& sm, uint32_t c_lo, uint32_t c_hi,
-                                            uint8_t* chan_status, uint32_t f,
-                                            uint32_t* flags_out) {
-    uint32_t any = 0;
+__device__ __forceinline__ void emit_status(const TileSmem<W, DW, S>& sm, uint32_t w, uint32_t c_lo,
+                                            uint32_t c_hi, uint32_t trailing, uint8_t* chan_status,
+                                            uint32_t f, uint32_t* flags_out) {
+    bool bad = false;
     for (uint32_t ch = c_lo + lane(); ch < c_hi; ch += kWave) {
-        const uint32_t st = sm.ch_st[ch];
-        if (chan_status) gm(chan_status)[f * kNch + ch] = (uint8_t)st;
-        any |= st;
+        const bool b = (sm.ch_base[ch + w] & kChBad) != 0u;
+        if (chan_status)
+            gm(chan_status)[f * kNch + ch] = (uint8_t)((b ? (uint32_t)SC_CH_MALFORMED : 0u) |
+                                                       (trailing ? (uint32_t)SC_CH_FED_TRAILING : 0u));
+        bad |= b;
     }
-    const uint64_t m = __ballot(any & SC_CH_MALFORMED);
-    const uint64_t t = __ballot(any & SC_CH_FED_TRAILING);
-    const uint32_t bits = (m ? kResMalformed : 0u) | (t ? kResTrailing : 0u);
+    const uint32_t bits = (__ballot(bad) ? kResMalformed : 0u) | (trailing ? kResTrailing : 0u);
     if (bits) atomicOr(flags_out, bits);   // uniform branch; every lane ORs the same bits
 }
 
 // The cluster stages of one channel group over its chunks (shared by the ZS and the dense front
-// ends). build(c0, c1) fills the group's digi list with channels [c0, c1). The waves of a tile
-// form their groups, exchange their counts in LDS, and wave 0 publishes the FED's counts and
+// ends). form(c0, c1, nd, n_cl, n_adc) fills the group's digi list with channels [c0, c1), nd digis,
+// forms it and counts its clusters and member ADCs. The waves of a tile form their groups, exchange their counts in LDS, and wave 0 publishes the FED's counts and
 // looks back over the earlier FEDs of the event; each group's output offset is then the FED's
 // plus the counts of the groups before it. Every wave passes the same two barriers.
-template <int W, int DW, bool kMod, int S, class BuildFn>
+template <int W, int DW, bool kMod, int S, class FormFn>
 __device__ void cluster_group(const FusedArgs& A, TileSmem<W, DW, S>& sm, const EventDesc& ev,
-                              uint32_t e, uint32_t f, uint32_t w, uint32_t n_chunks,
-                              Joins J, BuildFn build) {
+                              uint32_t e, uint32_t f, uint32_t w, uint32_t n_chunks, FormFn form) {
     const uint32_t n_fed = A.cal.n_fed;
     unsigned long long* row = A.tile_state + (size_t)e * n_fed;
-    uint32_t* dl = sm.digi + w * DW;
+    const uint32_t* dl = sm.digi + w * TileSmem<W, DW, S>::kList;
     const uint8_t* cf = sm.chunk_first[w];
+    const bool regular = A.cal.regular_gains != 0u;
     // counts: one pass over each chunk; the last chunk stays in the list for its writes
     uint32_t n_cl = 0, n_adc = 0, last_cl = 0, last_adc = 0, last_nd = 0;
     for (uint32_t ci = 0; ci < n_chunks; ++ci) {
         const uint32_t c0 = uni(cf[ci]), c1 = uni(cf[ci + 1]);
-        build(c0, c1);
-        last_nd = uni(sm.ch_base[c1 + w] - sm.ch_base[c0 + w]);
-        form_pass<kMod>(dl, last_nd, A.cal, f, J, last_cl, last_adc);
+        last_nd = uni(digi_base(sm, c1 + w) - digi_base(sm, c0 + w));
+        form(c0, c1, last_nd, last_cl, last_adc);
         n_cl += last_cl;
         n_adc += last_adc;
     }
@@ -1212,15 +1288,14 @@ __device__ void cluster_group(const FusedArgs& A, TileSmem<W, DW, S>& sm, const 
     // writes: the last chunk first (still formed in the list), then the earlier chunks of a
     // chunked group, built and formed again
     const uint32_t bc = ex_cl + pre_cl, ba = ex_adc + pre_adc;
-    write_pass<kMod>(sm, dl, last_nd, f, ev, bc + n_cl - last_cl, ba + n_adc - last_adc);
+    write_pass<kMod>(sm, dl, last_nd, f, ev, regular, bc + n_cl - last_cl, ba + n_adc - last_adc);
     uint32_t oc = bc, oa = ba;
     for (uint32_t ci = 0; ci + 1 < n_chunks; ++ci) {
         const uint32_t c0 = uni(cf[ci]), c1 = uni(cf[ci + 1]);
-        build(c0, c1);
-        const uint32_t nd = uni(sm.ch_base[c1 + w] - sm.ch_base[c0 + w]);
+        const uint32_t nd = uni(digi_base(sm, c1 + w) - digi_base(sm, c0 + w));
         uint32_t ccl, cadc;
-        form_pass<kMod>(dl, nd, A.cal, f, J, ccl, cadc);
-        write_pass<kMod>(sm, dl, nd, f, ev, oc, oa);
+        form(c0, c1, nd, ccl, cadc);
+        write_pass<kMod>(sm, dl, nd, f, ev, regular, oc, oa);
         oc += ccl;
         oa += cadc;
     }
@@ -1268,7 +1343,7 @@ __device__ void zs_tile(const FusedArgs& A, TileSmem<W, DW, S>& sm, uint32_t e, 
     const uint32_t L = hi > lo ? (uint32_t)(hi - lo) : 0u;
     const uint8_t* g = ev.zs + lo;
 
-    const WalkResult wk = stage_and_walk(sm, g, L, A.cal.gain + (size_t)f * 2 * kNch);
+    const WalkResult wk = stage_and_walk(sm, g, L, A.cal.gain + (size_t)f * 4 * kNch);
     const uint32_t w = wave_index<W>();
     uint32_t c_lo, c_hi;
     group_range<W>(w, c_lo, c_hi);
@@ -1286,15 +1361,20 @@ __device__ void zs_tile(const FusedArgs& A, TileSmem<W, DW, S>& sm, uint32_t e, 
                                      [&](uint32_t ch) { return check_channel(sm, gg, ch, wk); },
                                      total);
     }
-    emit_status(sm, c_lo, c_hi, ev.chan_status, f, &A.res[e].flags);
-    uint32_t* dl = sm.digi + w * DW;
+    emit_status(sm, w, c_lo, c_hi, wk.trailing, ev.chan_status, f, &A.res[e].flags);
+    uint32_t* dl = sm.digi + w * TileSmem<W, DW, S>::kList;
     const bool fits = wk.fits != 0;
     const uint32_t delta = wk.delta;
-    auto build = [&](uint32_t c0, uint32_t c1) {
-        if (fits) build_zs<true>(sm, w, dl, (const uint8_t*)(sm.stage + delta), c0, c1);
-        else      build_zs<false>(sm, w, dl, gc(g), c0, c1);
+    auto form = [&](uint32_t c0, uint32_t c1, uint32_t nd, uint32_t& n_cl, uint32_t& n_adc) {
+        if (fits) {
+            const bool maybe = build_markers<kMod>(sm, w, dl, delta, J, c0, c1);
+            form_pass<kMod, true>(dl, nd, sm.stage, A.cal, f, J, maybe, n_cl, n_adc);
+        } else {
+            build_words(sm, w, dl, gc(g), c0, c1);
+            form_pass<kMod, false>(dl, nd, sm.stage, A.cal, f, J, false, n_cl, n_adc);
+        }
     };
-    cluster_group<W, DW, kMod>(A, sm, ev, e, f, w, n_chunks, J, build);
+    cluster_group<W, DW, kMod>(A, sm, ev, e, f, w, n_chunks, form);
 }
 
 // ---- one FED tile from dense ADC rows (single event) --------------------------------------
@@ -1312,19 +1392,21 @@ __device__ void dense_tile(const FusedArgs& A, TileSmem<W, DW, S>& sm, const uin
     ev.cap_adc = uni(evp->cap_adc);
     const uint8_t* rows = dense + (size_t)f * kStripsPerFed;
     const uint32_t w = wave_index<W>();
-    if (w == 0u) store_gain_vec(sm, load_gain_vec(A.cal.gain + (size_t)f * 2 * kNch));
+    if (w == 0u) store_gain_vecs(sm, load_gain_vecs(A.cal.gain + (size_t)f * 4 * kNch));
     tile_sync();
     uint32_t c_lo, c_hi;
     group_range<W>(w, c_lo, c_hi);
-    for (uint32_t ch = c_lo + lane(); ch < c_hi; ch += kWave) sm.ch_st[ch] = 0;
     uint32_t total;
     const Joins J = fed_joins<kMod>(A.cal, f);
     const uint32_t n_chunks = plan_chunks<kMod>(
         sm, w, c_lo, c_hi, J,
         [&](uint32_t ch) { return count_dense_row(rows + ch * kStripsPerChannel); }, total);
-    uint32_t* dl = sm.digi + w * DW;
-    auto build = [&](uint32_t c0, uint32_t c1) { build_dense(sm, w, dl, rows, c0, c1); };
-    cluster_group<W, DW, kMod>(A, sm, ev, 0, f, w, n_chunks, J, build);
+    uint32_t* dl = sm.digi + w * TileSmem<W, DW, S>::kList;
+    auto form = [&](uint32_t c0, uint32_t c1, uint32_t nd, uint32_t& n_cl, uint32_t& n_adc) {
+        build_dense(sm, w, dl, rows, c0, c1);
+        form_pass<kMod, false>(dl, nd, sm.stage, A.cal, f, J, false, n_cl, n_adc);
+    };
+    cluster_group<W, DW, kMod>(A, sm, ev, 0, f, w, n_chunks, form);
 }
 
 // ---- kernels --------------------------------------------------------------------------------
@@ -1441,17 +1523,22 @@ __device__ __forceinline__ void run_tiles(TileSmem<W, DW, S>& sm, uint32_t* queu
     }
 }
 
+// Two-wave tiles: at most 128 vector registers, so that the eight tiles that fit a CU's LDS can be
+// resident (four waves per SIMD).
+constexpr int min_waves_per_simd(int w) { return w == 2 ? 4 : 1; }
+
 template <int W, int DW, bool kMod, int S>
-__global__ __launch_bounds__(kWave * W) void fused_kernel(FusedArgs A) {
+__global__ __launch_bounds__(kWave * W, min_waves_per_simd(W)) void fused_kernel(FusedArgs A) {
     __shared__ TileSmem<W, DW, S> sm;
     // the ZS build finds its record markers by bit 31 of the digi list's slots: clear them once
-    for (uint32_t i = threadIdx.x; i < (uint32_t)(W * DW); i += kWave * W) sm.digi[i] = 0u;
+    for (uint32_t i = threadIdx.x; i < (uint32_t)(W * TileSmem<W, DW, S>::kList); i += kWave * W)
+        sm.digi[i] = 0u;
     run_tiles(sm, A.queue, A.n_ev, A.cal.n_fed, A.fed_major,
               [&](uint32_t e, uint32_t f) { zs_tile<W, DW, kMod>(A, sm, e, f); });
 }
 
 template <int W, int DW, bool kMod, int S>
-__global__ __launch_bounds__(kWave * W) void cluster_dense_kernel(const uint8_t* dense, FusedArgs A) {
+__global__ __launch_bounds__(kWave * W, min_waves_per_simd(W)) void cluster_dense_kernel(const uint8_t* dense, FusedArgs A) {
     __shared__ TileSmem<W, DW, S> sm;
     run_tiles(sm, A.queue, 1u, A.cal.n_fed, 1u,
               [&](uint32_t, uint32_t f) { dense_tile<W, DW, kMod>(A, sm, dense, f); });
@@ -1477,7 +1564,7 @@ __global__ __launch_bounds__(kWave) void unpack_kernel(const uint8_t* zs, const 
         plan_chunks<false>(sm, 0u, 0u, (uint32_t)kNch, Joins{0u, 0u, 0u},
                            [&](uint32_t ch) { return check_channel(sm, gg, ch, w); }, total);
     }
-    emit_status(sm, 0u, (uint32_t)kNch, chan_status, f, &res->flags);
+    emit_status(sm, 0u, 0u, (uint32_t)kNch, w.trailing, chan_status, f, &res->flags);
     // 16 channels at a time: zero rows in LDS, expand records, copy out with 16-byte stores
     uint8_t* rowbuf = reinterpret_cast<uint8_t*>(sm.digi);   // 4 KiB
     gmut<u32x4>* out = gm(reinterpret_cast<u32x4*>(dense + (size_t)f * kStripsPerFed));
@@ -1487,9 +1574,9 @@ __global__ __launch_bounds__(kWave) void unpack_kernel(const uint8_t* zs, const 
         tile_sync();
         if (lane() < 16) {
             const uint32_t ch = g0 + lane();
-            if (!(sm.ch_st[ch] & SC_CH_MALFORMED)) {
+            if (!(sm.ch_base[ch] & kChBad)) {
                 const uint32_t p = sm.ch_pos[ch];
-                const uint32_t len = sm.ch_len[ch];
+                const uint32_t len = payload_len(sm, ch);
                 uint8_t* row = rowbuf + lane() * kStripsPerChannel;
                 uint32_t q = 0;
                 if (w.fits) {
@@ -1529,10 +1616,15 @@ __global__ void reset_kernel(unsigned long long* state, uint32_t n_state, uint32
 // Effective noise per strip: the noise itself, or +inf when the strip is unusable (bad flag,
 // noise NaN / negative / infinite, APV gain NaN / <= 0), so that ADC > T*noise never holds
 // for it (T >= 0 finite: T*inf is +inf, or NaN for T = 0; both compare false).
+// gain_pairs: each APV's gain and its reciprocal, rounded to nearest.
 __global__ void derive_calib_kernel(const float* noise, const float* gain, const uint8_t* bad,
-                                    uint32_t n_strips, float* out) {
+                                    uint32_t n_strips, float* out, float* gain_pairs) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_strips) return;
+    if (i < n_strips / kStripsPerApv) {
+        gain_pairs[2 * i] = gain[i];
+        gain_pairs[2 * i + 1] = 1.0f / gain[i];
+    }
     const float n = noise[i];
     const float g = gain[i / kStripsPerApv];
     const bool usable = bad[i] == 0 && !__builtin_isnan(n) && n >= 0.0f && !__builtin_isinf(n) &&
@@ -1613,11 +1705,11 @@ int fused_blocks_per_cu(uint32_t waves, uint32_t d, bool dense, bool modules, ui
 }
 
 hipError_t launch_derive_calib(const float* noise, const float* gain, const uint8_t* bad,
-                               uint32_t n_fed, float* out, hipStream_t stream) {
+                               uint32_t n_fed, float* out, float* gain_pairs, hipStream_t stream) {
     const uint32_t n = n_fed * kStripsPerFed;
     (void)hipGetLastError();
     hipLaunchKernelGGL(derive_calib_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, noise,
-                       gain, bad, n, out);
+                       gain, bad, n, out, gain_pairs);
     return hipGetLastError();
 }
 

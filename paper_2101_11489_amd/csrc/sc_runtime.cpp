@@ -151,7 +151,8 @@ struct sc_ctx {
     uint32_t n_fed = 0;
     float t_seed = 3, t_channel = 2, t_cluster = 5;
     float* d_noise = nullptr;   // effective noise per strip (+inf: unusable)
-    float* d_gain = nullptr;
+    float* d_gain = nullptr;    // per APV: gain, 1 / gain
+    bool regular_gains = true;  // every usable gain lies in [2^-60, 2^60]
     int n_cu = 0;
     std::string device_name;
     sc_tuning tuning{};
@@ -430,19 +431,32 @@ sc_status stage_batch(sc_ctx* c, Workspace& ws, const sc_event* ev, uint32_t n,
     return SC_OK;
 }
 
+DeviceCalib device_calib(const sc_ctx* c) {
+    DeviceCalib d{};
+    d.noise = c->d_noise;
+    d.gain = c->d_gain;
+    d.joins = c->modules ? c->d_joins.as<uint32_t>() : nullptr;
+    d.n_fed = c->n_fed;
+    d.t_seed = c->t_seed;
+    d.t_channel = c->t_channel;
+    d.t_cluster = c->t_cluster;
+    // squares of charges are in [1, 2^36]: within these bounds a product that overflows or
+    // underflows is still on its true side of them
+    const double t = c->t_cluster, t2 = t * t;
+    const bool squares = t == 0.0 || (t >= 0x1p-40 && t <= 0x1p40);
+    d.t2_hi = squares ? (float)(t2 * (1.0 + 0x1p-19)) : __builtin_nanf("");
+    d.t2_lo = squares ? (float)(t2 * (1.0 - 0x1p-19)) : __builtin_nanf("");
+    d.regular_gains = c->regular_gains ? 1u : 0u;
+    return d;
+}
+
 FusedArgs fused_args(sc_ctx* c, Workspace& ws, uint32_t n) {
     FusedArgs a{};
     a.ev = ws.desc.as<EventDesc>();
     a.res = ws.res.as<EventResult>();
     a.tile_state = ws.state.as<unsigned long long>();
     a.queue = ws.queue.as<uint32_t>();
-    a.cal.noise = c->d_noise;
-    a.cal.gain = c->d_gain;
-    a.cal.joins = c->modules ? c->d_joins.as<uint32_t>() : nullptr;
-    a.cal.n_fed = c->n_fed;
-    a.cal.t_seed = c->t_seed;
-    a.cal.t_channel = c->t_channel;
-    a.cal.t_cluster = c->t_cluster;
+    a.cal = device_calib(c);
     a.n_ev = n;
     a.fed_major = c->tuning.fed_major;
     return a;
@@ -1025,19 +1039,27 @@ sc_status sc_create(const sc_calib* cal, const sc_options* opt_in, sc_ctx** out)
     const size_t n_apv = n_strips / kStripsPerApv;
     float* d_noise_raw = nullptr;
     uint8_t* d_bad = nullptr;
-    hipError_t e = hipMalloc(&c->d_noise, sizeof(float) * n_strips);
-    if (e == hipSuccess) e = hipMalloc(&c->d_gain, sizeof(float) * n_apv);
+    float* d_gain_raw = nullptr;
+    for (size_t i = 0; i < n_apv; ++i) {
+        const float g = cal->gain[i];
+        if (g > 0.0f && !(g >= 0x1p-60f && g <= 0x1p60f)) c->regular_gains = false;
+    }
+    hipError_t e = hipMalloc(&c->d_noise, sizeof(float) * n_strips + kNoisePad);
+    if (e == hipSuccess) e = hipMalloc(&c->d_gain, 2 * sizeof(float) * n_apv);
+    if (e == hipSuccess) e = hipMalloc(&d_gain_raw, sizeof(float) * n_apv);
     if (e == hipSuccess) e = hipMalloc(&d_noise_raw, sizeof(float) * n_strips);
     if (e == hipSuccess) e = hipMalloc(&d_bad, n_strips);
-    if (e == hipSuccess) g_allocations.fetch_add(4, std::memory_order_relaxed);
+    if (e == hipSuccess) g_allocations.fetch_add(5, std::memory_order_relaxed);
     if (e == hipSuccess) e = hipMemcpyAsync(d_noise_raw, cal->noise, sizeof(float) * n_strips, hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(c->d_gain, cal->gain, sizeof(float) * n_apv, hipMemcpyHostToDevice, c->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(d_gain_raw, cal->gain, sizeof(float) * n_apv, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(d_bad, cal->bad, n_strips, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess)
-        e = launch_derive_calib(d_noise_raw, c->d_gain, d_bad, cal->n_fed, c->d_noise, c->stream);
+        e = launch_derive_calib(d_noise_raw, d_gain_raw, d_bad, cal->n_fed, c->d_noise, c->d_gain,
+                                c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (d_noise_raw) (void)hipFree(d_noise_raw);
     if (d_bad) (void)hipFree(d_bad);
+    if (d_gain_raw) (void)hipFree(d_gain_raw);
     if (e == hipSuccess) e = c->ws.ensure_batch(64, c->n_fed);
     if (e == hipSuccess) e = static_scratch_for_device(c->device, &c->d_static);
     if (e == hipSuccess)
@@ -1448,13 +1470,7 @@ sc_status sc_process_events_static(sc_ctx* c, const sc_event* ev, uint32_t n, sc
     a.res = reinterpret_cast<EventResult*>(c->d_static + kStaticResOff);
     a.tile_state = reinterpret_cast<unsigned long long*>(c->d_static + kStaticStateOff);
     a.queue = reinterpret_cast<uint32_t*>(c->d_static + kStaticQueueOff);
-    a.cal.noise = c->d_noise;
-    a.cal.gain = c->d_gain;
-    a.cal.joins = c->modules ? c->d_joins.as<uint32_t>() : nullptr;
-    a.cal.n_fed = c->n_fed;
-    a.cal.t_seed = c->t_seed;
-    a.cal.t_channel = c->t_channel;
-    a.cal.t_cluster = c->t_cluster;
+    a.cal = device_calib(c);
     a.n_ev = n;
     a.fed_major = c->tuning.fed_major;
     EventResult* hr = reinterpret_cast<EventResult*>(c->h_static.as<uint8_t>() +
