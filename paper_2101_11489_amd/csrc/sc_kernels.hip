@@ -183,14 +183,6 @@ __device__ __forceinline__ bool joined(Joins J, uint32_t ch) {
 // a module row's needs 18 (768 x 255).
 template <bool kMod> constexpr uint32_t kQShift = kMod ? 18u : 16u;
 
-// The little-endian u16 at byte o of a 4-byte aligned LDS buffer, from the two aligned words
-// around it (one ds_read2): LDS reads at odd addresses stall. The caller keeps o + 1 inside the
-// buffer, which has four readable bytes past its end.
-__device__ __forceinline__ uint32_t lds_u16(const uint8_t* buf, uint32_t o) {
-    const uint32_t* w = reinterpret_cast<const uint32_t*>(buf) + (o >> 2);
-    return __builtin_amdgcn_alignbyte(w[1], w[0], o & 3u) & 0xffffu;
-}
-
 // LDS stage sizes: the small one holds a FED of full-detector events at 5 % occupancy, the
 // large one (fewer resident tiles) a FED of the 6 %, long-cluster stress events.
 constexpr int kStageSmall = 6656, kStageLarge = 10240;
@@ -206,11 +198,11 @@ struct TileSmem {
     alignas(16) float gain[4 * kNch];                    // the FED's APV gains and reciprocals, in pairs
     alignas(16) uint8_t stage[kStageBytes + 4];          // the FED's bytes (+ readable pad)
     uint32_t digi[W * kList];                            // wave w: [w * kList, w * kList + DW)
-    uint32_t ch_pos[kNch + 2];    // payload offsets; [96]: past the last record, + 2; [97]: unused
+    uint32_t ch_pos[kNch + 2];    // payload positions; [96]: past the last record, + 2; [97]: unused
     uint16_t ch_base[kNch + W];   // channel c of wave w at index c + w: digi offset in the group,
                                   // and kChBad if its record is malformed
     uint8_t chunk_first[W][kNch / W + 1];
-    uint32_t walk[4];             // bad_from, trailing, delta (from wave 0), the next tile
+    uint32_t walk[4];             // bad_from, trailing (from wave 0), -, the next tile
     uint32_t grp_cnt[W + 1][3];   // per group: clusters, member ADCs; [W]: the FED's offsets
 };
 constexpr uint32_t kChBad = 0x8000u;
@@ -293,8 +285,8 @@ __device__ __forceinline__ uint32_t stage_bytes(TileSmem<W, DW, S>& sm, uint32_t
 struct WalkResult {
     uint32_t bad_from;   // first channel failing the record-in-FED rule (96: none)
     uint32_t trailing;   // 1 if bytes follow the 96th record
-    uint32_t fits;       // 1 if the whole FED is in the stage
-    uint32_t delta;      // stage offset of FED byte 0 (when fits)
+    uint32_t fits;       // 1 if the whole FED is in the stage, and the payload positions count
+                         // from the stage's start (else from the FED's)
 };
 
 // Stages the FED (and its gains) and walks its length fields; the channel positions and lengths
@@ -311,25 +303,28 @@ __device__ WalkResult stage_and_walk(TileSmem<W, DW, S>& sm, const uint8_t* g, u
             // the walk is a serial chain that the tile's other waves wait for at the next
             // barrier: its wave issues ahead of the CU's other waves meanwhile
             __builtin_amdgcn_s_setprio(3);
-            // lane k (mod 64) keeps channel k's payload position. Branch-free steps whose
-            // serial chain is only read, add, clamp (vector instructions, uniform values). Record k ends where record k + 1's length
-            // field starts, so the lengths and the fit test come from the positions afterwards:
-            // a record fits the FED when its end is <= L, and since ends only grow, the records
-            // that fit come first (past the first one that does not, the reads stay inside the
-            // stage and are unused). Ends stay below 2^23 (96 x (2 + 65535)): no sum wraps.
-            constexpr uint32_t omax = TileSmem<W, DW, S>::kStageBytes - 2;
-            uint32_t pos = 0;
+            // Lane k (mod 64) keeps channel k's payload position in the stage. Branch-free steps
+            // whose serial chain is only clamp, read, two adds (vector instructions, uniform
+            // values): 96 LDS round trips, which bound a tile that is alone on its CU. Record k
+            // ends where record k + 1's length field starts, so the fit test comes from the
+            // positions afterwards: a record fits the FED when its end is <= the FED's, and since
+            // ends only grow, the records that fit come first (past the first one that does not,
+            // the reads stay inside the stage and are unused). Ends stay below 2^23 (96 x (2 +
+            // 65535)): no sum wraps.
+            constexpr uint32_t omax = TileSmem<W, DW, S>::kStageBytes;   // two readable bytes
+            const uint32_t fed_end = delta + L;
+            uint32_t pos = delta;
             uint32_t vpos0 = 0, vpos1 = 0;
             auto step = [&](uint32_t k, uint32_t& vpos) {
-                uint32_t o = pos + delta;
-                o = o < omax ? o : omax;
-                // the chain stays in vector registers (the empty asm keeps P there): the
-                // CU's one scalar unit, shared by its four SIMDs, is busy with the other
-                // waves' scalar work, and a scalar chain would wait for it at every step
-                uint32_t P = lds_u16(sm.stage, o);
-                asm volatile("" : "+v"(P));
-                vpos = __builtin_amdgcn_inverse_ballot_w64(1ull << (k & 63u)) ? pos + 2u : vpos;
-                pos += 2u + P;
+                const uint32_t o = pos < omax ? pos : omax;
+                // the chain stays in vector registers (the empty asm keeps the bytes there): the
+                // CU's one scalar unit, shared by its four SIMDs, is busy with the other waves'
+                // scalar work, and a scalar chain would wait for it at every step
+                uint32_t lo = sm.stage[o], hi = sm.stage[o + 1u];
+                asm volatile("" : "+v"(lo), "+v"(hi));
+                const uint32_t payload = pos + 2u;
+                vpos = __builtin_amdgcn_inverse_ballot_w64(1ull << (k & 63u)) ? payload : vpos;
+                pos = (hi << 8) + (payload + lo);
             };
 #pragma unroll 8
             for (uint32_t k = 0; k < 64u; ++k) step(k, vpos0);
@@ -337,21 +332,21 @@ __device__ WalkResult stage_and_walk(TileSmem<W, DW, S>& sm, const uint8_t* g, u
             for (uint32_t k = 64; k < (uint32_t)kNch; ++k) step(k, vpos1);
             constexpr uint32_t kLast = (uint32_t)kNch - 65u;   // lane of channel 95 in vpos1
             const uint32_t l = lane();
+            // lane 32: where record 95 ends, as a payload position
+            vpos1 = l == kLast + 1u ? pos + 2u : vpos1;
             // (the cross-lane reads are taken by every lane first: inside a conditional
             // expression they would run under a partial exec mask, and a DPP read from a
             // disabled lane returns the fallback value)
             const uint32_t next1 = (uint32_t)__builtin_amdgcn_readlane((int)vpos1, 0);
             const uint32_t nx0 = from_next_lane(vpos0), nx1 = from_next_lane(vpos1);
-            const uint32_t end0 = (l == 63u ? next1 : nx0) - 2u;
-            const uint32_t end1 = l == kLast ? pos : nx1 - 2u;
-            const uint32_t good = popc(__ballot(end0 <= L)) + popc(__ballot(l <= kLast && end1 <= L));
+            const uint32_t end0 = (l == 63u ? next1 : nx0) - 2u, end1 = nx1 - 2u;
+            const uint32_t good = popc(__ballot(end0 <= fed_end)) +
+                                  popc(__ballot(l <= kLast && end1 <= fed_end));
             sm.ch_pos[l] = vpos0;
-            // lane 32: where record 95 ends; the lanes past it write the unused entry
-            vpos1 = l == kLast + 1u ? pos + 2u : vpos1;
+            // (the lanes past channel 95's end write the unused entry)
             sm.ch_pos[l <= kLast + 1u ? 64u + l : (uint32_t)kNch + 1u] = vpos1;
             sm.walk[0] = good;
-            sm.walk[1] = (good == (uint32_t)kNch && pos < L) ? 1u : 0u;
-            sm.walk[2] = delta;
+            sm.walk[1] = (good == (uint32_t)kNch && pos < fed_end) ? 1u : 0u;
             __builtin_amdgcn_s_setprio(0);
         }
     } else {
@@ -381,14 +376,12 @@ __device__ WalkResult stage_and_walk(TileSmem<W, DW, S>& sm, const uint8_t* g, u
             sm.ch_pos[bad_from] = pos + 2;   // where record bad_from - 1 ends
             sm.walk[0] = bad_from;
             sm.walk[1] = (bad_from == (uint32_t)kNch && pos < L) ? 1u : 0u;
-            sm.walk[2] = 0u;
         }
     }
     tile_sync();
     WalkResult w;
     w.bad_from = uni(sm.walk[0]);
     w.trailing = uni(sm.walk[1]);
-    w.delta = uni(sm.walk[2]);
     w.fits = fits ? 1u : 0u;
     return w;
 }
@@ -400,28 +393,34 @@ __device__ __forceinline__ uint32_t payload_len(const TileSmem<W, DW, S>& sm, ui
 }
 
 // ---- record validation, one lane per channel ----------------------------------------------
-// Returns the channel's digi count, or kChBad if it is malformed.
+// Returns the channel's digi count, or kChBad if it is malformed. All the conditions of a record
+// are signs of differences, gathered in one word that is looked at once; the loop's chain is one
+// LDS round trip, an addition and the compare with the record's end (a record that breaks the rules
+// ends the walk one record later, off that chain). With a branch for each condition an iteration
+// took 440 cycles on an idle CU.
 template <class P, int W, int DW, int S>
 __device__ __forceinline__ uint32_t check_channel(TileSmem<W, DW, S>& sm, P src, uint32_t ch,
                                                   const WalkResult& w) {
+    constexpr bool kStaged = std::is_same_v<P, const uint8_t*>;
     if (ch >= w.bad_from) return kChBad;
-    const uint32_t p = sm.ch_pos[ch];
-    const uint32_t len = payload_len(sm, ch);
-    uint32_t q = 0, next_free = 0, nd = 0;
-    bool ok = true;
-    while (q < len) {
-        if (q + 2 > len) { ok = false; break; }
-        // both header bytes are read before any test, and the tests are combined without
-        // short-circuit branches, so a record costs one LDS round trip
-        const uint32_t first = src[p + q], cnt = src[p + q + 1];
-        const bool bad = (cnt == 0u) | (first + cnt > (uint32_t)kStripsPerChannel) |
-                         (first < next_free) | (q + 2 + cnt > len);
-        if (bad) { ok = false; break; }
-        nd += cnt;
-        next_free = first + cnt;
-        q += 2 + cnt;
+    uint32_t a = sm.ch_pos[ch];
+    const uint32_t end = a + payload_len(sm, ch);
+    uint32_t n = end - a;   // - 2 per record: the digis
+    int32_t bad = 0;
+    uint32_t next_free = 0;
+    while (a < end) {
+        // (the second byte of a dangling header is the next length field's, or the stage's pad; in
+        // global memory it may lie past the buffer, and any byte in its place ends the same)
+        const uint32_t first = src[a], cnt = src[kStaged || a + 1u < end ? a + 1u : a];
+        const uint32_t next = a + 2u + cnt, free = first + cnt;
+        const bool stop = bad < 0;
+        bad |= (int32_t)((first - next_free) | ((uint32_t)kStripsPerChannel - free) | (cnt - 1u) |
+                         (end - next));
+        next_free = free;
+        n -= 2u;
+        a = stop ? end : next;
     }
-    return ok ? nd : kChBad;
+    return bad < 0 ? kChBad : n;
 }
 
 // Digi offset of entry i of the channel table (channel c of wave w: c + w) in its group.
@@ -492,30 +491,29 @@ __device__ uint32_t plan_chunks(TileSmem<W, DW, S>& sm, uint32_t w, uint32_t c_l
 // field, and with it the marker, grows, and the last marker at or before a slot is the largest.
 template <bool kMod, int W, int DW, int S>
 __device__ __forceinline__ bool build_markers(TileSmem<W, DW, S>& sm, uint32_t w, uint32_t* dl,
-                                              uint32_t delta, Joins J, uint32_t c0, uint32_t c1) {
+                                              Joins J, uint32_t c0, uint32_t c1) {
     static_assert(TileSmem<W, DW, S>::kStageBytes + 16 < (1 << 14), "marker sources are 14 bits");
     static_assert(DW * 4 < (1 << 18), "position - slot must not borrow past one source step");
     const uint32_t b0 = digi_base(sm, c0 + w);
-    const uint8_t* src = sm.stage + delta;
     bool maybe = false;
     __builtin_amdgcn_s_setprio(2);   // a serial pass that the digi pass waits for
     for (uint32_t ch = c0 + lane(); ch < c1; ch += kWave) {
         const uint32_t bw = sm.ch_base[ch + w];
-        if (bw & kChBad) continue;
-        const uint32_t p = sm.ch_pos[ch];
-        const uint32_t len = payload_len(sm, ch);
+        uint32_t a = sm.ch_pos[ch];
+        const uint32_t end = (bw & kChBad) ? a : a + payload_len(sm, ch);
         uint32_t o = bw - b0;
-        uint32_t q = 0;
+        // source - slot grows by the two header bytes from record to record
+        uint32_t m = kMarker + ((a + 2u - o) << 17) + (ch << 10);
         // the strip a record starts on if it goes on from what is before it
         uint32_t next = kMod && joined(J, ch) ? 0u : kNoStrip;
-        while (q < len) {
-            const uint32_t first = src[p + q], cnt = src[p + q + 1];
+        while (a < end) {
+            const uint32_t first = sm.stage[a], cnt = sm.stage[a + 1u];
             const bool on = first == next;
             maybe |= on;
-            dl[o] = (kMarker | (on ? kMaybeBit : 0u)) +
-                    (((delta + p + q + 2u) << 17 | (ch << 10) | (first << 2)) - o * kSlotStep);
+            dl[o] = m + ((first - o) << 2) + (on ? kMaybeBit : 0u);
+            m += 2u << 17;
+            a += 2u + cnt;
             o += cnt;
-            q += 2 + cnt;
             next = first + cnt;
         }
     }
@@ -1351,7 +1349,7 @@ __device__ void zs_tile(const FusedArgs& A, TileSmem<W, DW, S>& sm, uint32_t e, 
     uint32_t n_chunks;
     const Joins J = fed_joins<kMod>(A.cal, f);
     if (wk.fits) {
-        const uint8_t* st = sm.stage + wk.delta;
+        const uint8_t* st = sm.stage;
         n_chunks = plan_chunks<kMod>(sm, w, c_lo, c_hi, J,
                                      [&](uint32_t ch) { return check_channel(sm, st, ch, wk); },
                                      total);
@@ -1364,10 +1362,9 @@ __device__ void zs_tile(const FusedArgs& A, TileSmem<W, DW, S>& sm, uint32_t e, 
     emit_status(sm, w, c_lo, c_hi, wk.trailing, ev.chan_status, f, &A.res[e].flags);
     uint32_t* dl = sm.digi + w * TileSmem<W, DW, S>::kList;
     const bool fits = wk.fits != 0;
-    const uint32_t delta = wk.delta;
     auto form = [&](uint32_t c0, uint32_t c1, uint32_t nd, uint32_t& n_cl, uint32_t& n_adc) {
         if (fits) {
-            const bool maybe = build_markers<kMod>(sm, w, dl, delta, J, c0, c1);
+            const bool maybe = build_markers<kMod>(sm, w, dl, J, c0, c1);
             form_pass<kMod, true>(dl, nd, sm.stage, A.cal, f, J, maybe, n_cl, n_adc);
         } else {
             build_words(sm, w, dl, gc(g), c0, c1);
@@ -1556,7 +1553,7 @@ __global__ __launch_bounds__(kWave) void unpack_kernel(const uint8_t* zs, const 
     const WalkResult w = stage_and_walk(sm, g, L, nullptr);
     uint32_t total;
     if (w.fits) {
-        const uint8_t* st = sm.stage + w.delta;
+        const uint8_t* st = sm.stage;
         plan_chunks<false>(sm, 0u, 0u, (uint32_t)kNch, Joins{0u, 0u, 0u},
                            [&](uint32_t ch) { return check_channel(sm, st, ch, w); }, total);
     } else {
@@ -1580,7 +1577,7 @@ __global__ __launch_bounds__(kWave) void unpack_kernel(const uint8_t* zs, const 
                 uint8_t* row = rowbuf + lane() * kStripsPerChannel;
                 uint32_t q = 0;
                 if (w.fits) {
-                    const uint8_t* s = sm.stage + w.delta;
+                    const uint8_t* s = sm.stage;
                     while (q < len) {
                         const uint32_t first = s[p + q], cnt = s[p + q + 1];
                         for (uint32_t i = 0; i < cnt; ++i) row[first + i] = s[p + q + 2 + i];
