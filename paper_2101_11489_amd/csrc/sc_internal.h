@@ -61,6 +61,7 @@ struct FusedArgs {
     DeviceCalib cal;
     uint32_t n_ev;
     uint32_t fed_major;              // tile order: 0 event-major, 1 FED-major, 2 FED-major per XCD
+    uint32_t any_status;             // some event wants its channels' status
 };
 
 // Scratch of the allocation-free batch call (sc_process_events_static), a file-scope device

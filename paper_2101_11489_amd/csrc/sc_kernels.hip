@@ -43,10 +43,10 @@ hipError_t static_scratch_address(void** ptr) {
 namespace {
 
 constexpr uint32_t kSpinLimit = 1u << 22;   // look-back wait bound (seconds of sleeping)
+constexpr uint32_t kWalkPolls = 6;          // look-back polls that fit beside a walk
 constexpr uint32_t kXcds = 8;               // XCDs of the device (queues of tile order 2)
 constexpr int kNch = kChannelsPerFed;
 constexpr int kStripsPerFed = kChannelsPerFed * kStripsPerChannel;
-constexpr uint32_t kGainVecs = 2 * kNch / 4;   // half a FED's APV gain pairs as 16-byte vectors
 
 // ---- global-address-space views (plain global loads/stores, no flat addressing) ------------
 #ifndef SC_GLOBAL_AS
@@ -56,6 +56,12 @@ template <class T> using gconst = SC_GLOBAL_AS const T;
 template <class T> using gmut = SC_GLOBAL_AS T;
 template <class T> __device__ __forceinline__ gconst<T>* gc(const T* p) { return (gconst<T>*)p; }
 template <class T> __device__ __forceinline__ gmut<T>* gm(T* p) { return (gmut<T>*)p; }
+
+// The element `bytes` past a uniform base: a scalar base and one 32-bit offset, no 64-bit addition
+// per lane. (An event has at most 20000 x 96 channels of 128 clusters: 16 bytes each stay below 2^32.)
+template <class T> __device__ __forceinline__ gmut<T>* at_offset(gmut<T>* base, uint32_t bytes) {
+    return reinterpret_cast<gmut<T>*>(reinterpret_cast<gmut<uint8_t>*>(base) + bytes);
+}
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // 16-byte global accesses
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));   // two digi words
@@ -164,6 +170,10 @@ __device__ __forceinline__ uint32_t d_adc(uint32_t d) { return d & 255u; }
 __device__ __forceinline__ uint32_t d_strip(uint32_t d) { return (d >> 10) & 255u; }
 __device__ __forceinline__ uint32_t d_ch(uint32_t d) { return (d >> 18) & 127u; }
 __device__ __forceinline__ uint32_t d_pos(uint32_t d) { return (d >> 10) & 0x7fffu; }
+// x * y + z for x, y < 2^24 (a full-rate instruction; v_mul_lo_u32 runs at a quarter of it)
+__device__ __forceinline__ uint32_t mad24(uint32_t x, uint32_t y, uint32_t z) {
+    return __umul24(x, y) + z;
+}
 // a lane's bit of a wave mask, as a select condition
 __device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
@@ -201,10 +211,18 @@ struct TileSmem {
     uint32_t ch_pos[kNch + 2];    // payload positions; [96]: past the last record, + 2; [97]: unused
     uint16_t ch_base[kNch + W];   // channel c of wave w at index c + w: digi offset in the group,
                                   // and kChBad if its record is malformed
-    uint8_t chunk_first[W][kNch / W + 1];
-    uint32_t walk[4];             // bad_from, trailing (from wave 0), -, the next tile
-    uint32_t grp_cnt[W + 1][3];   // per group: clusters, member ADCs; [W]: the FED's offsets
+    // chunks of a group: two in a row hold more than DW digis, so there are few
+    static constexpr int kGroupChans = kNch / W;
+    static constexpr int kMaxChunks = 2 * kGroupChans * kStripsPerChannel / DW + 1 < kGroupChans
+                                          ? 2 * kGroupChans * kStripsPerChannel / DW + 1
+                                          : kGroupChans;
+    uint8_t chunk_first[W][kMaxChunks + 1];
+    uint32_t walk[2];             // bad_from, trailing
+    uint32_t next[5];             // the next tile: event (kNoTile: none), FED, bytes, address
+    uint32_t grp_cnt[W + 1][3];   // per group: clusters, member ADCs, chunks; [W]: the FED's
+                                  // offsets, look-back failure
 };
+constexpr uint32_t kNoTile = 0xffffffffu;
 constexpr uint32_t kChBad = 0x8000u;
 
 // Two-wave tiles of 2880 digis fit eight to a CU (160 KiB of LDS).
@@ -223,63 +241,70 @@ __device__ __forceinline__ uint32_t wave_index() {
     else return uni(threadIdx.x >> 6);
 }
 
-// The FED's 192 pairs of APV gain and reciprocal as 96 16-byte vectors, two per lane (lanes past
-// the 48th repeat the last ones).
+// The APV gains of a wave's channels (pairs of gain and reciprocal), as 16-byte vectors.
+template <int W>
 struct GainVecs {
-    u32x4 a, b;
+    static constexpr uint32_t kCount = kNch / W;   // 4 floats per channel
+    static constexpr int kPerLane = (kCount + kWave - 1) / kWave;
+    u32x4 v[kPerLane];
 };
-__device__ __forceinline__ GainVecs load_gain_vecs(const float* gains) {
-    const uint32_t i = lane() < kGainVecs ? lane() : kGainVecs - 1u;
-    gconst<u32x4>* g = gc(reinterpret_cast<const u32x4*>(gains));
-    return GainVecs{g[i], g[i + kGainVecs]};
+// (lanes past the last vector repeat it)
+template <int W>
+__device__ __forceinline__ uint32_t gain_index(int i) {
+    const uint32_t k = (uint32_t)i * kWave + lane();
+    return k < GainVecs<W>::kCount ? k : GainVecs<W>::kCount - 1u;
+}
+template <int W>
+__device__ __forceinline__ void load_gains(GainVecs<W>& g, const float* gains, uint32_t fed, uint32_t w) {
+    gconst<u32x4>* src = gc(reinterpret_cast<const u32x4*>(gains)) + fed * kNch + w * GainVecs<W>::kCount;
+#pragma unroll
+    for (int i = 0; i < GainVecs<W>::kPerLane; ++i) g.v[i] = src[gain_index<W>(i)];
 }
 template <int W, int DW, int S>
-__device__ __forceinline__ void store_gain_vecs(TileSmem<W, DW, S>& sm, const GainVecs& v) {
-    const uint32_t i = lane() < kGainVecs ? lane() : kGainVecs - 1u;
-    u32x4* g = reinterpret_cast<u32x4*>(sm.gain);
-    g[i] = v.a;
-    g[i + kGainVecs] = v.b;
+__device__ __forceinline__ void store_gains(TileSmem<W, DW, S>& sm, const GainVecs<W>& g, uint32_t w) {
+    u32x4* dst = reinterpret_cast<u32x4*>(sm.gain) + w * GainVecs<W>::kCount;
+#pragma unroll
+    for (int i = 0; i < GainVecs<W>::kPerLane; ++i) dst[gain_index<W>(i)] = g.v[i];
 }
 
 // ---- staging -----------------------------------------------------------------------------
-// Copy n bytes at gsrc into the stage so that gsrc[i] lands at stage[delta + i]; returns delta.
-// NT threads take part (thread index t): all waves of the tile, or wave 0 alone. Loads are
-// aligned 16-byte pieces, all issued before the first is stored; each piece holds at least one
-// byte of [gsrc, gsrc+n), so it lies inside the 4 KiB page of a byte of the buffer. With gains
-// != nullptr the FED's APV gains are loaded in the same batch (by wave 0).
-template <int NT, int W, int DW, int S>
-__device__ __forceinline__ uint32_t stage_bytes(TileSmem<W, DW, S>& sm, uint32_t t,
-                                                const uint8_t* gsrc, uint32_t n,
-                                                const float* gains) {
-    constexpr int K = (TileSmem<W, DW, S>::kStageBytes + 16 * NT - 1) / (16 * NT);
-    const uintptr_t a = reinterpret_cast<uintptr_t>(gsrc);
-    const uintptr_t a0 = a & ~uintptr_t(15);
-    const uint32_t delta = (uint32_t)(a - a0);
-    const uint32_t nchunks = n ? (delta + n + 15u) >> 4 : 0u;
-    gconst<u32x4>* s4 = gc(reinterpret_cast<const u32x4*>(a0));
-    u32x4* d4 = reinterpret_cast<u32x4*>(sm.stage);
-    const bool lead = wave_index<W>() == 0u;
-    GainVecs gv = {};
-    if (gains && lead) gv = load_gain_vecs(gains);
-    if (nchunks) {
-        // every thread loads K pieces (indices past the end repeat the last piece), then stores
-        // the ones that exist
-        const uint32_t last = nchunks - 1u;
-        u32x4 r[K];
+// The 16-byte aligned pieces that cover bytes [src, src + n), n <= kStageBytes - 15, held by NT
+// threads (t: the thread's index), all loaded before the first is put into the stage, where src[i]
+// lands at stage[delta + i]. Every piece holds at least one byte of the range, so it lies inside
+// the 4 KiB page of a byte of the buffer.
+template <int S, int NT>
+struct Pieces {
+    static constexpr int K = (S + 16 * NT - 1) / (16 * NT);
+    u32x4 r[K];
+    static __device__ __forceinline__ uint32_t delta(const uint8_t* src) {
+        return (uint32_t)(reinterpret_cast<uintptr_t>(src) & 15u);
+    }
+    static __device__ __forceinline__ uint32_t count(const uint8_t* src, uint32_t n) {
+        return n ? (delta(src) + n + 15u) >> 4 : 0u;
+    }
+    __device__ __forceinline__ void load(const uint8_t* src, uint32_t n, uint32_t t) {
+        const uint32_t pieces = count(src, n);
+        if (!pieces) return;
+        // every thread loads K pieces (indices past the end repeat the last piece)
+        const uint32_t last = pieces - 1u;
+        gconst<u32x4>* s4 = gc(reinterpret_cast<const u32x4*>(src - delta(src)));
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const uint32_t c = t + (uint32_t)(k * NT);
             r[k] = s4[c < last ? c : last];
         }
+    }
+    __device__ __forceinline__ void store(uint8_t* stage, const uint8_t* src, uint32_t n,
+                                          uint32_t t) const {
+        const uint32_t pieces = count(src, n);
+        u32x4* d4 = reinterpret_cast<u32x4*>(stage);
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const uint32_t c = t + (uint32_t)(k * NT);
-            if (c < nchunks) d4[c] = r[k];
+            if (c < pieces) d4[c] = r[k];
         }
     }
-    if (gains && lead) store_gain_vecs(sm, gv);
-    return delta;
-}
+};
 
 // ---- channel map: the 96 length fields (uniform walk by wave 0) ----------------------------
 struct WalkResult {
@@ -289,101 +314,100 @@ struct WalkResult {
                          // from the stage's start (else from the FED's)
 };
 
-// Stages the FED (and its gains) and walks its length fields; the channel positions and lengths
-// go to LDS. Every wave of the tile calls it (it contains the tile's barriers).
+// Walks the length fields of a FED of L bytes that lies in the stage from delta on; by one wave.
 template <int W, int DW, int S>
-__device__ WalkResult stage_and_walk(TileSmem<W, DW, S>& sm, const uint8_t* g, uint32_t L,
-                                     const float* gains) {
+__device__ __forceinline__ void walk_staged(TileSmem<W, DW, S>& sm, uint32_t delta, uint32_t L) {
+    // Lane k (mod 64) keeps channel k's payload position in the stage. Branch-free steps
+    // whose serial chain is only clamp, read, two adds (vector instructions, uniform
+    // values): 96 LDS round trips, which bound a tile that is alone on its CU. Record k
+    // ends where record k + 1's length field starts, so the fit test comes from the
+    // positions afterwards: a record fits the FED when its end is <= the FED's, and since
+    // ends only grow, the records that fit come first (past the first one that does not,
+    // the reads stay inside the stage and are unused). Ends stay below 2^23 (96 x (2 +
+    // 65535)): no sum wraps.
+    constexpr uint32_t omax = TileSmem<W, DW, S>::kStageBytes + 2;   // two readable bytes before it
+    const uint32_t fed_end = delta + L;
+    uint32_t pos = delta + 2u;   // past the length field of record k
+    uint32_t vpos0 = 0, vpos1 = 0;
+    auto step = [&](uint32_t k, uint32_t& vpos) {
+        const uint32_t o = pos < omax ? pos : omax;
+        // the chain stays in vector registers (the empty asm keeps the bytes there): the
+        // CU's one scalar unit, shared by its four SIMDs, is busy with the other waves'
+        // scalar work, and a scalar chain would wait for it at every step
+        uint32_t lo = sm.stage[o - 2u], hi = sm.stage[o - 1u];
+        asm volatile("" : "+v"(lo), "+v"(hi));
+        vpos = __builtin_amdgcn_inverse_ballot_w64(1ull << (k & 63u)) ? pos : vpos;
+        pos = (hi << 8) + (pos + lo + 2u);
+    };
+#pragma unroll 8
+    for (uint32_t k = 0; k < 64u; ++k) step(k, vpos0);
+#pragma unroll 8
+    for (uint32_t k = 64; k < (uint32_t)kNch; ++k) step(k, vpos1);
+    constexpr uint32_t kLast = (uint32_t)kNch - 65u;   // lane of channel 95 in vpos1
+    const uint32_t l = lane();
+    // lane 32: where record 95 ends, as a payload position
+    vpos1 = l == kLast + 1u ? pos : vpos1;
+    // (the cross-lane reads are taken by every lane first: inside a conditional
+    // expression they would run under a partial exec mask, and a DPP read from a
+    // disabled lane returns the fallback value)
+    const uint32_t next1 = (uint32_t)__builtin_amdgcn_readlane((int)vpos1, 0);
+    const uint32_t nx0 = from_next_lane(vpos0), nx1 = from_next_lane(vpos1);
+    const uint32_t end0 = (l == 63u ? next1 : nx0) - 2u, end1 = nx1 - 2u;
+    const uint32_t good = popc(__ballot(end0 <= fed_end)) +
+                          popc(__ballot(l <= kLast && end1 <= fed_end));
+    sm.ch_pos[l] = vpos0;
+    // (the lanes past channel 95's end write the unused entry)
+    sm.ch_pos[l <= kLast + 1u ? 64u + l : (uint32_t)kNch + 1u] = vpos1;
+    sm.walk[0] = good;
+    sm.walk[1] = (good == (uint32_t)kNch && pos - 2u < fed_end) ? 1u : 0u;
+}
+
+// The same for a FED larger than the stage: windows of it are staged in turn; the records are then
+// read from global memory.
+template <int W, int DW, int S>
+__device__ __forceinline__ void walk_windows(TileSmem<W, DW, S>& sm, const uint8_t* g, uint32_t L) {
     constexpr uint32_t cap = TileSmem<W, DW, S>::kStageData;
-    const bool fits = L <= cap;
-    if (fits) {
-        const uint32_t delta = stage_bytes<kWave * W>(sm, threadIdx.x, g, L, gains);
-        tile_sync();
-        if (wave_index<W>() == 0u) {
-            // the walk is a serial chain that the tile's other waves wait for at the next
-            // barrier: its wave issues ahead of the CU's other waves meanwhile
-            __builtin_amdgcn_s_setprio(3);
-            // Lane k (mod 64) keeps channel k's payload position in the stage. Branch-free steps
-            // whose serial chain is only clamp, read, two adds (vector instructions, uniform
-            // values): 96 LDS round trips, which bound a tile that is alone on its CU. Record k
-            // ends where record k + 1's length field starts, so the fit test comes from the
-            // positions afterwards: a record fits the FED when its end is <= the FED's, and since
-            // ends only grow, the records that fit come first (past the first one that does not,
-            // the reads stay inside the stage and are unused). Ends stay below 2^23 (96 x (2 +
-            // 65535)): no sum wraps.
-            constexpr uint32_t omax = TileSmem<W, DW, S>::kStageBytes;   // two readable bytes
-            const uint32_t fed_end = delta + L;
-            uint32_t pos = delta;
-            uint32_t vpos0 = 0, vpos1 = 0;
-            auto step = [&](uint32_t k, uint32_t& vpos) {
-                const uint32_t o = pos < omax ? pos : omax;
-                // the chain stays in vector registers (the empty asm keeps the bytes there): the
-                // CU's one scalar unit, shared by its four SIMDs, is busy with the other waves'
-                // scalar work, and a scalar chain would wait for it at every step
-                uint32_t lo = sm.stage[o], hi = sm.stage[o + 1u];
-                asm volatile("" : "+v"(lo), "+v"(hi));
-                const uint32_t payload = pos + 2u;
-                vpos = __builtin_amdgcn_inverse_ballot_w64(1ull << (k & 63u)) ? payload : vpos;
-                pos = (hi << 8) + (payload + lo);
-            };
-#pragma unroll 8
-            for (uint32_t k = 0; k < 64u; ++k) step(k, vpos0);
-#pragma unroll 8
-            for (uint32_t k = 64; k < (uint32_t)kNch; ++k) step(k, vpos1);
-            constexpr uint32_t kLast = (uint32_t)kNch - 65u;   // lane of channel 95 in vpos1
-            const uint32_t l = lane();
-            // lane 32: where record 95 ends, as a payload position
-            vpos1 = l == kLast + 1u ? pos + 2u : vpos1;
-            // (the cross-lane reads are taken by every lane first: inside a conditional
-            // expression they would run under a partial exec mask, and a DPP read from a
-            // disabled lane returns the fallback value)
-            const uint32_t next1 = (uint32_t)__builtin_amdgcn_readlane((int)vpos1, 0);
-            const uint32_t nx0 = from_next_lane(vpos0), nx1 = from_next_lane(vpos1);
-            const uint32_t end0 = (l == 63u ? next1 : nx0) - 2u, end1 = nx1 - 2u;
-            const uint32_t good = popc(__ballot(end0 <= fed_end)) +
-                                  popc(__ballot(l <= kLast && end1 <= fed_end));
-            sm.ch_pos[l] = vpos0;
-            // (the lanes past channel 95's end write the unused entry)
-            sm.ch_pos[l <= kLast + 1u ? 64u + l : (uint32_t)kNch + 1u] = vpos1;
-            sm.walk[0] = good;
-            sm.walk[1] = (good == (uint32_t)kNch && pos < fed_end) ? 1u : 0u;
-            __builtin_amdgcn_s_setprio(0);
+    uint32_t pos = 0, bad_from = kNch, win = 0, win_n = 0, delta = 0;
+    for (uint32_t k = 0; k < (uint32_t)kNch; ++k) {
+        if (pos + 2 > L) { bad_from = k; break; }
+        if (pos + 2 > win + win_n) {
+            wave_sync();
+            win = pos;
+            win_n = (L - win) < cap ? (L - win) : cap;
+            Pieces<TileSmem<W, DW, S>::kStageBytes, kWave> p;
+            p.load(g + win, win_n, lane());
+            p.store(sm.stage, g + win, win_n, lane());
+            delta = p.delta(g + win);
+            wave_sync();
         }
-    } else {
-        // larger than the stage: wave 0 stages windows of the FED in turn and walks them; the
-        // records are then read from global memory
-        if (gains) {
-            if (wave_index<W>() == 0u) store_gain_vecs(sm, load_gain_vecs(gains));
-        }
-        if (wave_index<W>() == 0u) {
-            uint32_t pos = 0, bad_from = kNch, win = 0, win_n = 0, delta = 0;
-            for (uint32_t k = 0; k < (uint32_t)kNch; ++k) {
-                if (pos + 2 > L) { bad_from = k; break; }
-                if (pos + 2 > win + win_n) {
-                    wave_sync();
-                    win = pos;
-                    win_n = (L - win) < cap ? (L - win) : cap;
-                    delta = stage_bytes<kWave>(sm, lane(), g + win, win_n, nullptr);
-                    wave_sync();
-                }
-                const uint32_t o = pos - win + delta;
-                const uint32_t P =
-                    uni((uint32_t)sm.stage[o] | ((uint32_t)sm.stage[o + 1] << 8));
-                if (pos + 2 + P > L) { bad_from = k; break; }
-                sm.ch_pos[k] = pos + 2;   // the same values from every lane
-                pos += 2 + P;
-            }
-            sm.ch_pos[bad_from] = pos + 2;   // where record bad_from - 1 ends
-            sm.walk[0] = bad_from;
-            sm.walk[1] = (bad_from == (uint32_t)kNch && pos < L) ? 1u : 0u;
-        }
+        const uint32_t o = pos - win + delta;
+        const uint32_t P = uni((uint32_t)sm.stage[o] | ((uint32_t)sm.stage[o + 1] << 8));
+        if (pos + 2 + P > L) { bad_from = k; break; }
+        sm.ch_pos[k] = pos + 2;   // the same values from every lane
+        pos += 2 + P;
     }
-    tile_sync();
-    WalkResult w;
-    w.bad_from = uni(sm.walk[0]);
-    w.trailing = uni(sm.walk[1]);
-    w.fits = fits ? 1u : 0u;
-    return w;
+    sm.ch_pos[bad_from] = pos + 2;   // where record bad_from - 1 ends
+    sm.walk[0] = bad_from;
+    sm.walk[1] = (bad_from == (uint32_t)kNch && pos < L) ? 1u : 0u;
+}
+
+// Whether a FED of L bytes is staged whole.
+template <int W, int DW, int S>
+__device__ __forceinline__ bool fits_stage(const TileSmem<W, DW, S>&, uint32_t L) {
+    return L <= (uint32_t)TileSmem<W, DW, S>::kStageData;
+}
+
+template <int W, int DW, int S>
+__device__ __forceinline__ void walk_fed(TileSmem<W, DW, S>& sm, const uint8_t* g, uint32_t L) {
+    __builtin_amdgcn_s_setprio(3);   // the tile's other waves wait for it
+    if (fits_stage(sm, L)) walk_staged(sm, Pieces<S, kWave * W>::delta(g), L);
+    else walk_windows(sm, g, L);
+    __builtin_amdgcn_s_setprio(0);
+}
+
+template <int W, int DW, int S>
+__device__ __forceinline__ WalkResult walk_result(const TileSmem<W, DW, S>& sm, uint32_t L) {
+    return WalkResult{uni(sm.walk[0]), uni(sm.walk[1]), fits_stage(sm, L) ? 1u : 0u};
 }
 
 // Payload bytes of channel ch (below the walk's bad_from): its record ends where the next begins.
@@ -393,34 +417,40 @@ __device__ __forceinline__ uint32_t payload_len(const TileSmem<W, DW, S>& sm, ui
 }
 
 // ---- record validation, one lane per channel ----------------------------------------------
-// Returns the channel's digi count, or kChBad if it is malformed. All the conditions of a record
-// are signs of differences, gathered in one word that is looked at once; the loop's chain is one
-// LDS round trip, an addition and the compare with the record's end (a record that breaks the rules
-// ends the walk one record later, off that chain). With a branch for each condition an iteration
-// took 440 cycles on an idle CU.
+// Returns the channel's digi count, or kChBad if it is malformed; near: the smallest distance of a
+// record's first strip from the end of the record before it (0: they are adjacent; `on`: the first
+// record's is taken from strip 0). Inside the loop a record is only tested for order and for holding
+// a digi: then the strips only grow, and that the last record ends at the channel's end or before,
+// and at the payload's end, is seen after it. A valid channel has at most 256 records of 3 bytes, so
+// no longer payload is walked. The loop's chain is one LDS round trip, an addition and the compare
+// with the payload's end; with a branch for each rule an iteration took 440 cycles on an idle CU.
 template <class P, int W, int DW, int S>
 __device__ __forceinline__ uint32_t check_channel(TileSmem<W, DW, S>& sm, P src, uint32_t ch,
-                                                  const WalkResult& w) {
+                                                  const WalkResult& w, bool on, uint32_t& near) {
     constexpr bool kStaged = std::is_same_v<P, const uint8_t*>;
     if (ch >= w.bad_from) return kChBad;
     uint32_t a = sm.ch_pos[ch];
-    const uint32_t end = a + payload_len(sm, ch);
-    uint32_t n = end - a;   // - 2 per record: the digis
+    const uint32_t n = payload_len(sm, ch), end = a + n;
+    if (n > 3u * kStripsPerChannel) return kChBad;
+    uint32_t nd = 0u, free = 0u, gap = kNoStrip;
     int32_t bad = 0;
-    uint32_t next_free = 0;
+    // the strip that the next record may start on; the first one's distance from it is not 0
+    // unless it may go on from the channel before
+    uint32_t next_free = on ? 0u : kNoStrip;
     while (a < end) {
         // (the second byte of a dangling header is the next length field's, or the stage's pad; in
         // global memory it may lie past the buffer, and any byte in its place ends the same)
         const uint32_t first = src[a], cnt = src[kStaged || a + 1u < end ? a + 1u : a];
-        const uint32_t next = a + 2u + cnt, free = first + cnt;
-        const bool stop = bad < 0;
-        bad |= (int32_t)((first - next_free) | ((uint32_t)kStripsPerChannel - free) | (cnt - 1u) |
-                         (end - next));
-        next_free = free;
-        n -= 2u;
-        a = stop ? end : next;
+        const uint32_t d = first - next_free;
+        bad |= (int32_t)(d | (cnt - 1u));
+        gap = __builtin_elementwise_min(gap, d);
+        next_free = free = first + cnt;
+        nd += cnt;
+        a += 2u + cnt;
     }
-    return bad < 0 ? kChBad : n;
+    near = gap;
+    const bool wrong = (bad < 0) | (free > (uint32_t)kStripsPerChannel) | (a != end);
+    return wrong ? kChBad : nd;
 }
 
 // Digi offset of entry i of the channel table (channel c of wave w: c + w) in its group.
@@ -430,20 +460,28 @@ __device__ __forceinline__ uint32_t digi_base(const TileSmem<W, DW, S>& sm, uint
 }
 
 // The channel group [c_lo, c_hi) of wave w: digi counts -> offsets in the group (ch_base) and
-// its split into chunks of at most DW digis; returns the number of chunks. Wave-local.
+// its split into chunks of at most DW digis; returns the number of chunks and whether any channel is
+// malformed, and any record may go on from the one before it: its first strip follows that one's last
+// (runs of more than 255 strips are written so) or, in a module row, is strip 0 of a joined
+// channel. Wave-local.
 template <bool kMod, int W, int DW, int S, class CountFn>
 __device__ uint32_t plan_chunks(TileSmem<W, DW, S>& sm, uint32_t w, uint32_t c_lo, uint32_t c_hi,
-                                Joins J, CountFn count, uint32_t& total) {
+                                Joins J, CountFn count, bool& any_bad, bool& any_on) {
     uint32_t carry = 0;
+    any_bad = any_on = false;
     for (uint32_t base = c_lo; base < c_hi; base += kWave) {
         const uint32_t ch = base + lane();
-        const uint32_t nd = ch < c_hi ? count(ch) : 0u;   // kChBad: malformed, no digis
+        uint32_t near = kNoStrip;
+        const bool on = kMod && joined(J, ch);
+        const uint32_t nd = ch < c_hi ? count(ch, on, near) : 0u;   // kChBad: malformed, no digis
         uint32_t tot;
         const uint32_t ex = wave_excl_scan(nd & ~kChBad, tot);
         if (ch < c_hi) sm.ch_base[ch + w] = (uint16_t)((carry + ex) | (nd & kChBad));
         carry += tot;
+        any_bad |= __ballot((nd & kChBad) != 0u) != 0ull;
+        any_on |= __ballot(near == 0u) != 0ull;
     }
-    total = carry;
+    const uint32_t total = carry;
     sm.ch_base[c_hi + w] = (uint16_t)carry;   // uniform stores from every lane
     uint8_t* cf = sm.chunk_first[w];
     uint32_t n_chunks = 1;
@@ -483,44 +521,50 @@ __device__ uint32_t plan_chunks(TileSmem<W, DW, S>& sm, uint32_t w, uint32_t c_l
 }
 
 // The records of channels [c0, c1) of a staged FED, as markers in the digi list dl (one lane per
-// channel). Returns whether any record may go on from the record before it: its first strip follows
-// the last one of the record before (runs of more than 255 strips are written so) or, in a module
-// row, it starts at strip 0 of a joined channel.
+// channel). any_on (uniform): some record may go on from the one before it, and such records get
+// kMaybeBit.
 // Records take their slots in the order of their bytes, and from one record to the next the source
 // grows by the first one's digis plus a 2-byte header, the slot by the digis alone: the source
 // field, and with it the marker, grows, and the last marker at or before a slot is the largest.
 template <bool kMod, int W, int DW, int S>
-__device__ __forceinline__ bool build_markers(TileSmem<W, DW, S>& sm, uint32_t w, uint32_t* dl,
-                                              Joins J, uint32_t c0, uint32_t c1) {
+__device__ __forceinline__ void build_markers(TileSmem<W, DW, S>& sm, uint32_t w, uint32_t* dl,
+                                              Joins J, bool any_on, uint32_t c0, uint32_t c1) {
     static_assert(TileSmem<W, DW, S>::kStageBytes + 16 < (1 << 14), "marker sources are 14 bits");
     static_assert(DW * 4 < (1 << 18), "position - slot must not borrow past one source step");
     const uint32_t b0 = digi_base(sm, c0 + w);
-    bool maybe = false;
     __builtin_amdgcn_s_setprio(2);   // a serial pass that the digi pass waits for
     for (uint32_t ch = c0 + lane(); ch < c1; ch += kWave) {
         const uint32_t bw = sm.ch_base[ch + w];
-        uint32_t a = sm.ch_pos[ch];
-        const uint32_t end = (bw & kChBad) ? a : a + payload_len(sm, ch);
+        // (a channel past the walk's last good one has no position)
+        uint32_t a = (bw & kChBad) ? 0u : sm.ch_pos[ch];
+        const uint32_t end = (bw & kChBad) ? 0u : a + payload_len(sm, ch);
         uint32_t o = bw - b0;
         // source - slot grows by the two header bytes from record to record
         uint32_t m = kMarker + ((a + 2u - o) << 17) + (ch << 10);
-        // the strip a record starts on if it goes on from what is before it
-        uint32_t next = kMod && joined(J, ch) ? 0u : kNoStrip;
-        while (a < end) {
-            const uint32_t first = sm.stage[a], cnt = sm.stage[a + 1u];
-            const bool on = first == next;
-            maybe |= on;
-            dl[o] = m + ((first - o) << 2) + (on ? kMaybeBit : 0u);
-            m += 2u << 17;
-            a += 2u + cnt;
-            o += cnt;
-            next = first + cnt;
-        }
+        // each record's header is read while the one before is put down (the last read is of the
+        // bytes after the channel, unused)
+        uint32_t first = sm.stage[a], cnt = sm.stage[a + 1u];
+        auto records = [&](auto with_on, uint32_t next) {
+            while (a < end) {
+                a += 2u + cnt;
+                const uint32_t first2 = sm.stage[a], cnt2 = sm.stage[a + 1u];
+                uint32_t marker = m + ((first - o) << 2);
+                if constexpr (decltype(with_on)::value) {
+                    marker += first == next ? kMaybeBit : 0u;
+                    next = first + cnt;
+                }
+                dl[o] = marker;
+                m += 2u << 17;
+                o += cnt;
+                first = first2;
+                cnt = cnt2;
+            }
+        };
+        if (any_on) records(std::true_type{}, kMod && joined(J, ch) ? 0u : kNoStrip);
+        else        records(std::false_type{}, 0u);
     }
     __builtin_amdgcn_s_setprio(0);
-    const bool any = __ballot(maybe) != 0ull;
     wave_sync();
-    return any;
 }
 
 // The same channels from global memory (a FED larger than the stage), as digi words: one lane per
@@ -885,7 +929,8 @@ __device__ uint32_t form_long_chain(uint32_t* dl, uint32_t base, uint32_t nd, co
     return j;
 }
 
-// Forming over the digi list dl[0, nd) of a FED, the next window's loads in flight.
+// Forming over the digi list dl[0, nd) of a FED, the next window's loads in flight (without module
+// rows).
 template <bool kMod, bool kMarkers>
 __device__ __forceinline__ void form_pass(uint32_t* dl, uint32_t nd, const uint8_t* stage,
                                           const DeviceCalib& cal, uint32_t fed, Joins J, bool maybe,
@@ -911,9 +956,14 @@ __device__ __forceinline__ void form_pass(uint32_t* dl, uint32_t nd, const uint8
                 form_window<kMod>(dl, x, cal, ncl, nadc);
                 break;
             }
-            const Window next = load(base);
-            form_window<kMod>(dl, x, cal, ncl, nadc);
-            x = next;
+            if constexpr (kMod) {   // (the registers do not reach for two windows)
+                form_window<kMod>(dl, x, cal, ncl, nadc);
+                x = load(base);
+            } else {
+                const Window next = load(base);
+                form_window<kMod>(dl, x, cal, ncl, nadc);
+                x = next;
+            }
         }
     }
     n_cl = ncl;
@@ -977,7 +1027,10 @@ __device__ __forceinline__ uint32_t corrected_adc(uint32_t adc, float g, float r
     const float a = (float)adc;
     const float q0 = a * r;
     float q = __builtin_fmaf(__builtin_fmaf(-q0, g, a), r, q0);
-    if (!regular) q = a / g;   // uniform
+    if (!regular) {   // uniform; the empty asm keeps the division from being taken in any case
+        asm volatile("");
+        q = a / g;
+    }
     return (uint32_t)__builtin_fminf(__builtin_rintf(q), 65535.0f);
 }
 
@@ -1088,7 +1141,7 @@ __device__ __forceinline__ void write_pass(const TileSmem<W, DW, S>& sm, const u
             s[k] = d_strip(d[k]);
             const bool on = k && in_mask(K[k]);
             if constexpr (kMod) {
-                const uint32_t m = d_pos(d[k]) * c[k];
+                const uint32_t m = __umul24(d_pos(d[k]), c[k]);
                 v[0][k] = c[k] + (on ? v[0][k ? k - 1 : 0] : 0u);
                 v[1][k] = (m & 0xffffu) + (on ? v[1][k ? k - 1 : 0] : 0u);
                 v[2][k] = (m >> 16) + (on ? v[2][k ? k - 1 : 0] : 0u);
@@ -1096,7 +1149,7 @@ __device__ __forceinline__ void write_pass(const TileSmem<W, DW, S>& sm, const u
             } else {
                 // at most 256 x 65535 < 2^24; a width of 256 reads as 0
                 v[0][k] = c[k] + (1u << 24) + (on ? v[0][k ? k - 1 : 0] : 0u);
-                v[1][k] = s[k] * c[k] + (on ? v[1][k ? k - 1 : 0] : 0u);
+                v[1][k] = mad24(s[k], c[k], on ? v[1][k ? k - 1 : 0] : 0u);
             }
         }
         carry_sums(v, K);
@@ -1156,35 +1209,41 @@ __device__ __forceinline__ void write_pass(const TileSmem<W, DW, S>& sm, const u
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-            if (in_mask(mem[k])) adc_out[ra[k]] = (uint16_t)c[k];
+            if (in_mask(mem[k])) *at_offset(adc_out, 2u * ra[k]) = (uint16_t)c[k];
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
-            if (in_mask(any[p])) cl_out[rr[2 * p]] = rec1[p];
-            if (in_mask(both[p])) cl_out[rr[2 * p + 1]] = rec2[p];
+            if (in_mask(any[p])) *at_offset(cl_out, 16u * rr[2 * p]) = rec1[p];
+            if (in_mask(both[p])) *at_offset(cl_out, 16u * rr[2 * p + 1]) = rec2[p];
         }
     }
     wave_sync();
 }
 
 // ---- decoupled look-back over the FEDs of one event -----------------------------------------
-// Publishes this FED's counts and sums those of the FEDs before it: lane i reads the word of
-// FED top-i, so 64 predecessors are inspected per load; only words not yet published are waited
-// for. Only the counts travel through these words, so relaxed atomics suffice. All values
-// steering the loop are uniform.
-__device__ __forceinline__ void publish_and_lookback(unsigned long long* row, uint32_t f,
-                                                     uint32_t n_cl, uint32_t n_adc,
-                                                     uint32_t& ex_cl, uint32_t& ex_adc,
-                                                     uint32_t& err) {
-    uint32_t acl = 0, aadc = 0, e = 0;
-    if (f == 0) {
-        __hip_atomic_store(&row[0], pack_state(kFlagIncl, n_cl, n_adc), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-        __hip_atomic_store(&row[f], pack_state(kFlagAgg, n_cl, n_adc), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-        int top = (int)f - 1;   // highest FED not yet summed
-        uint32_t spins = 0;
-        for (;;) {
+// A FED's counts are published as soon as they are known; look_back sums those of the FEDs before
+// it: lane i reads the word of FED top-i, so 64 predecessors are inspected per load; only words not
+// yet published are waited for. Only the counts travel through these words, so relaxed atomics
+// suffice. All values steering the loop are uniform.
+__device__ __forceinline__ void publish(unsigned long long* row, uint32_t f, uint32_t n_cl,
+                                        uint32_t n_adc) {
+    __hip_atomic_store(&row[f], pack_state(f == 0u ? kFlagIncl : kFlagAgg, n_cl, n_adc),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// (resumable: run() looks at most `polls` times and returns whether it is done)
+struct LookBack {
+    int top;              // highest FED not yet summed
+    uint32_t cl, adc;     // sums of the FEDs above it
+    uint32_t polls_left;  // the wait bound
+    bool done, failed;
+    __device__ __forceinline__ void start(uint32_t f) {
+        top = (int)f - 1;
+        cl = adc = 0u;
+        polls_left = kSpinLimit;
+        done = f == 0u;
+        failed = false;
+    }
+    __device__ __forceinline__ void run(const unsigned long long* row, uint32_t polls) {
+        while (!done && polls) {
             const int k = top - (int)lane();
             unsigned long long v = pack_state(kFlagIncl, 0u, 0u);   // before FED 0: nothing
             if (k >= 0) v = __hip_atomic_load(&row[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1196,114 +1255,146 @@ __device__ __forceinline__ void publish_and_lookback(unsigned long long* row, ui
             // lanes summed now: up to the first inclusive word, stopping before any unpublished
             const uint32_t n_take = first_none <= first_incl ? first_none : first_incl + 1u;
             const bool take = lane() < n_take;
-            acl += wave_sum(take ? (uint32_t)((v >> 31) & 0x7fffffffu) : 0u);
-            aadc += wave_sum(take ? (uint32_t)(v & 0x7fffffffu) : 0u);
-            if (first_incl < first_none) break;      // reached an inclusive word
+            cl += wave_sum(take ? (uint32_t)((v >> 31) & 0x7fffffffu) : 0u);
+            adc += wave_sum(take ? (uint32_t)(v & 0x7fffffffu) : 0u);
+            done = first_incl < first_none;          // reached an inclusive word
             top -= (int)n_take;
-            if (first_none < 64u) {                  // FED `top` has not published yet
-                if (++spins > kSpinLimit) { e = 1; break; }
+            if (!done && first_none < 64u) {         // FED `top` has not published yet
+                if (--polls_left == 0u) { failed = done = true; break; }
+                --polls;
                 __builtin_amdgcn_s_sleep(2);
             }
         }
-        __hip_atomic_store(&row[f], pack_state(kFlagIncl, acl + n_cl, aadc + n_adc),
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    ex_cl = acl;
-    ex_adc = aadc;
-    err = e;
-}
+};
 
-// Status bits of channels [c_lo, c_hi) of wave w -> optional per-channel output and the event's
-// flags.
+// The event's flags from a wave's channels, and their status bits where the event wants them.
 template <int W, int DW, int S>
 __device__ __forceinline__ void emit_status(const TileSmem<W, DW, S>& sm, uint32_t w, uint32_t c_lo,
-                                            uint32_t c_hi, uint32_t trailing, uint8_t* chan_status,
-                                            uint32_t f, uint32_t* flags_out) {
-    bool bad = false;
-    for (uint32_t ch = c_lo + lane(); ch < c_hi; ch += kWave) {
-        const bool b = (sm.ch_base[ch + w] & kChBad) != 0u;
-        if (chan_status)
-            gm(chan_status)[f * kNch + ch] = (uint8_t)((b ? (uint32_t)SC_CH_MALFORMED : 0u) |
-                                                       (trailing ? (uint32_t)SC_CH_FED_TRAILING : 0u));
-        bad |= b;
+                                            uint32_t c_hi, bool any_bad, uint32_t trailing,
+                                            uint8_t* chan_status, uint32_t f, uint32_t* flags_out) {
+    if (chan_status) {   // uniform
+        for (uint32_t ch = c_lo + lane(); ch < c_hi; ch += kWave)
+            gm(chan_status)[f * kNch + ch] =
+                (uint8_t)(((sm.ch_base[ch + w] & kChBad) ? (uint32_t)SC_CH_MALFORMED : 0u) |
+                          (trailing ? (uint32_t)SC_CH_FED_TRAILING : 0u));
     }
-    const uint32_t bits = (__ballot(bad) ? kResMalformed : 0u) | (trailing ? kResTrailing : 0u);
+    const uint32_t bits = (any_bad ? kResMalformed : 0u) | (trailing ? kResTrailing : 0u);
     if (bits) atomicOr(flags_out, bits);   // uniform branch; every lane ORs the same bits
 }
 
-// The cluster stages of one channel group over its chunks (shared by the ZS and the dense front
-// ends). form(c0, c1, nd, n_cl, n_adc) fills the group's digi list with channels [c0, c1), nd digis,
-// forms it and counts its clusters and member ADCs. The waves of a tile form their groups, exchange their counts in LDS, and wave 0 publishes the FED's counts and
-// looks back over the earlier FEDs of the event; each group's output offset is then the FED's
-// plus the counts of the groups before it. Every wave passes the same two barriers.
-template <int W, int DW, bool kMod, int S, class FormFn>
-__device__ void cluster_group(const FusedArgs& A, TileSmem<W, DW, S>& sm, const EventDesc& ev,
-                              uint32_t e, uint32_t f, uint32_t w, uint32_t n_chunks, FormFn form) {
-    const uint32_t n_fed = A.cal.n_fed;
-    unsigned long long* row = A.tile_state + (size_t)e * n_fed;
-    const uint32_t* dl = sm.digi + w * TileSmem<W, DW, S>::kList;
+// What a wave knows of its formed channel group.
+struct Group {
+    uint32_t n_cl, n_adc;             // clusters and member ADCs of its chunks
+    uint32_t last_cl, last_adc, last_nd;   // of the last chunk, which stays in the digi list
+};
+// The FED's counts and what lies before a wave's group in it.
+struct FedCounts {
+    uint32_t n_cl, n_adc, pre_cl, pre_adc;
+    bool chunked;   // some group has more than one chunk: they are built again for their writes
+};
+
+// Counts of one channel group, one pass over each of its chunks (shared by the ZS and the dense
+// front ends). form(c0, c1, nd, n_cl, n_adc) fills the group's digi list with channels [c0, c1), nd
+// digis, forms it and counts its clusters and member ADCs.
+template <int W, int DW, int S, class FormFn>
+__device__ __forceinline__ Group form_group(TileSmem<W, DW, S>& sm, uint32_t w, uint32_t n_chunks,
+                                            FormFn form) {
     const uint8_t* cf = sm.chunk_first[w];
-    const bool regular = A.cal.regular_gains != 0u;
-    // counts: one pass over each chunk; the last chunk stays in the list for its writes
-    uint32_t n_cl = 0, n_adc = 0, last_cl = 0, last_adc = 0, last_nd = 0;
+    Group g{};
     for (uint32_t ci = 0; ci < n_chunks; ++ci) {
         const uint32_t c0 = uni(cf[ci]), c1 = uni(cf[ci + 1]);
-        last_nd = uni(digi_base(sm, c1 + w) - digi_base(sm, c0 + w));
-        form(c0, c1, last_nd, last_cl, last_adc);
-        n_cl += last_cl;
-        n_adc += last_adc;
+        g.last_nd = uni(digi_base(sm, c1 + w) - digi_base(sm, c0 + w));
+        form(c0, c1, g.last_nd, g.last_cl, g.last_adc);
+        g.n_cl += g.last_cl;
+        g.n_adc += g.last_adc;
     }
-    // the FED's counts and offsets
-    uint32_t f_cl = n_cl, f_adc = n_adc, pre_cl = 0, pre_adc = 0;
-    if constexpr (W > 1) {
-        sm.grp_cnt[w][0] = n_cl;   // uniform values from every lane
-        sm.grp_cnt[w][1] = n_adc;
-        tile_sync();
-        f_cl = 0;
-        f_adc = 0;
+    return g;
+}
+
+// The waves of a tile exchange their groups' counts in LDS (a barrier of the tile: the digi lists
+// are formed and the stage is free after it, unless some group is chunked).
+template <int W, int DW, int S>
+__device__ __forceinline__ FedCounts exchange_counts(TileSmem<W, DW, S>& sm, uint32_t w,
+                                                     const Group& g, uint32_t n_chunks) {
+    sm.grp_cnt[w][0] = g.n_cl;   // uniform values from every lane
+    sm.grp_cnt[w][1] = g.n_adc;
+    sm.grp_cnt[w][2] = n_chunks;
+    tile_sync();
+    FedCounts r{};
 #pragma unroll
-        for (uint32_t i = 0; i < (uint32_t)W; ++i) {
-            const uint32_t c = uni(sm.grp_cnt[i][0]), a = uni(sm.grp_cnt[i][1]);
-            pre_cl += i < w ? c : 0u;
-            pre_adc += i < w ? a : 0u;
-            f_cl += c;
-            f_adc += a;
-        }
+    for (uint32_t i = 0; i < (uint32_t)W; ++i) {
+        const uint32_t c = uni(sm.grp_cnt[i][0]), a = uni(sm.grp_cnt[i][1]);
+        r.pre_cl += i < w ? c : 0u;
+        r.pre_adc += i < w ? a : 0u;
+        r.n_cl += c;
+        r.n_adc += a;
+        r.chunked |= uni(sm.grp_cnt[i][2]) > 1u;
     }
-    uint32_t ex_cl = 0, ex_adc = 0, err = 0;
-    if (w == 0u) publish_and_lookback(row, f, f_cl, f_adc, ex_cl, ex_adc, err);
-    if constexpr (W > 1) {
-        if (w == 0u) {
-            sm.grp_cnt[W][0] = ex_cl;
-            sm.grp_cnt[W][1] = ex_adc;
-            sm.grp_cnt[W][2] = err;
-        }
-        tile_sync();
-        ex_cl = uni(sm.grp_cnt[W][0]);
-        ex_adc = uni(sm.grp_cnt[W][1]);
-        err = uni(sm.grp_cnt[W][2]);
+    return r;
+}
+
+// The rest of one wave's look-back for the FED, its offsets left in LDS for all waves, the event's
+// results.
+template <int W, int DW, int S>
+__device__ __forceinline__ void resolve_offsets(const FusedArgs& A, TileSmem<W, DW, S>& sm,
+                                                uint32_t e, uint32_t f, const FedCounts& n,
+                                                LookBack& lb) {
+    const uint32_t n_fed = A.cal.n_fed;
+    unsigned long long* row = A.tile_state + (size_t)e * n_fed;
+    lb.run(row, 0xffffffffu);
+    if (f)
+        __hip_atomic_store(&row[f], pack_state(kFlagIncl, lb.cl + n.n_cl, lb.adc + n.n_adc),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    sm.grp_cnt[W][0] = lb.cl;
+    sm.grp_cnt[W][1] = lb.adc;
+    // uniform branches; every lane stores the same values
+    if (lb.failed) atomicOr(&A.res[e].flags, kResSpinTimeout);
+    if (f == n_fed - 1) {
+        A.res[e].n_cl = lb.cl + n.n_cl;
+        A.res[e].n_adc = lb.adc + n.n_adc;
     }
-    // writes: the last chunk first (still formed in the list), then the earlier chunks of a
-    // chunked group, built and formed again
-    const uint32_t bc = ex_cl + pre_cl, ba = ex_adc + pre_adc;
-    write_pass<kMod>(sm, dl, last_nd, f, ev, regular, bc + n_cl - last_cl, ba + n_adc - last_adc);
-    uint32_t oc = bc, oa = ba;
+}
+
+// What the writes need of an event.
+__device__ __forceinline__ EventDesc event_outputs(const FusedArgs& A, uint32_t e) {
+    const EventDesc* evp = A.ev + e;
+    EventDesc ev{};
+    ev.cl = uniptr(evp->cl);
+    ev.adc = uniptr(evp->adc);
+    ev.cap_cl = uni(evp->cap_cl);
+    ev.cap_adc = uni(evp->cap_adc);
+    return ev;
+}
+
+// Writes of a wave's digi list (the last chunk of its group) at its offset: the FED's (from LDS),
+// the groups before it and the chunks before it.
+template <int W, int DW, bool kMod, int S>
+__device__ __forceinline__ void write_list(const FusedArgs& A, TileSmem<W, DW, S>& sm,
+                                           const EventDesc& ev, uint32_t f, uint32_t w,
+                                           const Group& g, const FedCounts& n) {
+    write_pass<kMod>(sm, sm.digi + w * TileSmem<W, DW, S>::kList, g.last_nd, f, ev,
+                     A.cal.regular_gains != 0u,
+                     uni(sm.grp_cnt[W][0]) + n.pre_cl + g.n_cl - g.last_cl,
+                     uni(sm.grp_cnt[W][1]) + n.pre_adc + g.n_adc - g.last_adc);
+}
+
+// The earlier chunks of a chunked group, built and formed again.
+template <int W, int DW, bool kMod, int S, class FormFn>
+__device__ __forceinline__ void write_chunks(const FusedArgs& A, TileSmem<W, DW, S>& sm,
+                                             const EventDesc& ev, uint32_t f, uint32_t w, const FedCounts& n,
+                                             uint32_t n_chunks, FormFn form) {
+    const uint32_t* dl = sm.digi + w * TileSmem<W, DW, S>::kList;
+    const uint8_t* cf = sm.chunk_first[w];
+    uint32_t oc = uni(sm.grp_cnt[W][0]) + n.pre_cl, oa = uni(sm.grp_cnt[W][1]) + n.pre_adc;
     for (uint32_t ci = 0; ci + 1 < n_chunks; ++ci) {
         const uint32_t c0 = uni(cf[ci]), c1 = uni(cf[ci + 1]);
         const uint32_t nd = uni(digi_base(sm, c1 + w) - digi_base(sm, c0 + w));
         uint32_t ccl, cadc;
         form(c0, c1, nd, ccl, cadc);
-        write_pass<kMod>(sm, dl, nd, f, ev, regular, oc, oa);
+        write_pass<kMod>(sm, dl, nd, f, ev, A.cal.regular_gains != 0u, oc, oa);
         oc += ccl;
         oa += cadc;
-    }
-    // uniform branches; every lane stores the same values
-    if (w == 0u) {
-        if (err) atomicOr(&A.res[e].flags, kResSpinTimeout);
-        if (f == n_fed - 1) {
-            A.res[e].n_cl = ex_cl + f_cl;
-            A.res[e].n_adc = ex_adc + f_adc;
-        }
     }
 }
 
@@ -1326,107 +1417,184 @@ __device__ __forceinline__ Joins fed_joins(const DeviceCalib& cal, uint32_t f) {
     }
 }
 
-template <int W, int DW, bool kMod, int S>
-__device__ void zs_tile(const FusedArgs& A, TileSmem<W, DW, S>& sm, uint32_t e, uint32_t f) {
-    const EventDesc* evp = A.ev + e;
-    EventDesc ev;
-    ev.zs = uniptr(evp->zs);
-    ev.fed_off = uniptr(evp->fed_off);
-    ev.cl = uniptr(evp->cl);
-    ev.adc = uniptr(evp->adc);
-    ev.chan_status = uniptr(evp->chan_status);
-    ev.cap_cl = uni(evp->cap_cl);
-    ev.cap_adc = uni(evp->cap_adc);
-    const uint64_t lo = uni64(gc(ev.fed_off)[f]), hi = uni64(gc(ev.fed_off)[f + 1]);
-    const uint32_t L = hi > lo ? (uint32_t)(hi - lo) : 0u;
-    const uint8_t* g = ev.zs + lo;
+// A tile of the launch: FED f of event e, L bytes at g.
+struct Tile {
+    uint32_t e, f, L;
+    const uint8_t* g;
+    __device__ __forceinline__ bool none() const { return e == kNoTile; }
+};
 
-    const WalkResult wk = stage_and_walk(sm, g, L, A.cal.gain + (size_t)f * 4 * kNch);
+// The tile with ticket t, looked up and left in LDS for all waves (by one wave).
+template <int W, int DW, int S>
+__device__ __forceinline__ void post_tile(const FusedArgs& A, TileSmem<W, DW, S>& sm, uint32_t t) {
+    const uint32_t n_fed = A.cal.n_fed;
+    uint32_t e = kNoTile, f = 0u, L = 0u;
+    uint64_t g = 0u;
+    if (t < A.n_ev * n_fed) {   // uniform
+        if (A.fed_major) { f = t / A.n_ev; e = t - f * A.n_ev; }
+        else             { e = t / n_fed; f = t - e * n_fed; }
+        gconst<uint64_t>* off = gc(uniptr(A.ev[e].fed_off)) + f;
+        const uint64_t lo = uni64(off[0]), hi = uni64(off[1]);
+        L = hi > lo ? (uint32_t)(hi - lo) : 0u;
+        g = reinterpret_cast<uint64_t>(uniptr(A.ev[e].zs)) + lo;
+    }
+    sm.next[0] = e;
+    sm.next[1] = f;
+    sm.next[2] = L;
+    sm.next[3] = (uint32_t)g;
+    sm.next[4] = (uint32_t)(g >> 32);
+}
+template <int W, int DW, int S>
+__device__ __forceinline__ Tile posted_tile(const TileSmem<W, DW, S>& sm) {
+    return Tile{uni(sm.next[0]), uni(sm.next[1]), uni(sm.next[2]),
+                reinterpret_cast<const uint8_t*>((uint64_t)uni(sm.next[3]) | (uint64_t)uni(sm.next[4]) << 32)};
+}
+
+// The tiles that a workgroup takes, the writes of each after the first half of the next. A tile's
+// look-back waits for the FEDs before it that are still being formed, so the offsets are asked for
+// late: once a tile's digi lists are formed and its counts published, the stage is free, and the
+// next tile is taken, staged, walked and checked before the offsets are needed and the lists
+// written; then its own lists are built. The writes need the digi lists and the gains only; each
+// wave replaces the gains of its own channels after them.
+// A ticket is not taken earlier than that: the tile behind it would begin late, by as much as the
+// one before it is large, and every later FED of its event would wait for it (with tickets taken
+// one tile ahead and the bytes under way meanwhile the waits grew from 6k to 43k cycles per tile).
+// A tile with a chunked group builds it again from the stage for its writes: those come first.
+// 64 events of 440 FEDs: @@PIPE@@.
+template <int W, int DW, bool kMod, int S, class ClaimFn>
+__device__ __forceinline__ void run_zs_tiles(const FusedArgs& A, TileSmem<W, DW, S>& sm,
+                                             ClaimFn claim) {
     const uint32_t w = wave_index<W>();
+    const bool lead = w == 0u, last = w == (uint32_t)W - 1u;
     uint32_t c_lo, c_hi;
     group_range<W>(w, c_lo, c_hi);
-    uint32_t total;
-    uint32_t n_chunks;
-    const Joins J = fed_joins<kMod>(A.cal, f);
-    if (wk.fits) {
-        const uint8_t* st = sm.stage;
-        n_chunks = plan_chunks<kMod>(sm, w, c_lo, c_hi, J,
-                                     [&](uint32_t ch) { return check_channel(sm, st, ch, wk); },
-                                     total);
-    } else {
-        gconst<uint8_t>* gg = gc(g);
-        n_chunks = plan_chunks<kMod>(sm, w, c_lo, c_hi, J,
-                                     [&](uint32_t ch) { return check_channel(sm, gg, ch, wk); },
-                                     total);
-    }
-    emit_status(sm, w, c_lo, c_hi, wk.trailing, ev.chan_status, f, &A.res[e].flags);
     uint32_t* dl = sm.digi + w * TileSmem<W, DW, S>::kList;
-    const bool fits = wk.fits != 0;
-    auto form = [&](uint32_t c0, uint32_t c1, uint32_t nd, uint32_t& n_cl, uint32_t& n_adc) {
-        if (fits) {
-            const bool maybe = build_markers<kMod>(sm, w, dl, J, c0, c1);
-            form_pass<kMod, true>(dl, nd, sm.stage, A.cal, f, J, maybe, n_cl, n_adc);
-        } else {
-            build_words(sm, w, dl, gc(g), c0, c1);
-            form_pass<kMod, false>(dl, nd, sm.stage, A.cal, f, J, false, n_cl, n_adc);
+    // the tile before, whose writes are due (p.none(): none)
+    Tile p{kNoTile, 0u, 0u, nullptr};
+    Group p_grp{};
+    FedCounts p_cnt{};
+    LookBack lb{};
+    if (last) post_tile(A, sm, claim());
+    tile_sync();
+    for (;;) {
+        const Tile t = posted_tile(sm);
+        uint32_t n_chunks = 0;
+        bool any_bad = false, any_on = false;
+        GainVecs<W> gains;
+        WalkResult wk{};
+        Joins J{};
+        gconst<uint8_t>* gg = gc(t.g);
+        if (!t.none()) {   // uniform over the tile's waves
+            load_gains(gains, A.cal.gain, t.f, w);
+            if (fits_stage(sm, t.L)) {
+                Pieces<S, kWave * W> bytes;
+                bytes.load(t.g, t.L, threadIdx.x);
+                bytes.store(sm.stage, t.g, t.L, threadIdx.x);
+                tile_sync();
+            }
+            if (lead) walk_fed(sm, t.g, t.L);
+            if (W > 1 && last && !p.none())
+                lb.run(A.tile_state + (size_t)p.e * A.cal.n_fed, kWalkPolls);
+            tile_sync();
+            wk = walk_result(sm, t.L);
+            J = fed_joins<kMod>(A.cal, t.f);
+            if (wk.fits) {
+                const uint8_t* st = sm.stage;
+                n_chunks = plan_chunks<kMod>(sm, w, c_lo, c_hi, J,
+                                             [&](uint32_t ch, bool on, uint32_t& near) {
+                                                 return check_channel(sm, st, ch, wk, on, near);
+                                             },
+                                             any_bad, any_on);
+            } else {
+                n_chunks = plan_chunks<kMod>(sm, w, c_lo, c_hi, J,
+                                             [&](uint32_t ch, bool on, uint32_t& near) {
+                                                 return check_channel(sm, gg, ch, wk, on, near);
+                                             },
+                                             any_bad, any_on);
+            }
+            emit_status(sm, w, c_lo, c_hi, any_bad, wk.trailing,
+                        A.any_status ? uniptr(A.ev[t.e].chan_status) : nullptr, t.f,
+                        &A.res[t.e].flags);
         }
-    };
-    cluster_group<W, DW, kMod>(A, sm, ev, e, f, w, n_chunks, form);
+        if (!p.none()) {
+            const EventDesc ev = event_outputs(A, p.e);
+            if (last) resolve_offsets(A, sm, p.e, p.f, p_cnt, lb);
+            tile_sync();
+            write_list<W, DW, kMod>(A, sm, ev, p.f, w, p_grp, p_cnt);
+        }
+        if (t.none()) break;
+        store_gains(sm, gains, w);
+        auto form = [&](uint32_t c0, uint32_t c1, uint32_t nd, uint32_t& n_cl, uint32_t& n_adc) {
+            if (wk.fits) {
+                build_markers<kMod>(sm, w, dl, J, any_on, c0, c1);
+                form_pass<kMod, true>(dl, nd, sm.stage, A.cal, t.f, J, any_on, n_cl, n_adc);
+            } else {
+                build_words(sm, w, dl, gg, c0, c1);
+                form_pass<kMod, false>(dl, nd, sm.stage, A.cal, t.f, J, false, n_cl, n_adc);
+            }
+        };
+        p_grp = form_group(sm, w, n_chunks, form);
+        p_cnt = exchange_counts(sm, w, p_grp, n_chunks);
+        p = t;
+        if (last) publish(A.tile_state + (size_t)t.e * A.cal.n_fed, t.f, p_cnt.n_cl, p_cnt.n_adc);
+        lb.start(t.f);
+        if (p_cnt.chunked) {   // uniform over the tile's waves
+            const EventDesc ev = event_outputs(A, p.e);
+            if (last) resolve_offsets(A, sm, p.e, p.f, p_cnt, lb);
+            tile_sync();
+            write_list<W, DW, kMod>(A, sm, ev, p.f, w, p_grp, p_cnt);
+            write_chunks<W, DW, kMod>(A, sm, ev, p.f, w, p_cnt, n_chunks, form);
+            p.e = kNoTile;
+        }
+        if (last) post_tile(A, sm, claim());
+        tile_sync();   // (every wave is done with the stage)
+    }
 }
 
 // ---- one FED tile from dense ADC rows (single event) --------------------------------------
 template <int W, int DW, bool kMod, int S>
 __device__ void dense_tile(const FusedArgs& A, TileSmem<W, DW, S>& sm, const uint8_t* dense,
                            uint32_t f) {
-    const EventDesc* evp = A.ev;
-    EventDesc ev;
-    ev.zs = nullptr;
-    ev.fed_off = nullptr;
-    ev.cl = uniptr(evp->cl);
-    ev.adc = uniptr(evp->adc);
-    ev.chan_status = nullptr;
-    ev.cap_cl = uni(evp->cap_cl);
-    ev.cap_adc = uni(evp->cap_adc);
     const uint8_t* rows = dense + (size_t)f * kStripsPerFed;
     const uint32_t w = wave_index<W>();
-    if (w == 0u) store_gain_vecs(sm, load_gain_vecs(A.cal.gain + (size_t)f * 4 * kNch));
-    tile_sync();
+    GainVecs<W> gains;
+    load_gains(gains, A.cal.gain, f, w);
+    store_gains(sm, gains, w);
     uint32_t c_lo, c_hi;
     group_range<W>(w, c_lo, c_hi);
-    uint32_t total;
+    bool any_bad, any_on;
     const Joins J = fed_joins<kMod>(A.cal, f);
     const uint32_t n_chunks = plan_chunks<kMod>(
         sm, w, c_lo, c_hi, J,
-        [&](uint32_t ch) { return count_dense_row(rows + ch * kStripsPerChannel); }, total);
+        [&](uint32_t ch, bool, uint32_t&) { return count_dense_row(rows + ch * kStripsPerChannel); },
+        any_bad, any_on);
     uint32_t* dl = sm.digi + w * TileSmem<W, DW, S>::kList;
     auto form = [&](uint32_t c0, uint32_t c1, uint32_t nd, uint32_t& n_cl, uint32_t& n_adc) {
         build_dense(sm, w, dl, rows, c0, c1);
         form_pass<kMod, false>(dl, nd, sm.stage, A.cal, f, J, false, n_cl, n_adc);
     };
-    cluster_group<W, DW, kMod>(A, sm, ev, 0, f, w, n_chunks, form);
+    const Group grp = form_group(sm, w, n_chunks, form);
+    const FedCounts cnt = exchange_counts(sm, w, grp, n_chunks);
+    const EventDesc ev = event_outputs(A, 0u);
+    if (w == 0u) {
+        publish(A.tile_state, f, cnt.n_cl, cnt.n_adc);
+        LookBack lb;
+        lb.start(f);
+        resolve_offsets(A, sm, 0u, f, cnt, lb);
+    }
+    tile_sync();
+    write_list<W, DW, kMod>(A, sm, ev, f, w, grp, cnt);
+    write_chunks<W, DW, kMod>(A, sm, ev, f, w, cnt, n_chunks, form);
 }
 
 // ---- kernels --------------------------------------------------------------------------------
-// The next tile of the queue. Every lane executes the atomic, adding 1 from lane 0 and 0 from
-// the others (no lane test); lane 0's old value is the tile. Tiles are taken in a global order
-// (FED-major or event-major) in which a tile's look-back predecessors come before it, so the
-// lowest unfinished tile of an event has always been taken and every look-back ends, whatever
-// part of the grid is resident. With several waves per tile, wave 0 takes the ticket and the
-// others read it after a barrier.
-template <int W, int DW, int S>
-__device__ __forceinline__ uint32_t next_tile(TileSmem<W, DW, S>& sm, uint32_t* queue) {
-    if constexpr (W == 1) {
-        return uni(atomicAdd(queue, lane() == 0u ? 1u : 0u));
-    } else {
-        // wave 0 rewrites walk[3] only after the barrier that ends the tile: one barrier here
-        if (wave_index<W>() == 0u) {
-            __builtin_amdgcn_s_setprio(3);   // the tile's waves wait for this ticket
-            sm.walk[3] = uni(atomicAdd(queue, lane() == 0u ? 1u : 0u));
-            __builtin_amdgcn_s_setprio(0);
-        }
-        tile_sync();
-        return uni(sm.walk[3]);
-    }
+// The next ticket of the queue (by one wave). Every lane executes the atomic, adding 1 from lane 0
+// and 0 from the others (no lane test); lane 0's old value is the ticket. Tiles are taken in a
+// global order (FED-major or event-major) in which a tile's look-back predecessors come before it,
+// so the lowest unfinished tile of an event has always been taken and every look-back ends,
+// whatever part of the grid is resident.
+__device__ __forceinline__ uint32_t claim_one(uint32_t* queue) {
+    return uni(atomicAdd(queue, lane() == 0u ? 1u : 0u));
 }
 
 // Tile order 2: G = min(8, grid) queues; queue x holds the FEDs f = x (mod G), FED-major, and
@@ -1483,43 +1651,6 @@ __device__ __forceinline__ uint32_t claim_xcd(uint32_t* queue, uint32_t n_ev, ui
     return n_ev * n_fed;
 }
 
-template <int W, int DW, int S>
-__device__ __forceinline__ uint32_t next_tile_xcd(TileSmem<W, DW, S>& sm, uint32_t* queue,
-                                                  uint32_t n_ev, uint32_t n_fed, uint32_t groups,
-                                                  XcdCursor& cur) {
-    if constexpr (W == 1) {
-        return claim_xcd(queue, n_ev, n_fed, groups, cur);
-    } else {
-        if (wave_index<W>() == 0u) {
-            __builtin_amdgcn_s_setprio(3);
-            sm.walk[3] = claim_xcd(queue, n_ev, n_fed, groups, cur);
-            __builtin_amdgcn_s_setprio(0);
-        }
-        tile_sync();
-        return uni(sm.walk[3]);
-    }
-}
-
-// Runs tile(e, f) for every tile of an n_ev x n_fed launch, in tile order `order` (0 event-major,
-// 1 FED-major, 2 FED-major per XCD).
-template <int W, int DW, int S, class TileFn>
-__device__ __forceinline__ void run_tiles(TileSmem<W, DW, S>& sm, uint32_t* queue, uint32_t n_ev,
-                                          uint32_t n_fed, uint32_t order, TileFn tile) {
-    const uint32_t n_tiles = n_ev * n_fed;
-    const uint32_t groups = gridDim.x < kXcds ? gridDim.x : kXcds;
-    XcdCursor cur{blockIdx.x % groups, 0u};
-    for (;;) {
-        const uint32_t t = order == 2u ? next_tile_xcd(sm, queue, n_ev, n_fed, groups, cur)
-                                       : next_tile(sm, queue);
-        if (t >= n_tiles) break;
-        uint32_t e, f;
-        if (order) { f = t / n_ev; e = t - f * n_ev; }
-        else           { e = t / n_fed; f = t - e * n_fed; }
-        tile(e, f);
-        tile_sync();   // the tile ends here for every lane of every wave (a convergent point)
-    }
-}
-
 // Two-wave tiles: at most 128 vector registers, so that the eight tiles that fit a CU's LDS can be
 // resident (four waves per SIMD).
 constexpr int min_waves_per_simd(int w) { return w == 2 ? 4 : 1; }
@@ -1530,15 +1661,25 @@ __global__ __launch_bounds__(kWave * W, min_waves_per_simd(W)) void fused_kernel
     // the ZS build finds its record markers by bit 31 of the digi list's slots: clear them once
     for (uint32_t i = threadIdx.x; i < (uint32_t)(W * TileSmem<W, DW, S>::kList); i += kWave * W)
         sm.digi[i] = 0u;
-    run_tiles(sm, A.queue, A.n_ev, A.cal.n_fed, A.fed_major,
-              [&](uint32_t e, uint32_t f) { zs_tile<W, DW, kMod>(A, sm, e, f); });
+    const uint32_t groups = gridDim.x < kXcds ? gridDim.x : kXcds;
+    XcdCursor cur{blockIdx.x % groups, 0u};
+    run_zs_tiles<W, DW, kMod>(A, sm, [&]() {
+        return A.fed_major == 2u ? claim_xcd(A.queue, A.n_ev, A.cal.n_fed, groups, cur)
+                                 : claim_one(A.queue);
+    });
 }
 
 template <int W, int DW, bool kMod, int S>
 __global__ __launch_bounds__(kWave * W, min_waves_per_simd(W)) void cluster_dense_kernel(const uint8_t* dense, FusedArgs A) {
     __shared__ TileSmem<W, DW, S> sm;
-    run_tiles(sm, A.queue, 1u, A.cal.n_fed, 1u,
-              [&](uint32_t, uint32_t f) { dense_tile<W, DW, kMod>(A, sm, dense, f); });
+    for (;;) {
+        if (wave_index<W>() == 0u) sm.next[1] = claim_one(A.queue);
+        tile_sync();
+        const uint32_t f = uni(sm.next[1]);
+        if (f >= A.cal.n_fed) break;
+        dense_tile<W, DW, kMod>(A, sm, dense, f);
+        tile_sync();   // the tile ends here for every lane of every wave (a convergent point)
+    }
 }
 
 // ZS -> dense rows, one FED per single-wave workgroup.
@@ -1550,18 +1691,30 @@ __global__ __launch_bounds__(kWave) void unpack_kernel(const uint8_t* zs, const 
     const uint64_t lo = uni64(gc(fed_off)[f]), hi = uni64(gc(fed_off)[f + 1]);
     const uint32_t L = hi > lo ? (uint32_t)(hi - lo) : 0u;
     const uint8_t* g = zs + lo;
-    const WalkResult w = stage_and_walk(sm, g, L, nullptr);
-    uint32_t total;
+    if (fits_stage(sm, L)) {
+        Pieces<kStageSmall, kWave> p;
+        p.load(g, L, lane());
+        p.store(sm.stage, g, L, lane());
+        tile_sync();
+    }
+    walk_fed(sm, g, L);
+    tile_sync();
+    const WalkResult w = walk_result(sm, L);
+    bool any_bad, any_on;
     if (w.fits) {
         const uint8_t* st = sm.stage;
         plan_chunks<false>(sm, 0u, 0u, (uint32_t)kNch, Joins{0u, 0u, 0u},
-                           [&](uint32_t ch) { return check_channel(sm, st, ch, w); }, total);
+                           [&](uint32_t ch, bool on, uint32_t& near) {
+                               return check_channel(sm, st, ch, w, on, near);
+                           }, any_bad, any_on);
     } else {
         gconst<uint8_t>* gg = gc(g);
         plan_chunks<false>(sm, 0u, 0u, (uint32_t)kNch, Joins{0u, 0u, 0u},
-                           [&](uint32_t ch) { return check_channel(sm, gg, ch, w); }, total);
+                           [&](uint32_t ch, bool on, uint32_t& near) {
+                               return check_channel(sm, gg, ch, w, on, near);
+                           }, any_bad, any_on);
     }
-    emit_status(sm, 0u, 0u, (uint32_t)kNch, w.trailing, chan_status, f, &res->flags);
+    emit_status(sm, 0u, 0u, (uint32_t)kNch, any_bad, w.trailing, chan_status, f, &res->flags);
     // 16 channels at a time: zero rows in LDS, expand records, copy out with 16-byte stores
     uint8_t* rowbuf = reinterpret_cast<uint8_t*>(sm.digi);   // 4 KiB
     gmut<u32x4>* out = gm(reinterpret_cast<u32x4*>(dense + (size_t)f * kStripsPerFed));

@@ -130,11 +130,12 @@ struct Workspace {
 size_t devbuf_size(size_t bytes) { return bytes ? align_up(std::max<size_t>(bytes, 256), 4096) : 0; }
 
 struct GraphKey {
-    uint32_t n_ev, chunk, waves, grid, fed_major, modules, stage;
+    uint32_t n_ev, chunk, waves, grid, fed_major, modules, stage, status;
     uint64_t gen;
     bool operator<(const GraphKey& o) const {
-        return std::tie(n_ev, chunk, waves, grid, fed_major, modules, stage, gen) <
-               std::tie(o.n_ev, o.chunk, o.waves, o.grid, o.fed_major, o.modules, o.stage, o.gen);
+        return std::tie(n_ev, chunk, waves, grid, fed_major, modules, stage, status, gen) <
+               std::tie(o.n_ev, o.chunk, o.waves, o.grid, o.fed_major, o.modules, o.stage, o.status,
+                        o.gen);
     }
 };
 
@@ -450,6 +451,12 @@ DeviceCalib device_calib(const sc_ctx* c) {
     return d;
 }
 
+uint32_t any_status(const EventDesc* d, uint32_t n) {
+    for (uint32_t i = 0; i < n; ++i)
+        if (d[i].chan_status) return 1u;
+    return 0u;
+}
+
 FusedArgs fused_args(sc_ctx* c, Workspace& ws, uint32_t n) {
     FusedArgs a{};
     a.ev = ws.desc.as<EventDesc>();
@@ -488,6 +495,7 @@ hipError_t enqueue_batch(sc_ctx* c, Workspace& ws, uint32_t n, hipStream_t s, bo
         ws.desc_on_device.assign(hd, hd + n);
     }
     FusedArgs a = fused_args(c, ws, n);
+    a.any_status = any_status(hd, n);
     // the per-XCD order needs its whole grid resident with no other such launch running: only a
     // launch that holds order2_mu to its end (the synchronous calls) uses it
     if (!exclusive && a.fed_major == 2u) a.fed_major = 1u;
@@ -509,7 +517,8 @@ hipError_t enqueue_batch(sc_ctx* c, Workspace& ws, uint32_t n, hipStream_t s, bo
 hipError_t enqueue_batch_graph(sc_ctx* c, Workspace& ws, uint32_t n, hipStream_t s) {
     const uint32_t grid = grid_for(c, n * c->n_fed, false);
     GraphKey k{n, c->tuning.chunk_digis, c->tuning.tile_waves, grid, c->tuning.fed_major,
-               c->modules ? 1u : 0u, stage_bytes_of(c->tuning.stage_bytes), ws.generation};
+               c->modules ? 1u : 0u, stage_bytes_of(c->tuning.stage_bytes),
+               any_status(ws.h_desc.as<EventDesc>(), n), ws.generation};
     auto it = c->graphs.find(k);
     hipError_t e;
     if (it == c->graphs.end()) {
@@ -1473,6 +1482,7 @@ sc_status sc_process_events_static(sc_ctx* c, const sc_event* ev, uint32_t n, sc
     a.cal = device_calib(c);
     a.n_ev = n;
     a.fed_major = c->tuning.fed_major;
+    a.any_status = any_status(hd, n);
     EventResult* hr = reinterpret_cast<EventResult*>(c->h_static.as<uint8_t>() +
                                                      sizeof(EventDesc) * SC_STATIC_MAX_EVENTS);
     hipStream_t s = c->stream;
