@@ -24,13 +24,14 @@ struct EventDesc {
     uint32_t cap_adc;
 };
 
-// Per-event result written by the last FED tile of the event (counts) and by any tile (flags).
-enum : uint32_t { kResMalformed = 1u, kResTrailing = 2u, kResSpinTimeout = 4u };
+// Per-event result, in pinned host memory that the host clears before the launch: the tile of the
+// event's last FED stores the counts, any tile may store 1 to either of the other words (all plain
+// stores of one value each, so nothing is read or added across the link).
 struct EventResult {
     uint32_t n_cl;
     uint32_t n_adc;
-    uint32_t flags;
-    uint32_t pad;
+    uint32_t malformed;   // some channel is
+    uint32_t failed;      // a look-back gave up waiting
 };
 
 // Device-resident calibration, derived once per context.
@@ -55,7 +56,7 @@ constexpr size_t kQueueBytes = 8 * kQueueStride * sizeof(uint32_t);
 
 struct FusedArgs {
     const EventDesc* ev;
-    EventResult* res;
+    EventResult* res;                // pinned host memory
     unsigned long long* tile_state;  // [n_ev * n_fed] decoupled look-back words
     uint32_t* queue;                 // kQueueBytes of tile ticket counters
     DeviceCalib cal;
@@ -65,10 +66,8 @@ struct FusedArgs {
 };
 
 // Scratch of the allocation-free batch call (sc_process_events_static), a file-scope device
-// array of sc_kernels.hip: per-event results, event descriptors, the tile queue and the
-// look-back words, for at most SC_STATIC_MAX_EVENTS events and SC_STATIC_MAX_TILES tiles.
-constexpr size_t kStaticResOff = 0;
-constexpr size_t kStaticDescOff = kStaticResOff + sizeof(EventResult) * SC_STATIC_MAX_EVENTS;
+// array of sc_kernels.hip: event descriptors, the tile queue and the look-back words, for at most SC_STATIC_MAX_EVENTS events and SC_STATIC_MAX_TILES tiles.
+constexpr size_t kStaticDescOff = 0;
 constexpr size_t kStaticQueueOff = (kStaticDescOff + sizeof(EventDesc) * SC_STATIC_MAX_EVENTS + 255) / 256 * 256;
 constexpr size_t kStaticStateOff = kStaticQueueOff + kQueueBytes;
 constexpr size_t kStaticScratchBytes = kStaticStateOff + sizeof(unsigned long long) * SC_STATIC_MAX_TILES;
@@ -79,7 +78,7 @@ hipError_t static_scratch_address(void** ptr);
 hipError_t launch_derive_calib(const float* noise, const float* gain, const uint8_t* bad,
                                uint32_t n_fed, float* noise_out, float* gain_pairs,
                                hipStream_t stream);
-// Clears n_state look-back words (n_ev x n_fed), the queue and the results.
+// Clears n_state look-back words (n_ev x n_fed) and the queue.
 hipError_t launch_reset(const FusedArgs& a, uint32_t n_state, hipStream_t stream);
 // stage: the LDS stage size in bytes of the tuning (0: the small one)
 hipError_t launch_fused(const FusedArgs& a, uint32_t tile_waves, uint32_t chunk_digis,
