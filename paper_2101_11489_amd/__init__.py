@@ -360,7 +360,9 @@ class Context:
     def _order(self):
         torch = _torch()
         cur = torch.cuda.current_stream(self.device)
-        if cur.cuda_stream != self.stream.cuda_stream:
+        # (a stream with nothing left to do need not be waited for: asking costs 2 us, an event
+        # recorded and waited for 16)
+        if cur.cuda_stream != self.stream.cuda_stream and not cur.query():
             self.stream.wait_stream(cur)
 
     def _check(self, rc, allowed=(SC_OK, SC_MALFORMED)):
@@ -551,7 +553,8 @@ class Context:
         ptrs = (ctypes.c_void_p * n)(*[h.data_ptr() for h in hits])
         self._order()
         self._check(lib().sc_cluster_hits(self._h, cs, n, ptrs))
-        return [h[:min(o.cs.n_cl, o.cs.cap_cl)] for h, o in zip(hits, outs)]
+        ns = [min(o.cs.n_cl, o.cs.cap_cl) for o in outs]
+        return [h if h.shape[0] == k else h[:k] for h, k in zip(hits, ns)]
 
     def stats(self) -> dict:
         s = ScStats()
