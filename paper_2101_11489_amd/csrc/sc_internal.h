@@ -63,7 +63,16 @@ struct FusedArgs {
     uint32_t n_ev;
     uint32_t fed_major;              // tile order: 0 event-major, 1 FED-major, 2 FED-major per XCD
     uint32_t any_status;             // some event wants its channels' status
+    uint32_t ev_magic;               // ceil(2^32 / n_ev), 0 for n_ev = 1
+    uint32_t one_each;               // order 2 with a workgroup for every tile: no second tickets
+    uint32_t pick;                   // 0: run; 1, 2: run if the events' FEDs are mostly ordinary,
+                                     // or large (of two shapes enqueued for the same events)
 };
+// A FED from this size on counts as large: from about 3000 digis, which two wave lists of 1440 hold
+// no more, to 3800, by the hits' width.
+constexpr uint32_t kLargeFed = 5200;
+// Member ADCs per FED from which an event's output capacity leaves room for large FEDs.
+constexpr uint32_t kLargeFedMembers = 3600;
 
 // Scratch of the allocation-free batch call (sc_process_events_static), a file-scope device
 // array of sc_kernels.hip: event descriptors, the tile queue and the look-back words, for at most SC_STATIC_MAX_EVENTS events and SC_STATIC_MAX_TILES tiles.

@@ -44,7 +44,8 @@ namespace {
 
 constexpr uint32_t kSpinLimit = 1u << 22;   // look-back wait bound (seconds of sleeping)
 constexpr uint32_t kWalkPolls = 6;          // look-back polls that fit beside a walk
-constexpr uint32_t kXcds = 8;               // XCDs of the device (queues of tile order 2)
+constexpr uint32_t kXcdShift = 3;           // 8 XCDs (queues of tile order 2)
+constexpr uint32_t kXcds = 1u << kXcdShift;
 constexpr int kNch = kChannelsPerFed;
 constexpr int kStripsPerFed = kChannelsPerFed * kStripsPerChannel;
 
@@ -1422,6 +1423,19 @@ __device__ __forceinline__ Joins fed_joins(const DeviceCalib& cal, uint32_t f) {
     }
 }
 
+// A tile as event and FED (e = kNoTile: none left).
+struct Ticket {
+    uint32_t e, f;
+};
+
+// t / n for n = A.n_ev, with ev_magic = ceil(2^32 / n) (0 stands for n = 1): the high half of the
+// product is the quotient or one more.
+__device__ __forceinline__ uint32_t div_events(const FusedArgs& A, uint32_t t) {
+    if (A.ev_magic == 0u) return t;   // uniform
+    const uint32_t q = __umulhi(t, A.ev_magic);
+    return q * A.n_ev > t ? q - 1u : q;
+}
+
 // A tile of the launch: FED f of event e, L bytes at g.
 struct Tile {
     uint32_t e, f, L;
@@ -1429,22 +1443,20 @@ struct Tile {
     __device__ __forceinline__ bool none() const { return e == kNoTile; }
 };
 
-// The tile with ticket t, looked up and left in LDS for all waves (by one wave).
+// A ticket's tile, looked up and left in LDS for all waves (by one wave).
 template <int W, int DW, int S>
-__device__ __forceinline__ void post_tile(const FusedArgs& A, TileSmem<W, DW, S>& sm, uint32_t t) {
-    const uint32_t n_fed = A.cal.n_fed;
-    uint32_t e = kNoTile, f = 0u, L = 0u;
+__device__ __forceinline__ void post_tile(const FusedArgs& A, TileSmem<W, DW, S>& sm,
+                                          const Ticket& t) {
+    uint32_t L = 0u;
     uint64_t g = 0u;
-    if (t < A.n_ev * n_fed) {   // uniform
-        if (A.fed_major) { f = t / A.n_ev; e = t - f * A.n_ev; }
-        else             { e = t / n_fed; f = t - e * n_fed; }
-        gconst<uint64_t>* off = gc(uniptr(A.ev[e].fed_off)) + f;
+    if (t.e != kNoTile) {   // uniform
+        gconst<uint64_t>* off = gc(uniptr(A.ev[t.e].fed_off)) + t.f;
         const uint64_t lo = uni64(off[0]), hi = uni64(off[1]);
         L = hi > lo ? (uint32_t)(hi - lo) : 0u;
-        g = reinterpret_cast<uint64_t>(uniptr(A.ev[e].zs)) + lo;
+        g = reinterpret_cast<uint64_t>(uniptr(A.ev[t.e].zs)) + lo;
     }
-    sm.next[0] = e;
-    sm.next[1] = f;
+    sm.next[0] = t.e;
+    sm.next[1] = t.f;
     sm.next[2] = L;
     sm.next[3] = (uint32_t)g;
     sm.next[4] = (uint32_t)(g >> 32);
@@ -1467,9 +1479,9 @@ __device__ __forceinline__ Tile posted_tile(const TileSmem<W, DW, S>& sm) {
 // A tile with a chunked group builds it again from the stage for its writes: those come first.
 // 64 events of 440 FEDs: the wait for offsets fell from 6.3k to 2.9k cycles per tile, most of which
 // the other phases took up (vector issue is 70 % busy); one event: 30.3 -> 27.5 us.
-template <int W, int DW, bool kMod, int S, class ClaimFn>
+template <int W, int DW, bool kMod, int S, class FirstFn, class ClaimFn>
 __device__ __forceinline__ void run_zs_tiles(const FusedArgs& A, TileSmem<W, DW, S>& sm,
-                                             ClaimFn claim) {
+                                             FirstFn first, ClaimFn claim) {
     const uint32_t w = wave_index<W>();
     const bool lead = w == 0u, last = w == (uint32_t)W - 1u;
     uint32_t c_lo, c_hi;
@@ -1480,10 +1492,11 @@ __device__ __forceinline__ void run_zs_tiles(const FusedArgs& A, TileSmem<W, DW,
     Group p_grp{};
     FedCounts p_cnt{};
     LookBack lb{};
-    if (last) post_tile(A, sm, claim());
+    if (last) post_tile(A, sm, first());
     tile_sync();
+    bool more = true;
     for (;;) {
-        const Tile t = posted_tile(sm);
+        const Tile t = more ? posted_tile(sm) : Tile{kNoTile, 0u, 0u, nullptr};
         uint32_t n_chunks = 0;
         bool any_bad = false, any_on = false;
         GainVecs<W> gains;
@@ -1552,8 +1565,11 @@ __device__ __forceinline__ void run_zs_tiles(const FusedArgs& A, TileSmem<W, DW,
             write_chunks<W, DW, kMod>(A, sm, ev, p.f, w, p_cnt, n_chunks, form);
             p.e = kNoTile;
         }
-        if (last) post_tile(A, sm, claim());
-        tile_sync();   // (every wave is done with the stage)
+        more = !A.one_each;   // uniform over the grid: no second tile
+        if (more) {
+            if (last) post_tile(A, sm, claim());
+            tile_sync();   // (every wave is done with the stage)
+        }
     }
 }
 
@@ -1594,20 +1610,29 @@ __device__ void dense_tile(const FusedArgs& A, TileSmem<W, DW, S>& sm, const uin
 }
 
 // ---- kernels --------------------------------------------------------------------------------
-// The next ticket of the queue (by one wave). Every lane executes the atomic, adding 1 from lane 0
-// and 0 from the others (no lane test); lane 0's old value is the ticket. Tiles are taken in a
-// global order (FED-major or event-major) in which a tile's look-back predecessors come before it,
-// so the lowest unfinished tile of an event has always been taken and every look-back ends,
-// whatever part of the grid is resident.
-__device__ __forceinline__ uint32_t claim_one(uint32_t* queue) {
-    return uni(atomicAdd(queue, lane() == 0u ? 1u : 0u));
+// Orders 0 and 1: the next ticket of the one queue (by one wave). Every lane executes the atomic,
+// adding 1 from lane 0 and 0 from the others (no lane test); lane 0's old value is the ticket.
+// Tiles are taken in a global order (event-major or FED-major) in which a tile's look-back
+// predecessors come before it, so the lowest unfinished tile of an event has always been taken and
+// every look-back ends, whatever part of the grid is resident.
+__device__ __forceinline__ Ticket claim_one(const FusedArgs& A) {
+    const uint32_t n_fed = A.cal.n_fed;
+    const uint32_t t = uni(atomicAdd(A.queue, lane() == 0u ? 1u : 0u));
+    if (t >= A.n_ev * n_fed) return Ticket{kNoTile, 0u};
+    if (A.fed_major) {
+        const uint32_t f = div_events(A, t);
+        return Ticket{t - f * A.n_ev, f};
+    }
+    const uint32_t e = t / n_fed;
+    return Ticket{e, t - e * n_fed};
 }
 
-// Tile order 2: G = min(8, grid) queues; queue x holds the FEDs f = x (mod G), FED-major, and
-// counts its tickets in queue[x * kQueueStride] (one cache line each). A workgroup takes tiles
-// from queue (blockIdx mod G), its home, until that is exhausted, then moves on to another open
-// queue; it ends once every queue is known to be exhausted. Returns the tile as f * n_ev + e, or
-// n_ev * n_fed at the end.
+// Tile order 2: G = 8 queues (one in a grid of fewer workgroups); queue x holds the FEDs f = x
+// (mod G), FED-major. A workgroup's home queue is blockIdx mod G, and its first tile is its own
+// place there (blockIdx / G), without an atomic: as many workgroups asking at once for their first
+// ticket cost a launch of one tile each 2 us. The tickets after the homes' are counted in
+// queue[x * kQueueStride] (one cache line each). A workgroup takes tiles from its home until that is
+// exhausted, then moves on to another open queue; it ends once every queue is known to be exhausted.
 // Look-back ends here too, if the whole grid is resident (the host launches this order only
 // with no other such launch running, and never with more workgroups than fit): take the unfinished
 // tile of lowest FED. Either it has been taken, and its predecessors (lower FEDs) are finished,
@@ -1619,24 +1644,31 @@ struct XcdCursor {
     uint32_t known;   // bit x: queue x is exhausted (a ticket past its end, or its counter seen so)
 };
 
-__device__ __forceinline__ uint32_t queue_tiles(uint32_t x, uint32_t n_ev, uint32_t n_fed,
-                                                uint32_t groups) {
-    return x < n_fed ? (n_fed - x + groups - 1u) / groups * n_ev : 0u;
+__device__ __forceinline__ uint32_t queue_shift() { return gridDim.x < kXcds ? 0u : kXcdShift; }
+
+// Tiles of queue x, and those that are some workgroup's first.
+__device__ __forceinline__ uint32_t queue_tiles(const FusedArgs& A, uint32_t x) {
+    const uint32_t s = queue_shift(), n_fed = A.cal.n_fed;
+    return x < n_fed ? ((n_fed - x + (1u << s) - 1u) >> s) * A.n_ev : 0u;
+}
+__device__ __forceinline__ uint32_t home_tiles(uint32_t x) {
+    const uint32_t s = queue_shift();
+    return (gridDim.x - x + (1u << s) - 1u) >> s;
+}
+__device__ __forceinline__ Ticket tile_of(const FusedArgs& A, uint32_t x, uint32_t t) {
+    const uint32_t j = div_events(A, t);
+    return Ticket{t - j * A.n_ev, x + (j << queue_shift())};
 }
 
-__device__ __forceinline__ uint32_t claim_xcd(uint32_t* queue, uint32_t n_ev, uint32_t n_fed,
-                                              uint32_t groups, XcdCursor& c) {
-    const uint32_t all = (1u << groups) - 1u;
+__device__ __forceinline__ Ticket claim_xcd(const FusedArgs& A, XcdCursor& c) {
+    const uint32_t groups = 1u << queue_shift(), all = (1u << groups) - 1u;
     // each pass either returns a tile or adds a queue to `known`: at most groups + 1 passes
     for (uint32_t k = 0; k <= groups && c.known != all; ++k) {
         const uint32_t x = uni(c.cur);   // a scalar address: one atomic per wave, not per lane
-        const uint32_t size = queue_tiles(x, n_ev, n_fed, groups);
-        if (size && !(c.known >> x & 1u)) {
-            const uint32_t t = uni(atomicAdd(queue + x * kQueueStride, lane() == 0u ? 1u : 0u));
-            if (t < size) {
-                const uint32_t j = t / n_ev;
-                return (x + j * groups) * n_ev + (t - j * n_ev);
-            }
+        const uint32_t size = queue_tiles(A, x), home = home_tiles(x);
+        if (size > home && !(c.known >> x & 1u)) {
+            const uint32_t t = home + uni(atomicAdd(A.queue + x * kQueueStride, lane() == 0u ? 1u : 0u));
+            if (t < size) return tile_of(A, x, t);
         }
         c.known |= 1u << x;
         // the next queue not known to be exhausted, from the counters (lane i reads queue i's);
@@ -1644,9 +1676,9 @@ __device__ __forceinline__ uint32_t claim_xcd(uint32_t* queue, uint32_t n_ev, ui
         // costs one more failed ticket
         bool open = false;
         if (lane() < groups && !(c.known >> lane() & 1u)) {
-            const uint32_t v = __hip_atomic_load(queue + lane() * kQueueStride, __ATOMIC_RELAXED,
+            const uint32_t v = __hip_atomic_load(A.queue + lane() * kQueueStride, __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT);
-            open = v < queue_tiles(lane(), n_ev, n_fed, groups);
+            open = home_tiles(lane()) + v < queue_tiles(A, lane());
         }
         const uint32_t m = (uint32_t)__ballot(open);
         c.known = uni(c.known | (all & ~m));
@@ -1654,7 +1686,30 @@ __device__ __forceinline__ uint32_t claim_xcd(uint32_t* queue, uint32_t n_ev, ui
         const uint32_t after = m & ~((2u << x) - 1u);   // open queues past x, then from 0
         c.cur = uni((uint32_t)__builtin_ctz(after ? after : m));
     }
-    return n_ev * n_fed;
+    return Ticket{kNoTile, 0u};
+}
+
+// A workgroup's first tile: its own place in its home queue, or where that is past the queue's end
+// (the homes have the same number of workgroups, the queues not always of tiles) a ticket of another.
+__device__ __forceinline__ Ticket first_xcd(const FusedArgs& A, XcdCursor& c) {
+    const uint32_t s = queue_shift();
+    const uint32_t x = blockIdx.x & ((1u << s) - 1u), t = blockIdx.x >> s;
+    if (t < queue_tiles(A, x)) return tile_of(A, x, t);
+    return A.one_each ? Ticket{kNoTile, 0u} : claim_xcd(A, c);
+}
+
+// Whether this launch's shape is the one for its events, where two are enqueued for the same events
+// and each looks for itself (A.pick: 1 the ordinary shape, 2 the large one): 64 tiles spread over
+// the launch are sampled, the same ones by every workgroup, and the large shape is for launches
+// with 16 or more FEDs among them of kLargeFed bytes.
+__device__ __forceinline__ bool picked(const FusedArgs& A) {
+    const uint32_t n_tiles = A.n_ev * A.cal.n_fed;
+    const uint32_t t = (uint32_t)((uint64_t)lane() * n_tiles / kWave) + n_tiles / (2u * kWave);
+    const uint32_t f = div_events(A, t), e = t - f * A.n_ev;
+    gconst<uint64_t>* off = gc(gc(A.ev)[e].fed_off) + f;
+    const uint64_t lo = off[0], hi = off[1];
+    const bool large = popc(__ballot(hi > lo && hi - lo >= kLargeFed)) >= 16u;
+    return large == (A.pick == 2u);
 }
 
 // Two-wave tiles: at most 128 vector registers, so that the eight tiles that fit a CU's LDS can be
@@ -1664,25 +1719,28 @@ constexpr int min_waves_per_simd(int w) { return w == 2 ? 4 : 1; }
 template <int W, int DW, bool kMod, int S>
 __global__ __launch_bounds__(kWave * W, min_waves_per_simd(W)) void fused_kernel(FusedArgs A) {
     __shared__ TileSmem<W, DW, S> sm;
+    if (A.pick && !picked(A)) return;   // uniform over the grid
     // the ZS build finds its record markers by bit 31 of the digi list's slots: clear them once
     for (uint32_t i = threadIdx.x; i < (uint32_t)(W * TileSmem<W, DW, S>::kList); i += kWave * W)
         sm.digi[i] = 0u;
-    const uint32_t groups = gridDim.x < kXcds ? gridDim.x : kXcds;
-    XcdCursor cur{blockIdx.x % groups, 0u};
-    run_zs_tiles<W, DW, kMod>(A, sm, [&]() {
-        return A.fed_major == 2u ? claim_xcd(A.queue, A.n_ev, A.cal.n_fed, groups, cur)
-                                 : claim_one(A.queue);
-    });
+    XcdCursor cur{blockIdx.x & ((1u << queue_shift()) - 1u), 0u};
+    run_zs_tiles<W, DW, kMod>(
+        A, sm, [&]() { return A.fed_major == 2u ? first_xcd(A, cur) : claim_one(A); },
+        [&]() { return A.fed_major == 2u ? claim_xcd(A, cur) : claim_one(A); });
 }
 
 template <int W, int DW, bool kMod, int S>
 __global__ __launch_bounds__(kWave * W, min_waves_per_simd(W)) void cluster_dense_kernel(const uint8_t* dense, FusedArgs A) {
     __shared__ TileSmem<W, DW, S> sm;
     for (;;) {
-        if (wave_index<W>() == 0u) sm.next[1] = claim_one(A.queue);
+        if (wave_index<W>() == 0u) {
+            const Ticket t = claim_one(A);   // n_ev = 1, FED-major
+            sm.next[0] = t.e;
+            sm.next[1] = t.f;
+        }
         tile_sync();
         const uint32_t f = uni(sm.next[1]);
-        if (f >= A.cal.n_fed) break;
+        if (uni(sm.next[0]) == kNoTile) break;
         dense_tile<W, DW, kMod>(A, sm, dense, f);
         tile_sync();   // the tile ends here for every lane of every wave (a convergent point)
     }

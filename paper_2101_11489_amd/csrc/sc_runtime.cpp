@@ -84,11 +84,19 @@ struct PinBuf {
     template <class T> T* as() const { return static_cast<T*>(p); }
 };
 
+// What the host knows of a batch's FED sizes: those of host events, and for events in device memory
+// whether their output capacities leave room for large ones.
+struct FedMix {
+    uint64_t known = 0, large = 0;
+    bool maybe_large = false;
+};
+
 // Buffers of one batched launch. Grown on demand, never shrunk (a caching arena in the spirit of
 // the paper's cached allocator, without per-event allocation).
 struct Workspace {
     DevBuf desc, state, queue, zs, fo, cl, adc, chst, dense;
     PinBuf h_desc, h_res, h_zs, h_fo;
+    FedMix mix;                              // of the batch that is staged
     std::vector<EventDesc> desc_on_device;   // what `desc` holds, so that equal uploads are skipped
     bool clean = false;        // look-back words and queue zeroed (over their capacity)
     uint64_t generation = 0;   // bumps whenever a buffer that graphs capture moves
@@ -128,15 +136,8 @@ struct Workspace {
 // What DevBuf::ensure allocates for a request of `bytes` (0: nothing).
 size_t devbuf_size(size_t bytes) { return bytes ? align_up(std::max<size_t>(bytes, 256), 4096) : 0; }
 
-struct GraphKey {
-    uint32_t n_ev, chunk, waves, grid, fed_major, modules, stage, status;
-    uint64_t gen;
-    bool operator<(const GraphKey& o) const {
-        return std::tie(n_ev, chunk, waves, grid, fed_major, modules, stage, status, gen) <
-               std::tie(o.n_ev, o.chunk, o.waves, o.grid, o.fed_major, o.modules, o.stage, o.status,
-                        o.gen);
-    }
-};
+// What a captured graph depends on: the launches' arguments and the buffers.
+using GraphKey = std::vector<uint64_t>;
 
 struct Req;
 
@@ -228,12 +229,73 @@ sc_status device_fail(sc_ctx* c, hipError_t e, const char* where) {
         if (e_ != hipSuccess) return device_fail(ctx, e_, #call); \
     } while (0)
 
-uint32_t grid_for(const sc_ctx* c, uint32_t n_tiles, bool dense) {
-    const int occ = std::max(1, fused_blocks_per_cu(c->tuning.tile_waves, c->tuning.chunk_digis,
-                                                    dense, c->modules, c->tuning.stage_bytes));
+// A tile shape, and the workgroups of it that are resident at once.
+struct Shape {
+    uint32_t waves, digis, stage;
+};
+uint32_t resident(const sc_ctx* c, const Shape& s, bool dense) {
+    const int occ = std::max(1, fused_blocks_per_cu(s.waves, s.digis, dense, c->modules, s.stage));
     const uint32_t per_cu = std::max<uint32_t>(1, std::min<uint32_t>(c->tuning.tiles_per_cu, occ));
-    const uint32_t g = per_cu * (uint32_t)std::max(1, c->n_cu);
-    return std::max<uint32_t>(1, std::min<uint32_t>(g, n_tiles));
+    return per_cu * (uint32_t)std::max(1, c->n_cu);
+}
+uint32_t grid_for(const sc_ctx* c, const Shape& s, uint32_t n_tiles, bool dense) {
+    return std::max<uint32_t>(1, std::min<uint32_t>(resident(c, s, dense), n_tiles));
+}
+Shape tuned_shape(const sc_ctx* c) {
+    return Shape{c->tuning.tile_waves, c->tuning.chunk_digis, stage_bytes_of(c->tuning.stage_bytes)};
+}
+
+// The default tuning's shape stands for a choice between it and the large one.
+constexpr Shape kOrdinaryShape{2, 2880, 6656}, kLargeShape{4, 6144, 10240};
+bool adaptive(const sc_ctx* c) {
+    const Shape s = tuned_shape(c);
+    return s.waves == kOrdinaryShape.waves && s.digis == kOrdinaryShape.digis &&
+           s.stage == kOrdinaryShape.stage;
+}
+
+// The kernels of one batch: one launch, or two of which the device runs one (pick).
+struct Launch {
+    Shape shape;
+    uint32_t grid, one_each, pick;
+};
+
+// A batch's launches. Where the default tuning leaves the shape open:
+//  * where every tile can have a resident workgroup of the large shape, they take it: four waves on
+//    a FED shorten its chain of passes (one 50-FED event 21.1 us with the ordinary shape and 18.5
+//    with the large one, one of 440 FEDs 26.2 and 23.4); beyond that the ordinary one is faster (20
+//    events of 50 FEDs 23.2 us and 26.3, 20 of 440 FEDs 105 and 146);
+//  * batches whose FEDs are mostly large take it too: the ordinary shape's stage and lists do not
+//    hold such FEDs, which are then read from global memory and formed twice (64 events of 440
+//    FEDs of 8.2 KB: 1795 us against 687). The host counts the FEDs of host events. Of device
+//    events it knows the capacity of their outputs: room for as many member ADCs as a large FED may
+//    have, on average, enqueues both shapes, and the kernels themselves look which of them is for
+//    the events (an idle launch is 4 us of a batch of this size).
+std::vector<Launch> plan_launches(const sc_ctx* c, const FedMix& mix, uint32_t n, uint32_t order) {
+    const uint64_t n_tiles = (uint64_t)n * c->n_fed;
+    // workgroups for order 2 with one for every tile: eight queues of equal length
+    const uint64_t each = (uint64_t)n * ((c->n_fed + 7u) / 8u) * 8u;
+    auto launch = [&](const Shape& s, uint32_t pick) {
+        const uint32_t fit = resident(c, s, false);
+        const bool one_each = order == 2u && each <= fit;
+        return Launch{s, one_each ? (uint32_t)each : (uint32_t)std::min<uint64_t>(fit, n_tiles),
+                      one_each ? 1u : 0u, pick};
+    };
+    if (!adaptive(c)) return {launch(tuned_shape(c), 0u)};
+    if ((order == 2u ? each : n_tiles) <= resident(c, kLargeShape, false))
+        return {launch(kLargeShape, 0u)};
+    if (mix.maybe_large) return {launch(kOrdinaryShape, 1u), launch(kLargeShape, 2u)};
+    return {launch(4u * mix.large >= n_tiles ? kLargeShape : kOrdinaryShape, 0u)};
+}
+
+// Adds an event to the mix: its FED offsets where the host has them, else its output capacity.
+void add_event(FedMix& mix, const uint64_t* fed_offset, uint32_t cap_adc, uint32_t n_fed) {
+    if (!fed_offset) {
+        mix.maybe_large |= cap_adc / n_fed >= kLargeFedMembers;
+        return;
+    }
+    mix.known += n_fed;
+    for (uint32_t f = 0; f < n_fed; ++f)
+        mix.large += fed_offset[f + 1] > fed_offset[f] && fed_offset[f + 1] - fed_offset[f] >= kLargeFed;
 }
 
 // Largest byte offset an event references (its buffer must be at least this long).
@@ -368,8 +430,10 @@ sc_status stage_batch(sc_ctx* c, Workspace& ws, const sc_event* ev, uint32_t n,
     if (adc_b) SC_HIP(c, ws.adc.ensure(adc_b));
     if (st_b) SC_HIP(c, ws.chst.ensure(st_b));
     EventDesc* hd = ws.h_desc.as<EventDesc>();
+    ws.mix = FedMix{};
     for (uint32_t i = 0; i < n; ++i) {
         EventDesc d{};
+        add_event(ws.mix, host_mem(ev[i].mem) ? ev[i].fed_offset : nullptr, out[i].cap_adc, n_fed);
         if (host_mem(ev[i].mem)) {
             const uint64_t span = event_span(ev[i].fed_offset, n_fed);
             if (span && ev[i].mem == SC_MEM_HOST)
@@ -449,6 +513,8 @@ DeviceCalib device_calib(const sc_ctx* c) {
     return d;
 }
 
+uint32_t ev_magic(uint32_t n) { return n > 1u ? (uint32_t)(((1ull << 32) + n - 1u) / n) : 0u; }
+
 uint32_t any_status(const EventDesc* d, uint32_t n) {
     for (uint32_t i = 0; i < n; ++i)
         if (d[i].chan_status) return 1u;
@@ -463,6 +529,7 @@ FusedArgs fused_args(sc_ctx* c, Workspace& ws, uint32_t n) {
     a.queue = ws.queue.as<uint32_t>();
     a.cal = device_calib(c);
     a.n_ev = n;
+    a.ev_magic = ev_magic(n);
     a.fed_major = c->tuning.fed_major;
     return a;
 }
@@ -508,19 +575,21 @@ hipError_t enqueue_batch(sc_ctx* c, Workspace& ws, uint32_t n, hipStream_t s, bo
     // launch that holds order2_mu to its end (the synchronous calls) uses it
     if (!exclusive && a.fed_major == 2u) a.fed_major = 1u;
     if (timed && (e = hipEventRecord(c->ev0, s))) return e;
-    const uint32_t grid = grid_for(c, n * c->n_fed, false);
-    if ((e = launch_fused(a, c->tuning.tile_waves, c->tuning.chunk_digis, c->tuning.stage_bytes,
-                          grid, s)))
-        return e;
+    for (const Launch& l : plan_launches(c, ws.mix, n, a.fed_major)) {
+        a.one_each = l.one_each;
+        a.pick = l.pick;
+        if ((e = launch_fused(a, l.shape.waves, l.shape.digis, l.shape.stage, l.grid, s))) return e;
+    }
     return timed ? hipEventRecord(c->ev1, s) : hipSuccess;
 }
 
 // Replays (capturing on first use) the batched launch as a hipGraph.
 hipError_t enqueue_batch_graph(sc_ctx* c, Workspace& ws, uint32_t n, hipStream_t s) {
-    const uint32_t grid = grid_for(c, n * c->n_fed, false);
-    GraphKey k{n, c->tuning.chunk_digis, c->tuning.tile_waves, grid, c->tuning.fed_major,
-               c->modules ? 1u : 0u, stage_bytes_of(c->tuning.stage_bytes),
-               any_status(ws.h_desc.as<EventDesc>(), n), ws.generation};
+    GraphKey k{n, c->tuning.fed_major, c->modules ? 1u : 0u, any_status(ws.h_desc.as<EventDesc>(), n),
+               ws.generation};
+    for (const Launch& l : plan_launches(c, ws.mix, n, c->tuning.fed_major))
+        for (uint32_t v : {l.shape.waves, l.shape.digis, l.shape.stage, l.grid, l.one_each, l.pick})
+            k.push_back(v);
     auto it = c->graphs.find(k);
     hipError_t e;
     if (it == c->graphs.end()) {
@@ -1194,8 +1263,9 @@ sc_status sc_cluster(sc_ctx* c, const uint8_t* adc_dense, sc_mem in_mem, sc_clus
     SC_HIP(c, enqueue_inputs(c, ws, 1, c->stream));
     FusedArgs a = fused_args(c, ws, 1);
     SC_HIP(c, hipEventRecord(c->ev0, c->stream));
-    SC_HIP(c, launch_cluster_dense(d_in, a, c->tuning.tile_waves, c->tuning.chunk_digis,
-                                   c->tuning.stage_bytes, grid_for(c, c->n_fed, true), c->stream));
+    const Shape shape = tuned_shape(c);
+    SC_HIP(c, launch_cluster_dense(d_in, a, shape.waves, shape.digis, shape.stage,
+                                   grid_for(c, shape, c->n_fed, true), c->stream));
     SC_HIP(c, hipEventRecord(c->ev1, c->stream));
     SC_HIP(c, hipEventRecord(c->done, c->stream));
     SC_HIP(c, enqueue_clean(c, ws, c->stream));
@@ -1476,6 +1546,7 @@ sc_status sc_process_events_static(sc_ctx* c, const sc_event* ev, uint32_t n, sc
     a.queue = reinterpret_cast<uint32_t*>(c->d_static + kStaticQueueOff);
     a.cal = device_calib(c);
     a.n_ev = n;
+    a.ev_magic = ev_magic(n);
     a.fed_major = c->tuning.fed_major;
     a.any_status = any_status(hd, n);
     EventResult* hr = reinterpret_cast<EventResult*>(c->h_static.as<uint8_t>() +
@@ -1490,8 +1561,13 @@ sc_status sc_process_events_static(sc_ctx* c, const sc_event* ev, uint32_t n, sc
     // the array keeps the last call's contents: clear the look-back words and the queue
     SC_HIP(c, launch_reset(a, n * c->n_fed, s));
     SC_HIP(c, hipEventRecord(c->ev0, s));
-    SC_HIP(c, launch_fused(a, c->tuning.tile_waves, c->tuning.chunk_digis, c->tuning.stage_bytes,
-                           grid_for(c, n * c->n_fed, false), s));
+    FedMix mix;
+    for (uint32_t i = 0; i < n; ++i) add_event(mix, nullptr, out[i].cap_adc, c->n_fed);
+    for (const Launch& l : plan_launches(c, mix, n, a.fed_major)) {
+        a.one_each = l.one_each;
+        a.pick = l.pick;
+        SC_HIP(c, launch_fused(a, l.shape.waves, l.shape.digis, l.shape.stage, l.grid, s));
+    }
     SC_HIP(c, hipEventRecord(c->ev1, s));
     SC_HIP(c, hipStreamSynchronize(s));
     record_kernel_ms(c);
