@@ -75,7 +75,8 @@ constexpr uint32_t kLargeFed = 5200;
 constexpr uint32_t kLargeFedMembers = 3600;
 
 // Scratch of the allocation-free batch call (sc_process_events_static), a file-scope device
-// array of sc_kernels.hip: event descriptors, the tile queue and the look-back words, for at most SC_STATIC_MAX_EVENTS events and SC_STATIC_MAX_TILES tiles.
+// array of sc_kernels.hip: event descriptors, the tile queue and the look-back words, for at most
+// SC_STATIC_MAX_EVENTS events and SC_STATIC_MAX_TILES tiles.
 constexpr size_t kStaticDescOff = 0;
 constexpr size_t kStaticQueueOff = (kStaticDescOff + sizeof(EventDesc) * SC_STATIC_MAX_EVENTS + 255) / 256 * 256;
 constexpr size_t kStaticStateOff = kStaticQueueOff + kQueueBytes;

@@ -650,6 +650,60 @@ __device__ __forceinline__ uint32_t count_dense_row(const uint8_t* row) {
     return cnt;
 }
 
+// Bit i: byte i of the 16 is not zero.
+__device__ __forceinline__ uint32_t nonzero_bytes(u32x4 v) {
+    const uint32_t wds[4] = {v.x, v.y, v.z, v.w};
+    uint32_t m = 0;
+#pragma unroll
+    for (int k = 3; k >= 0; --k) {
+        // the top bit of each nonzero byte, then the four next to each other
+        const uint32_t x = wds[k];
+        uint32_t nz = ((((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) >> 7) & 0x01010101u;
+        nz |= nz >> 7;
+        nz |= nz >> 14;
+        m = m << 4 | (nz & 15u);
+    }
+    return m;
+}
+
+// All digi words of a channel group in one pass over its dense rows: a lane takes 16 strips, a step
+// four channels, so lane order is list order and a scan over the lanes places each step's digis.
+// Returns their number, or kNoStrip if they do not fit the list (nothing is lost: the group is then
+// taken in chunks). The loads of six steps are in flight together. (Rows counted a lane each and then
+// read again took 36 us for 440 FEDs with two waves each, this 17 with four; the rows' bytes alone
+// take 2 at a copy's rate: bound by one FED's chain of load, scan, passes and look-back.)
+template <int W, int DW, int S>
+__device__ __forceinline__ uint32_t build_dense_group(TileSmem<W, DW, S>& sm, uint32_t* dl,
+                                                      const uint8_t* rows, uint32_t c_lo) {
+    constexpr int kBatch = 6, kSteps = kNch / W / 4;
+    static_assert(kSteps % kBatch == 0, "whole batches");
+    gconst<u32x4>* src = gc(reinterpret_cast<const u32x4*>(rows + c_lo * kStripsPerChannel)) + lane();
+    uint32_t n = 0;
+    for (int b = 0; b < kSteps; b += kBatch) {
+        u32x4 v[kBatch];
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k) v[k] = src[(b + k) * kWave];
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k) {
+            const uint32_t wds[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
+            uint32_t m = nonzero_bytes(v[k]), tot;
+            uint32_t o = n + wave_excl_scan(__popc(m), tot);
+            n += tot;
+            if (n > (uint32_t)DW) return kNoStrip;   // uniform
+            const uint32_t base = (c_lo * kStripsPerChannel + ((uint32_t)(b + k) * kWave + lane()) * 16u) << 10;
+            while (m) {
+                const uint32_t i = (uint32_t)__builtin_ctz(m);
+                m &= m - 1u;
+                const uint32_t lo = i & 4u ? wds[1] : wds[0], hi = i & 4u ? wds[3] : wds[2];
+                const uint32_t a = ((i & 8u ? hi : lo) >> ((i & 3u) * 8u)) & 255u;
+                dl[o++] = base + (i << 10) + a;
+            }
+        }
+    }
+    wave_sync();
+    return n;
+}
+
 // ---- windows of the digi list ---------------------------------------------------------------
 // Forming and writing take the list in windows of up to 256 digis, four consecutive ones per lane
 // (lane l: slots 4 l .. 4 l + 3 of the window). A window begins where a run can begin and is cut
@@ -1584,15 +1638,26 @@ __device__ void dense_tile(const FusedArgs& A, TileSmem<W, DW, S>& sm, const uin
     store_gains(sm, gains, w);
     uint32_t c_lo, c_hi;
     group_range<W>(w, c_lo, c_hi);
-    bool any_bad, any_on;
     const Joins J = fed_joins<kMod>(A.cal, f);
-    const uint32_t n_chunks = plan_chunks<kMod>(
-        sm, w, c_lo, c_hi, J,
-        [&](uint32_t ch, bool, uint32_t&) { return count_dense_row(rows + ch * kStripsPerChannel); },
-        any_bad, any_on);
     uint32_t* dl = sm.digi + w * TileSmem<W, DW, S>::kList;
+    const uint32_t n_digis = build_dense_group(sm, dl, rows, c_lo);
+    const bool whole = n_digis != kNoStrip;   // uniform
+    uint32_t n_chunks = 1u;
+    if (whole) {
+        sm.ch_base[c_lo + w] = 0u;
+        sm.ch_base[c_hi + w] = (uint16_t)n_digis;
+        sm.chunk_first[w][0] = (uint8_t)c_lo;
+        sm.chunk_first[w][1] = (uint8_t)c_hi;
+        wave_sync();
+    } else {
+        bool any_bad, any_on;
+        n_chunks = plan_chunks<kMod>(
+            sm, w, c_lo, c_hi, J,
+            [&](uint32_t ch, bool, uint32_t&) { return count_dense_row(rows + ch * kStripsPerChannel); },
+            any_bad, any_on);
+    }
     auto form = [&](uint32_t c0, uint32_t c1, uint32_t nd, uint32_t& n_cl, uint32_t& n_adc) {
-        build_dense(sm, w, dl, rows, c0, c1);
+        if (!whole) build_dense(sm, w, dl, rows, c0, c1);
         form_pass<kMod, false>(dl, nd, sm.stage, A.cal, f, J, false, n_cl, n_adc);
     };
     const Group grp = form_group(sm, w, n_chunks, form);
@@ -1746,76 +1811,82 @@ __global__ __launch_bounds__(kWave * W, min_waves_per_simd(W)) void cluster_dens
     }
 }
 
-// ZS -> dense rows, one FED per single-wave workgroup.
-__global__ __launch_bounds__(kWave) void unpack_kernel(const uint8_t* zs, const uint64_t* fed_off,
-                                                       uint8_t* dense, uint8_t* chan_status,
-                                                       EventResult* res) {
-    __shared__ TileSmem<1, 1024> sm;
-    const uint32_t f = blockIdx.x;
+// ZS -> dense rows, a workgroup of four waves per FED: the stage, the walk, then a lane per channel
+// checks its records and expands them into zeroed rows in LDS, which all threads copy out with 16-byte
+// stores. Bound by its chains (the walk's 96 LDS round trips, a channel's records); one wave per FED
+// with 16 channels at a time took 49 us for 440 FEDs, this 17 us.
+constexpr int kUnpackWaves = 4;
+constexpr uint32_t kRowStride = kStripsPerChannel + 16;   // the lanes' rows start at different banks
+
+// One valid channel's records into its zeroed row. (staged: up to three bytes past a record are read)
+template <class P>
+__device__ __forceinline__ void expand_channel(P src, uint32_t a, uint32_t end, uint8_t* row) {
+    constexpr bool kStaged = std::is_same_v<P, const uint8_t*>;
+    while (a < end) {
+        const uint32_t first = src[a], cnt = src[a + 1u];
+        a += 2u;
+        uint8_t* out = row + first;
+        if constexpr (kStaged) {
+            for (uint32_t i = 0; i < cnt; i += 4u) {
+                const uint8_t b0 = src[a + i], b1 = src[a + i + 1u], b2 = src[a + i + 2u],
+                              b3 = src[a + i + 3u];
+                out[i] = b0;
+                if (i + 1u < cnt) out[i + 1u] = b1;
+                if (i + 2u < cnt) out[i + 2u] = b2;
+                if (i + 3u < cnt) out[i + 3u] = b3;
+            }
+        } else {
+            for (uint32_t i = 0; i < cnt; ++i) out[i] = src[a + i];
+        }
+        a += cnt;
+    }
+}
+
+__global__ __launch_bounds__(kWave * kUnpackWaves) void unpack_kernel(
+    const uint8_t* zs, const uint64_t* fed_off, uint8_t* dense, uint8_t* chan_status,
+    EventResult* res) {
+    constexpr int W = kUnpackWaves, S = kStageLarge;
+    __shared__ TileSmem<W, 4, S> sm;
+    __shared__ alignas(16) uint8_t rows[kNch * kRowStride + 16];
+    const uint32_t f = blockIdx.x, w = wave_index<W>();
     const uint64_t lo = uni64(gc(fed_off)[f]), hi = uni64(gc(fed_off)[f + 1]);
     const uint32_t L = hi > lo ? (uint32_t)(hi - lo) : 0u;
     const uint8_t* g = zs + lo;
-    if (fits_stage(sm, L)) {
-        Pieces<kStageSmall, kWave> p;
-        p.load(g, L, lane());
-        p.store(sm.stage, g, L, lane());
-        tile_sync();
-    }
-    walk_fed(sm, g, L);
+    Pieces<S, kWave * W> bytes;
+    if (fits_stage(sm, L)) bytes.load(g, L, threadIdx.x);
+    u32x4* row4 = reinterpret_cast<u32x4*>(rows);
+    for (uint32_t i = threadIdx.x; i < kNch * kRowStride / 16u; i += kWave * W)
+        row4[i] = u32x4{0u, 0u, 0u, 0u};
+    if (fits_stage(sm, L)) bytes.store(sm.stage, g, L, threadIdx.x);
     tile_sync();
-    const WalkResult w = walk_result(sm, L);
-    bool any_bad, any_on;
-    if (w.fits) {
-        const uint8_t* st = sm.stage;
-        plan_chunks<false>(sm, 0u, 0u, (uint32_t)kNch, Joins{0u, 0u, 0u},
-                           [&](uint32_t ch, bool on, uint32_t& near) {
-                               return check_channel(sm, st, ch, w, on, near);
-                           }, any_bad, any_on);
-    } else {
-        gconst<uint8_t>* gg = gc(g);
-        plan_chunks<false>(sm, 0u, 0u, (uint32_t)kNch, Joins{0u, 0u, 0u},
-                           [&](uint32_t ch, bool on, uint32_t& near) {
-                               return check_channel(sm, gg, ch, w, on, near);
-                           }, any_bad, any_on);
-    }
-    emit_status(sm, 0u, 0u, (uint32_t)kNch, any_bad, w.trailing, chan_status, f, res);
-    // 16 channels at a time: zero rows in LDS, expand records, copy out with 16-byte stores
-    uint8_t* rowbuf = reinterpret_cast<uint8_t*>(sm.digi);   // 4 KiB
-    gmut<u32x4>* out = gm(reinterpret_cast<u32x4*>(dense + (size_t)f * kStripsPerFed));
-    for (uint32_t g0 = 0; g0 < (uint32_t)kNch; g0 += 16) {
-        for (uint32_t i = lane(); i < 16 * kStripsPerChannel / 4; i += kWave)
-            reinterpret_cast<uint32_t*>(rowbuf)[i] = 0u;
-        tile_sync();
-        if (lane() < 16) {
-            const uint32_t ch = g0 + lane();
-            if (!(sm.ch_base[ch] & kChBad)) {
-                const uint32_t p = sm.ch_pos[ch];
-                const uint32_t len = payload_len(sm, ch);
-                uint8_t* row = rowbuf + lane() * kStripsPerChannel;
-                uint32_t q = 0;
-                if (w.fits) {
-                    const uint8_t* s = sm.stage;
-                    while (q < len) {
-                        const uint32_t first = s[p + q], cnt = s[p + q + 1];
-                        for (uint32_t i = 0; i < cnt; ++i) row[first + i] = s[p + q + 2 + i];
-                        q += 2 + cnt;
-                    }
-                } else {
-                    gconst<uint8_t>* s = gc(g);
-                    while (q < len) {
-                        const uint32_t first = s[p + q], cnt = s[p + q + 1];
-                        for (uint32_t i = 0; i < cnt; ++i) row[first + i] = s[p + q + 2 + i];
-                        q += 2 + cnt;
-                    }
-                }
-            }
+    if (w == 0u) walk_fed(sm, g, L);
+    tile_sync();
+    const WalkResult wk = walk_result(sm, L);
+    bool bad = false;
+    if (lane() < (uint32_t)(kNch / W)) {
+        const uint32_t ch = w * (uint32_t)(kNch / W) + lane();
+        uint8_t* row = rows + ch * kRowStride;
+        uint32_t near;
+        if (wk.fits) {
+            const uint8_t* s = sm.stage;
+            bad = check_channel(sm, s, ch, wk, false, near) == kChBad;
+            if (!bad) expand_channel(s, sm.ch_pos[ch], sm.ch_pos[ch] + payload_len(sm, ch), row);
+        } else {
+            gconst<uint8_t>* s = gc(g);
+            bad = check_channel(sm, s, ch, wk, false, near) == kChBad;
+            if (!bad) expand_channel(s, sm.ch_pos[ch], sm.ch_pos[ch] + payload_len(sm, ch), row);
         }
-        tile_sync();
-        const u32x4* src = reinterpret_cast<const u32x4*>(rowbuf);
-        for (uint32_t i = lane(); i < 16 * kStripsPerChannel / 16; i += kWave)
-            out[g0 * (kStripsPerChannel / 16) + i] = src[i];
-        tile_sync();
+        if (chan_status)
+            gm(chan_status)[f * kNch + ch] = (uint8_t)((bad ? (uint32_t)SC_CH_MALFORMED : 0u) |
+                                                       (wk.trailing ? (uint32_t)SC_CH_FED_TRAILING : 0u));
     }
+    if (__ballot(bad)) store_result(&res->malformed, 1u);
+    tile_sync();
+    constexpr uint32_t kRowVecs = kStripsPerChannel / 16;
+    gmut<u32x4>* out = gm(reinterpret_cast<u32x4*>(dense + (size_t)f * kStripsPerFed));
+#pragma unroll
+    for (uint32_t i = threadIdx.x; i < kNch * kRowVecs; i += kWave * W)
+        out[i] = row4[i / kRowVecs * (kRowStride / 16u) + i % kRowVecs];
 }
 
 __global__ void reset_kernel(unsigned long long* state, uint32_t n_state, uint32_t* queue) {
@@ -1978,7 +2049,7 @@ hipError_t launch_unpack(const uint8_t* zs, const uint64_t* fed_off, uint32_t n_
                          uint8_t* dense, uint8_t* chan_status, EventResult* res,
                          hipStream_t stream) {
     (void)hipGetLastError();
-    hipLaunchKernelGGL(unpack_kernel, dim3(n_fed), dim3(kWave), 0, stream, zs, fed_off, dense,
+    hipLaunchKernelGGL(unpack_kernel, dim3(n_fed), dim3(kWave * kUnpackWaves), 0, stream, zs, fed_off, dense,
                        chan_status, res);
     return hipGetLastError();
 }

@@ -534,8 +534,9 @@ FusedArgs fused_args(sc_ctx* c, Workspace& ws, uint32_t n) {
     return a;
 }
 
-// Zeroes the look-back words and the queue over their whole capacity, for whatever batch comes next; enqueued after a synchronous batch has handed its results over, so that it
-// runs while the host takes them.
+// Zeroes the look-back words and the queue over their whole capacity, for whatever batch comes next;
+// enqueued after a synchronous batch has handed its results over, so that it runs while the host
+// takes them.
 hipError_t enqueue_clean(sc_ctx* c, Workspace& ws, hipStream_t s) {
     const uint32_t n_state = (uint32_t)(ws.state.n / sizeof(unsigned long long));
     FusedArgs a = fused_args(c, ws, 0);
@@ -1263,7 +1264,9 @@ sc_status sc_cluster(sc_ctx* c, const uint8_t* adc_dense, sc_mem in_mem, sc_clus
     SC_HIP(c, enqueue_inputs(c, ws, 1, c->stream));
     FusedArgs a = fused_args(c, ws, 1);
     SC_HIP(c, hipEventRecord(c->ev0, c->stream));
-    const Shape shape = tuned_shape(c);
+    // as for batches: four waves on a FED where each can have a resident workgroup
+    const bool small = adaptive(c) && c->n_fed <= resident(c, kLargeShape, true);
+    const Shape shape = small ? kLargeShape : tuned_shape(c);
     SC_HIP(c, launch_cluster_dense(d_in, a, shape.waves, shape.digis, shape.stage,
                                    grid_for(c, shape, c->n_fed, true), c->stream));
     SC_HIP(c, hipEventRecord(c->ev1, c->stream));
