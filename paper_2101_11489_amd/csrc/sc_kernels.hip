@@ -65,7 +65,8 @@ template <class T> __device__ __forceinline__ gmut<T>* at_offset(gmut<T>* base, 
 }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // 16-byte global accesses
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));   // two digi words
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef u32x2 u32x2_by2 __attribute__((aligned(2)));          // at any even address
 
 __device__ __forceinline__ uint32_t lane() { return __lane_id(); }
 // x + the set bits of the wave mask m below this lane (v_mbcnt)
@@ -161,10 +162,11 @@ __device__ __forceinline__ unsigned long long pack_state(uint64_t flag, uint32_t
 //      (source << 17 | position << 2) - slot * kSlotStep   (+ kMaybeBit),
 //    source = the stage offset of the digi's ADC byte, position = channel-in-FED * 256 + strip.
 //    Adding slot' * kSlotStep gives source and position of any later digi of the record, at slot';
-//  * digi words: position << 10 | ADC, and once formed kMemberBit (a member of an accepted cluster)
-//    and kContBit (active, as the digi before it on the adjacent strip: both in one run).
+//  * digi words: position << 10 | ADC.
+// Once formed, it holds the words of the members of accepted clusters alone, close together from its
+// start, with kContBit on each but the first of a cluster.
 constexpr uint32_t kSlotStep = 1u << 17 | 4u, kMarker = 1u << 31, kMaybeBit = 1u;
-constexpr uint32_t kMemberBit = 1u << 30, kContBit = 1u << 29;
+constexpr uint32_t kContBit = 1u << 29;
 constexpr uint32_t kNoStrip = 0xffffffffu;
 constexpr uint32_t kNoiseMask = 0x1fffcu;   // position << 2: byte offset in the FED's noise table
 __device__ __forceinline__ uint32_t d_adc(uint32_t d) { return d & 255u; }
@@ -198,8 +200,9 @@ template <bool kMod> constexpr uint32_t kQShift = kMod ? 18u : 16u;
 // large one (fewer resident tiles) a FED of the 6 %, long-cluster stress events.
 constexpr int kStageSmall = 6656, kStageLarge = 10240;
 
-// A wave's list is read four words at a time from any slot below its end: three words of pad.
-constexpr int kListPad = 3;
+// A wave's list is read four words at a time from any slot below its end, and cleared in 16-byte
+// pieces: four words of pad, of which three are read.
+constexpr int kListPad = 4;
 
 template <int W, int DW, int S = kStageSmall>
 struct TileSmem {
@@ -208,7 +211,7 @@ struct TileSmem {
     static constexpr int kList = DW + kListPad;
     alignas(16) float gain[4 * kNch];                    // the FED's APV gains and reciprocals, in pairs
     alignas(16) uint8_t stage[kStageBytes + 4];          // the FED's bytes (+ readable pad)
-    uint32_t digi[W * kList];                            // wave w: [w * kList, w * kList + DW)
+    alignas(16) uint32_t digi[W * kList];                // wave w: [w * kList, w * kList + DW)
     uint32_t ch_pos[kNch + 2];    // payload positions; [96]: past the last record, + 2; [97]: unused
     uint16_t ch_base[kNch + W];   // channel c of wave w at index c + w: digi offset in the group,
                                   // and kChBad if its record is malformed
@@ -533,6 +536,11 @@ __device__ __forceinline__ void build_markers(TileSmem<W, DW, S>& sm, uint32_t w
     static_assert(TileSmem<W, DW, S>::kStageBytes + 16 < (1 << 14), "marker sources are 14 bits");
     static_assert(DW * 4 < (1 << 18), "position - slot must not borrow past one source step");
     const uint32_t b0 = digi_base(sm, c0 + w);
+    const uint32_t nd = digi_base(sm, c1 + w) - b0;
+    static_assert(DW % 4 == 0 && TileSmem<W, DW, S>::kList % 4 == 0, "lists of whole 16-byte pieces");
+    // (what the list held before may look like markers)
+    for (uint32_t o = 4u * lane(); o < nd; o += 4u * kWave)
+        *reinterpret_cast<u32x4*>(dl + o) = u32x4{0u, 0u, 0u, 0u};
     __builtin_amdgcn_s_setprio(2);   // a serial pass that the digi pass waits for
     for (uint32_t ch = c0 + lane(); ch < c1; ch += kWave) {
         const uint32_t bw = sm.ch_base[ch + w];
@@ -828,8 +836,12 @@ __device__ __forceinline__ bool passes_exactly(float q, float S, float t) {
     return q >= t * __builtin_sqrtf(S);
 }
 
-// Flags and runs of one window; adds the flag bits to its words and counts its clusters and
-// member ADCs (uniform).
+// Runs of one window; puts the words of its clusters' members down from slot n_adc on and counts its
+// clusters and member ADCs (uniform; n_adc counts from the list's start). A member's slot is at or
+// below its own, and later windows are read from slots above all of these.
+// Only members are kept: of the strips above twice their noise that a front end sends, most
+// belong to no cluster at low occupancy (45 % of the digis at 1.5 %), and the writes take that many
+// windows less.
 //  * cluster threshold: the sums S and Q are the definition's own (S in strip order), and the test
 //    q >= t sqrt(S) is taken on squares first: q q >= S t2_hi passes and q q < S t2_lo fails, with
 //    t2_hi and t2_lo = t^2 (1 +- 2^-19). Every rounding on either way is 2^-24 or less relative
@@ -843,15 +855,13 @@ __device__ __forceinline__ bool passes_exactly(float q, float S, float t) {
 template <bool kMod>
 __device__ __forceinline__ void form_window(uint32_t* dl, const Window& x, const DeviceCalib& cal,
                                             uint32_t& n_cl, uint32_t& n_adc) {
-    const uint32_t l4 = 4u * lane();
-    uint64_t valid[4], act[4], K[5];   // K: continues the digi before it (both active)
+    uint64_t act[4], K[5];   // K: continues the digi before it (both active)
     uint32_t Q[4];                     // raw ADC sum | seed count << kQShift, along the run so far
     float S[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const float a = (float)x.adc[k];
-        valid[k] = slots_below(k, x.n);
-        act[k] = __ballot(a > cal.t_channel * x.noise[k]) & valid[k];
+        act[k] = __ballot(a > cal.t_channel * x.noise[k]) & slots_below(k, x.n);
         const bool seed = a > cal.t_seed * x.noise[k];
         Q[k] = seed ? x.adc[k] | 1u << kQShift<kMod> : x.adc[k];
     }
@@ -915,24 +925,24 @@ __device__ __forceinline__ void form_window(uint32_t* dl, const Window& x, const
     mem[2] = yes[2] | (K[3] & mem[3]);
     mem[1] = yes[1] | (K[2] & mem[2]);
     mem[0] = yes[0] | (K[1] & mem[1]);
-    uint32_t v[4];
+    uint32_t o = n_adc;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         n_cl += popc(yes[k]);
         n_adc += popc(mem[k]);
-        const uint32_t word = x.pos4[k] << 8 | x.adc[k] | (in_mask(mem[k]) ? kMemberBit : 0u) |
-                              (in_mask(K[k]) ? kContBit : 0u);
-        v[k] = in_mask(valid[k]) ? word : x.raw[k];   // the slots past the cut stay as they are
+        o = count_below(mem[k], o);
     }
-    if (l4 < x.n) {
-        uint32_t* at = dl + x.base + l4;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) at[k] = v[k];
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t word = x.pos4[k] << 8 | x.adc[k] | (in_mask(K[k]) ? kContBit : 0u);
+        if (in_mask(mem[k])) dl[o] = word;
+        o += in_mask(mem[k]) ? 1u : 0u;
     }
 }
 
 // A chain of adjacent digis that fills the window at base (module rows only), one digi at a time,
-// the same in every lane; returns the slot after it.
+// the same in every lane; returns the slot after it. (n_cl, n_adc and the members' slots as in
+// form_window)
 template <bool kMarkers>
 __device__ uint32_t form_long_chain(uint32_t* dl, uint32_t base, uint32_t nd, const uint8_t* stage,
                                     gconst<float>* noise, Joins J, const DeviceCalib& cal,
@@ -943,9 +953,8 @@ __device__ uint32_t form_long_chain(uint32_t* dl, uint32_t base, uint32_t nd, co
     auto close = [&](uint32_t end) {   // the run [head, end)
         if (open && seeds && passes_exactly((float)Q, S, cal.t_cluster)) {
             n_cl += 1u;
-            n_adc += end - head;
             for (uint32_t i = head; i < end; ++i)
-                dl[i] = uni(dl[i]) | kMemberBit | (i > head ? kContBit : 0u);
+                dl[n_adc++] = uni(dl[i]) | (i > head ? kContBit : 0u);
         }
         open = false;
     };
@@ -985,7 +994,7 @@ __device__ uint32_t form_long_chain(uint32_t* dl, uint32_t base, uint32_t nd, co
 }
 
 // Forming over the digi list dl[0, nd) of a FED, the next window's loads in flight (without module
-// rows).
+// rows). The list becomes that of the n_adc members.
 template <bool kMod, bool kMarkers>
 __device__ __forceinline__ void form_pass(uint32_t* dl, uint32_t nd, const uint8_t* stage,
                                           const DeviceCalib& cal, uint32_t fed, Joins J, bool maybe,
@@ -1046,8 +1055,8 @@ __device__ __forceinline__ float quotient_to_float(double N, double D) {
 // A cluster's record from its last digi dw: rp = its width - 1, C the charge, M the sum of strip * c.
 // Module rows: the cluster may start in an earlier channel of the row, so its channel and first
 // strip come from the position of its first digi (d_pos(dw) - rp), and the strip moment from that
-// channel's strip 0 is sum(pos * c) - 256 ch C, with sum(pos * c) = 65536 Mh + M (pos * c < 2^31,
-// summed in two halves so that 768 strips cannot overflow).
+// channel's strip 0 is sum(pos * c) - 256 ch C, with sum(pos * c) = 4096 Mh + M (pos * c < 2^31,
+// summed in two parts so that 768 strips cannot overflow: M < 768 x 2^12 < 2^22, Mh < 768 x 2^19).
 template <bool kMod>
 __device__ __forceinline__ u32x4 make_record(uint32_t fed, uint32_t dw, uint32_t rp, uint32_t C,
                                              uint32_t M, uint32_t Mh) {
@@ -1057,7 +1066,7 @@ __device__ __forceinline__ u32x4 make_record(uint32_t fed, uint32_t dw, uint32_t
         const uint32_t head = d_pos(dw) - rp;
         ch = head >> 8;
         first = head & 255u;
-        m = ((double)Mh * 65536.0 + (double)M) - 256.0 * (double)ch * (double)C;   // exact
+        m = ((double)Mh * 4096.0 + (double)M) - 256.0 * (double)ch * (double)C;   // exact
     } else {
         ch = d_ch(dw);
         first = d_strip(dw) - rp;
@@ -1128,13 +1137,13 @@ __device__ uint32_t write_long_cluster(const TileSmem<W, DW, S>& sm, const uint3
     uint32_t C = 0u, M = 0u, Mh = 0u, last = 0u, j = base;
     for (; j < nd; ++j) {
         const uint32_t d = uni(dl[j]);
-        if (j > base && d < (kMemberBit | kContBit)) break;
+        if (j > base && d < kContBit) break;
         const float* gr = sm.gain + 2u * (d_pos(d) >> 7);
         const uint32_t c = uni(corrected_adc(d_adc(d), gr[0], gr[1], regular));
         const uint32_t m = d_pos(d) * c;
         C += c;
-        M += m & 0xffffu;
-        Mh += m >> 16;
+        M += m & 0xfffu;
+        Mh += m >> 12;
         if (pa < ev.cap_adc) adc_out[pa] = (uint16_t)c;
         ++pa;
         last = d;
@@ -1145,9 +1154,10 @@ __device__ uint32_t write_long_cluster(const TileSmem<W, DW, S>& sm, const uint3
     return j;
 }
 
-// Records and member ADCs of the digi list dl[0, nd) at their final positions, by windows as in
+// Records and member ADCs of the formed list dl[0, nd) at their final positions, by windows as in
 // forming (here cut at the last digi that continues no cluster). The member ADCs are
-// gain-corrected here. Straight-line windows: every value of a window is formed first and the
+// gain-corrected here; a lane's four lie together and leave in one 8-byte store (of any 2-byte
+// alignment). Straight-line windows: every value of a window is formed first and the
 // stores come last, so that no lane mask has to live across a branch.
 template <bool kMod, int W, int DW, int S>
 __device__ __forceinline__ void write_pass(const TileSmem<W, DW, S>& sm, const uint32_t* dl,
@@ -1159,12 +1169,9 @@ __device__ __forceinline__ void write_pass(const TileSmem<W, DW, S>& sm, const u
     for (uint32_t base = 0; base < nd;) {
         uint32_t d[4];
         read_words(dl, base, nd, d);
-        uint64_t mem[4], K[5];   // members, and those that continue the cluster of the one before
+        uint64_t valid[4], K[5];   // K: continues the cluster of the one before
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            mem[k] = __ballot(d[k] >= kMemberBit);
-            K[k] = __ballot(d[k] >= (kMemberBit | kContBit));
-        }
+        for (int k = 0; k < 4; ++k) K[k] = __ballot(d[k] >= kContBit);
         uint32_t n = nd - base;
         if (n > kWindow) {
             const uint64_t heads[4] = {~K[0] | 1ull, ~K[1], ~K[2], ~K[3]};
@@ -1176,18 +1183,17 @@ __device__ __forceinline__ void write_pass(const TileSmem<W, DW, S>& sm, const u
                 }
                 n = kWindow;
             }
+        }
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint64_t valid = slots_below(k, n);
-                mem[k] &= valid;
-                K[k] &= valid;
-            }
+        for (int k = 0; k < 4; ++k) {
+            valid[k] = slots_below(k, n);
+            K[k] &= valid[k];
         }
         base += n;
         K[4] = K[0] >> 1;
         // corrected ADCs, and the sums along clusters: charge, strip moment and width
         uint32_t c[4], s[4];
-        constexpr int kSums = kMod ? 4 : 2;   // C | width << 24, M; module rows: C, M, Mh, width
+        constexpr int kSums = kMod ? 3 : 2;   // C | width << 24, M; module rows: C, M | width << 22, Mh
         uint32_t v[kSums][4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -1198,9 +1204,8 @@ __device__ __forceinline__ void write_pass(const TileSmem<W, DW, S>& sm, const u
             if constexpr (kMod) {
                 const uint32_t m = __umul24(d_pos(d[k]), c[k]);
                 v[0][k] = c[k] + (on ? v[0][k ? k - 1 : 0] : 0u);
-                v[1][k] = (m & 0xffffu) + (on ? v[1][k ? k - 1 : 0] : 0u);
-                v[2][k] = (m >> 16) + (on ? v[2][k ? k - 1 : 0] : 0u);
-                v[3][k] = 1u + (on ? v[3][k ? k - 1 : 0] : 0u);
+                v[1][k] = (m & 0xfffu) + (1u << 22) + (on ? v[1][k ? k - 1 : 0] : 0u);
+                v[2][k] = (m >> 12) + (on ? v[2][k ? k - 1 : 0] : 0u);
             } else {
                 // at most 256 x 65535 < 2^24; a width of 256 reads as 0
                 v[0][k] = c[k] + (1u << 24) + (on ? v[0][k ? k - 1 : 0] : 0u);
@@ -1208,24 +1213,18 @@ __device__ __forceinline__ void write_pass(const TileSmem<W, DW, S>& sm, const u
             }
         }
         carry_sums(v, K);
-        // positions: members in list order, records by their cluster's last digi
+        // positions: records by their cluster's last digi
         uint64_t end[4];
-        uint32_t ra[4], rr[4];
-        ra[0] = pa;
+        uint32_t rr[4];
         rr[0] = rc;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            end[k] = mem[k] & ~K[k + 1];
-            ra[0] = count_below(mem[k], ra[0]);
+            end[k] = valid[k] & ~K[k + 1];
             rr[0] = count_below(end[k], rr[0]);
-            pa += popc(mem[k]);
             rc += popc(end[k]);
         }
 #pragma unroll
-        for (int k = 1; k < 4; ++k) {
-            ra[k] = ra[k - 1] + (in_mask(mem[k - 1]) ? 1u : 0u);
-            rr[k] = rr[k - 1] + (in_mask(end[k - 1]) ? 1u : 0u);
-        }
+        for (int k = 1; k < 4; ++k) rr[k] = rr[k - 1] + (in_mask(end[k - 1]) ? 1u : 0u);
         // Records by pairs of digis A and B: at most one cluster of the pair has more than one
         // member, and rec1 is A's where it ends at A, else B's. Where A's cluster ends at A, one
         // that ends at B is B alone: first = its strip, width 1, barycenter strip + 1/2 exactly
@@ -1240,8 +1239,8 @@ __device__ __forceinline__ void write_pass(const TileSmem<W, DW, S>& sm, const u
             const uint32_t dw = eA ? d[A] : d[B];
             const uint32_t v0 = eA ? v[0][A] : v[0][B], v1 = eA ? v[1][A] : v[1][B];
             if constexpr (kMod) {
-                const uint32_t v2 = eA ? v[2][A] : v[2][B], v3 = eA ? v[3][A] : v[3][B];
-                rec1[p] = make_record<true>(fed, dw, v3 - 1u, v0, v1, v2);
+                const uint32_t v2 = eA ? v[2][A] : v[2][B];
+                rec1[p] = make_record<true>(fed, dw, (v1 >> 22) - 1u, v0, v1 & 0x3fffffu, v2);
             } else {
                 rec1[p] = make_record<false>(fed, dw, ((v0 >> 24) - 1u) & 255u, v0 & 0xffffffu, v1, 0u);
             }
@@ -1251,10 +1250,7 @@ __device__ __forceinline__ void write_pass(const TileSmem<W, DW, S>& sm, const u
             both[p] = end[A] & end[B];
         }
         // (uniform: mostly the whole window fits)
-        if (pa > ev.cap_adc) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) mem[k] &= __ballot(ra[k] < ev.cap_adc);
-        }
+        const uint32_t room = pa < ev.cap_adc ? ev.cap_adc - pa : 0u, n_out = n < room ? n : room;
         if (rc > ev.cap_cl) {
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
@@ -1263,13 +1259,21 @@ __device__ __forceinline__ void write_pass(const TileSmem<W, DW, S>& sm, const u
             }
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (in_mask(mem[k])) *at_offset(adc_out, 2u * ra[k]) = (uint16_t)c[k];
-#pragma unroll
         for (int p = 0; p < 2; ++p) {
             if (in_mask(any[p])) *at_offset(cl_out, 16u * rr[2 * p]) = rec1[p];
             if (in_mask(both[p])) *at_offset(cl_out, 16u * rr[2 * p + 1]) = rec2[p];
         }
+        const uint32_t l4 = 4u * lane();
+        gmut<uint16_t>* at = at_offset(adc_out, 2u * (pa + l4));
+        const u32x2 c4{c[0] | c[1] << 16, c[2] | c[3] << 16};
+        if (l4 + 4u <= n_out) {
+            *reinterpret_cast<gmut<u32x2_by2>*>(at) = c4;
+        } else {
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                if (l4 + k < n_out) at[k] = (uint16_t)c[k];
+        }
+        pa += n;
     }
     wave_sync();
 }
@@ -1346,7 +1350,7 @@ __device__ __forceinline__ void emit_status(const TileSmem<W, DW, S>& sm, uint32
 // What a wave knows of its formed channel group.
 struct Group {
     uint32_t n_cl, n_adc;             // clusters and member ADCs of its chunks
-    uint32_t last_cl, last_adc, last_nd;   // of the last chunk, which stays in the digi list
+    uint32_t last_cl, last_adc;       // of the last chunk, which stays in the digi list
 };
 // The FED's counts and what lies before a wave's group in it.
 struct FedCounts {
@@ -1364,8 +1368,8 @@ __device__ __forceinline__ Group form_group(TileSmem<W, DW, S>& sm, uint32_t w, 
     Group g{};
     for (uint32_t ci = 0; ci < n_chunks; ++ci) {
         const uint32_t c0 = uni(cf[ci]), c1 = uni(cf[ci + 1]);
-        g.last_nd = uni(digi_base(sm, c1 + w) - digi_base(sm, c0 + w));
-        form(c0, c1, g.last_nd, g.last_cl, g.last_adc);
+        const uint32_t nd = uni(digi_base(sm, c1 + w) - digi_base(sm, c0 + w));
+        form(c0, c1, nd, g.last_cl, g.last_adc);
         g.n_cl += g.last_cl;
         g.n_adc += g.last_adc;
     }
@@ -1433,7 +1437,7 @@ template <int W, int DW, bool kMod, int S>
 __device__ __forceinline__ void write_list(const FusedArgs& A, TileSmem<W, DW, S>& sm,
                                            const EventDesc& ev, uint32_t f, uint32_t w,
                                            const Group& g, const FedCounts& n) {
-    write_pass<kMod>(sm, sm.digi + w * TileSmem<W, DW, S>::kList, g.last_nd, f, ev,
+    write_pass<kMod>(sm, sm.digi + w * TileSmem<W, DW, S>::kList, g.last_adc, f, ev,
                      A.cal.regular_gains != 0u,
                      uni(sm.grp_cnt[W][0]) + n.pre_cl + g.n_cl - g.last_cl,
                      uni(sm.grp_cnt[W][1]) + n.pre_adc + g.n_adc - g.last_adc);
@@ -1452,7 +1456,7 @@ __device__ __forceinline__ void write_chunks(const FusedArgs& A, TileSmem<W, DW,
         const uint32_t nd = uni(digi_base(sm, c1 + w) - digi_base(sm, c0 + w));
         uint32_t ccl, cadc;
         form(c0, c1, nd, ccl, cadc);
-        write_pass<kMod>(sm, dl, nd, f, ev, A.cal.regular_gains != 0u, oc, oa);
+        write_pass<kMod>(sm, dl, cadc, f, ev, A.cal.regular_gains != 0u, oc, oa);
         oc += ccl;
         oa += cadc;
     }
@@ -1785,9 +1789,6 @@ template <int W, int DW, bool kMod, int S>
 __global__ __launch_bounds__(kWave * W, min_waves_per_simd(W)) void fused_kernel(FusedArgs A) {
     __shared__ TileSmem<W, DW, S> sm;
     if (A.pick && !picked(A)) return;   // uniform over the grid
-    // the ZS build finds its record markers by bit 31 of the digi list's slots: clear them once
-    for (uint32_t i = threadIdx.x; i < (uint32_t)(W * TileSmem<W, DW, S>::kList); i += kWave * W)
-        sm.digi[i] = 0u;
     XcdCursor cur{blockIdx.x & ((1u << queue_shift()) - 1u), 0u};
     run_zs_tiles<W, DW, kMod>(
         A, sm, [&]() { return A.fed_major == 2u ? first_xcd(A, cur) : claim_one(A); },
