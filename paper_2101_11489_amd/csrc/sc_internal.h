@@ -93,6 +93,9 @@ hipError_t launch_reset(const FusedArgs& a, uint32_t n_state, hipStream_t stream
 // stage: the LDS stage size in bytes of the tuning (0: the small one)
 hipError_t launch_fused(const FusedArgs& a, uint32_t tile_waves, uint32_t chunk_digis,
                         uint32_t stage, uint32_t grid, hipStream_t stream);
+// The same launch as a node of a graph, after the node *last (NULL: the first), which it replaces.
+hipError_t add_fused(hipGraph_t graph, hipGraphNode_t* last, const FusedArgs& a, uint32_t tile_waves,
+                     uint32_t chunk_digis, uint32_t stage, uint32_t grid);
 hipError_t launch_cluster_dense(const uint8_t* adc_dense, const FusedArgs& a,
                                 uint32_t tile_waves, uint32_t chunk_digis, uint32_t stage,
                                 uint32_t grid, hipStream_t stream);

@@ -2007,24 +2007,45 @@ hipError_t launch_reset(const FusedArgs& a, uint32_t n_state, hipStream_t stream
     return hipGetLastError();
 }
 
-// The module-row kernels (cal.joins set) exist for the shapes whose wave lists hold a row.
-hipError_t launch_fused(const FusedArgs& a, uint32_t waves, uint32_t d, uint32_t stage,
-                        uint32_t grid, hipStream_t stream) {
-    (void)hipGetLastError();
+// The fused kernel of a shape (NULL: there is none). The module-row kernels (cal.joins set) exist for
+// the shapes whose wave lists hold a row.
+static const void* fused_function(const FusedArgs& a, uint32_t waves, uint32_t d, uint32_t stage) {
     const bool mod = a.cal.joins != nullptr;
-    bool ok = false;
+    const void* fn = nullptr;
     dispatch(waves, d, stage, [&](auto W, auto DW, auto SS) {
         constexpr int w = decltype(W)::value, dw = decltype(DW)::value, st = decltype(SS)::value;
-        if constexpr (dw >= kRowDigis) {
-            if (mod) hipLaunchKernelGGL((fused_kernel<w, dw, true, st>), dim3(grid), dim3(kWave * w), 0, stream, a);
-            else     hipLaunchKernelGGL((fused_kernel<w, dw, false, st>), dim3(grid), dim3(kWave * w), 0, stream, a);
-            ok = true;
-        } else if (!mod) {
-            hipLaunchKernelGGL((fused_kernel<w, dw, false, st>), dim3(grid), dim3(kWave * w), 0, stream, a);
-            ok = true;
-        }
+        if (!mod) fn = reinterpret_cast<const void*>(&fused_kernel<w, dw, false, st>);
+        if constexpr (dw >= kRowDigis)
+            if (mod) fn = reinterpret_cast<const void*>(&fused_kernel<w, dw, true, st>);
     });
-    return ok ? hipGetLastError() : hipErrorInvalidValue;
+    return fn;
+}
+
+hipError_t launch_fused(const FusedArgs& a, uint32_t waves, uint32_t d, uint32_t stage,
+                        uint32_t grid, hipStream_t stream) {
+    const void* fn = fused_function(a, waves, d, stage);
+    if (!fn) return hipErrorInvalidValue;
+    FusedArgs args = a;
+    void* params[] = {&args};
+    (void)hipGetLastError();
+    return hipLaunchKernel(fn, dim3(grid), dim3(kWave * waves), params, 0, stream);
+}
+
+hipError_t add_fused(hipGraph_t graph, hipGraphNode_t* last, const FusedArgs& a, uint32_t waves,
+                     uint32_t d, uint32_t stage, uint32_t grid) {
+    const void* fn = fused_function(a, waves, d, stage);
+    if (!fn) return hipErrorInvalidValue;
+    FusedArgs args = a;
+    void* params[] = {&args};
+    hipKernelNodeParams p{};
+    p.func = const_cast<void*>(fn);
+    p.gridDim = dim3(grid);
+    p.blockDim = dim3(kWave * waves);
+    p.kernelParams = params;   // (copied by the call)
+    hipGraphNode_t node;
+    const hipError_t e = hipGraphAddKernelNode(&node, graph, last, *last ? 1 : 0, &p);
+    if (e == hipSuccess) *last = node;
+    return e;
 }
 
 hipError_t launch_cluster_dense(const uint8_t* dense, const FusedArgs& a, uint32_t waves,

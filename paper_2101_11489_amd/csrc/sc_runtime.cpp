@@ -563,28 +563,53 @@ hipError_t enqueue_inputs(sc_ctx* c, Workspace& ws, uint32_t n, hipStream_t s) {
     return hipSuccess;
 }
 
-// The launch itself: one kernel, which leaves the events' results in pinned host memory. (With the
-// results copied back, and the descriptors sent by every graph replay, a call on one 50-FED event
-// took 41.0 us around a kernel of 21 us, now 37.5.)
-hipError_t enqueue_batch(sc_ctx* c, Workspace& ws, uint32_t n, hipStream_t s, bool timed,
-                         bool exclusive = true) {
-    hipError_t e;
-    const EventDesc* hd = ws.h_desc.as<EventDesc>();
+// The launches of a batch, each handed to f(args, launch). The kernels leave the events' results in
+// pinned host memory. (With the results copied back, and the descriptors sent by every graph replay,
+// a call on one 50-FED event took 41.0 us around a kernel of 21 us, now 37.5.)
+template <class F>
+hipError_t each_launch(sc_ctx* c, Workspace& ws, uint32_t n, bool exclusive, F&& f) {
     FusedArgs a = fused_args(c, ws, n);
-    a.any_status = any_status(hd, n);
+    a.any_status = any_status(ws.h_desc.as<EventDesc>(), n);
     // the per-XCD order needs its whole grid resident with no other such launch running: only a
     // launch that holds order2_mu to its end (the synchronous calls) uses it
     if (!exclusive && a.fed_major == 2u) a.fed_major = 1u;
-    if (timed && (e = hipEventRecord(c->ev0, s))) return e;
     for (const Launch& l : plan_launches(c, ws.mix, n, a.fed_major)) {
         a.one_each = l.one_each;
         a.pick = l.pick;
-        if ((e = launch_fused(a, l.shape.waves, l.shape.digis, l.shape.stage, l.grid, s))) return e;
+        const hipError_t e = f(a, l);
+        if (e != hipSuccess) return e;
     }
+    return hipSuccess;
+}
+
+hipError_t enqueue_batch(sc_ctx* c, Workspace& ws, uint32_t n, hipStream_t s, bool timed,
+                         bool exclusive = true) {
+    hipError_t e;
+    if (timed && (e = hipEventRecord(c->ev0, s))) return e;
+    e = each_launch(c, ws, n, exclusive, [&](const FusedArgs& a, const Launch& l) {
+        return launch_fused(a, l.shape.waves, l.shape.digis, l.shape.stage, l.grid, s);
+    });
+    if (e != hipSuccess) return e;
     return timed ? hipEventRecord(c->ev1, s) : hipSuccess;
 }
 
-// Replays (capturing on first use) the batched launch as a hipGraph.
+// The same as a graph. Its one or two nodes are put together here rather than captured: a stream to
+// capture on took 290 us to create and 40 to destroy, about half of a context's first call. (Event
+// nodes around the kernels, to time them, made every replay 20 us longer.)
+hipError_t batch_graph(sc_ctx* c, Workspace& ws, uint32_t n, hipGraphExec_t* out) {
+    hipGraph_t g;
+    hipError_t e = hipGraphCreate(&g, 0);
+    if (e != hipSuccess) return e;
+    hipGraphNode_t last = nullptr;
+    e = each_launch(c, ws, n, true, [&](const FusedArgs& a, const Launch& l) {
+        return add_fused(g, &last, a, l.shape.waves, l.shape.digis, l.shape.stage, l.grid);
+    });
+    if (e == hipSuccess) e = hipGraphInstantiate(out, g, nullptr, nullptr, 0);
+    (void)hipGraphDestroy(g);
+    return e;
+}
+
+// Replays (building it on first use) the batched launch as a hipGraph.
 hipError_t enqueue_batch_graph(sc_ctx* c, Workspace& ws, uint32_t n, hipStream_t s) {
     GraphKey k{n, c->tuning.fed_major, c->modules ? 1u : 0u, any_status(ws.h_desc.as<EventDesc>(), n),
                ws.generation};
@@ -592,21 +617,10 @@ hipError_t enqueue_batch_graph(sc_ctx* c, Workspace& ws, uint32_t n, hipStream_t
         for (uint32_t v : {l.shape.waves, l.shape.digis, l.shape.stage, l.grid, l.one_each, l.pick})
             k.push_back(v);
     auto it = c->graphs.find(k);
-    hipError_t e;
     if (it == c->graphs.end()) {
-        hipStream_t cs;
-        if ((e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking))) return e;
-        hipGraph_t g;
-        if ((e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal))) return e;
-        e = enqueue_batch(c, ws, n, cs, true);
-        hipError_t e2 = hipStreamEndCapture(cs, &g);
-        (void)hipStreamDestroy(cs);
-        if (e) return e;
-        if (e2) return e2;
         hipGraphExec_t ge;
-        e = hipGraphInstantiate(&ge, g, nullptr, nullptr, 0);
-        (void)hipGraphDestroy(g);
-        if (e) return e;
+        const hipError_t e = batch_graph(c, ws, n, &ge);
+        if (e != hipSuccess) return e;
         it = c->graphs.emplace(k, ge).first;
         c->stats.graph_captures++;
     }
