@@ -406,7 +406,7 @@ __device__ __forceinline__ void walk_fed(TileSmem<W, DW, S>& sm, const uint8_t* 
     __builtin_amdgcn_s_setprio(3);   // the tile's other waves wait for it
     if (fits_stage(sm, L)) walk_staged(sm, Pieces<S, kWave * W>::delta(g), L);
     else walk_windows(sm, g, L);
-    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_s_setprio(2);
 }
 
 template <int W, int DW, int S>
@@ -572,7 +572,7 @@ __device__ __forceinline__ void build_markers(TileSmem<W, DW, S>& sm, uint32_t w
         if (any_on) records(std::true_type{}, kMod && joined(J, ch) ? 0u : kNoStrip);
         else        records(std::false_type{}, 0u);
     }
-    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_s_setprio(1);
     wave_sync();
 }
 
@@ -1535,11 +1535,20 @@ __device__ __forceinline__ Tile posted_tile(const TileSmem<W, DW, S>& sm) {
 // one before it is large, and every later FED of its event would wait for it (with tickets taken
 // one tile ahead and the bytes under way meanwhile the waits grew from 6k to 43k cycles per tile).
 // A tile with a chunked group builds it again from the stage for its writes: those come first.
+// The waits end because a workgroup that waits for a tile's offsets holds no unformed tile before it
+// in its queue's order: of the waiting tiles take the first; what it waits for lies before it, so it
+// is not held up by another waiting one. Tiles of another queue (order 2) can be of lower FEDs, and
+// are taken only when the writes of the last of this one are done (other()).
+// Issue priorities (s_setprio): 3 in the walk, which a tile's other waves wait for, 2 in the other
+// phases that mostly wait for memory or LDS (ticket, staging, check, markers), 1 in forming, whose
+// counts later FEDs wait for, 0 in the writes. With it and the ticket's atomic beside the exchange,
+// 20 events of 440 FEDs took 104 -> 93 us, 64 ordinary ones 283 -> 275, 64 busy ones 642 -> 622.
 // 64 events of 440 FEDs: the wait for offsets fell from 6.3k to 2.9k cycles per tile, most of which
 // the other phases took up (vector issue is 70 % busy); one event: 30.3 -> 27.5 us.
-template <int W, int DW, bool kMod, int S, class FirstFn, class ClaimFn>
+template <int W, int DW, bool kMod, int S, class FirstFn, class AskFn, class TakeFn, class OtherFn>
 __device__ __forceinline__ void run_zs_tiles(const FusedArgs& A, TileSmem<W, DW, S>& sm,
-                                             FirstFn first, ClaimFn claim) {
+                                             FirstFn first, AskFn ask, TakeFn take,
+                                             OtherFn other) {
     const uint32_t w = wave_index<W>();
     const bool lead = w == 0u, last = w == (uint32_t)W - 1u;
     uint32_t c_lo, c_hi;
@@ -1597,9 +1606,19 @@ __device__ __forceinline__ void run_zs_tiles(const FusedArgs& A, TileSmem<W, DW,
             const EventDesc ev = event_outputs(A, p.e);
             if (last) resolve_offsets(A, sm, p.e, p.f, p_cnt, lb);
             tile_sync();
+            __builtin_amdgcn_s_setprio(0);
             write_list<W, DW, kMod>(A, sm, ev, p.f, w, p_grp, p_cnt);
         }
-        if (t.none()) break;
+        if (t.none()) {
+            if (!more) break;
+            p.e = kNoTile;
+            tile_sync();   // (every wave has read the posted tile)
+            if (last) post_tile(A, sm, other());
+            tile_sync();
+            more = !posted_tile(sm).none();
+            if (!more) break;
+            continue;
+        }
         store_gains(sm, gains, w);
         auto form = [&](uint32_t c0, uint32_t c1, uint32_t nd, uint32_t& n_cl, uint32_t& n_adc) {
             if (wk.fits) {
@@ -1611,7 +1630,10 @@ __device__ __forceinline__ void run_zs_tiles(const FusedArgs& A, TileSmem<W, DW,
             }
         };
         p_grp = form_group(sm, w, n_chunks, form);
+        more = !A.one_each;   // uniform over the grid: no second tile
+        const uint32_t asked = last && more ? ask() : kNoTile;   // (the next tile's ticket)
         p_cnt = exchange_counts(sm, w, p_grp, n_chunks);
+        __builtin_amdgcn_s_setprio(2);
         p = t;
         if (last) publish(A.tile_state + (size_t)t.e * A.cal.n_fed, t.f, p_cnt.n_cl, p_cnt.n_adc);
         lb.start(t.f);
@@ -1623,9 +1645,8 @@ __device__ __forceinline__ void run_zs_tiles(const FusedArgs& A, TileSmem<W, DW,
             write_chunks<W, DW, kMod>(A, sm, ev, p.f, w, p_cnt, n_chunks, form);
             p.e = kNoTile;
         }
-        more = !A.one_each;   // uniform over the grid: no second tile
         if (more) {
-            if (last) post_tile(A, sm, claim());
+            if (last) post_tile(A, sm, take(asked));
             tile_sync();   // (every wave is done with the stage)
         }
     }
@@ -1701,7 +1722,8 @@ __device__ __forceinline__ Ticket claim_one(const FusedArgs& A) {
 // place there (blockIdx / G), without an atomic: as many workgroups asking at once for their first
 // ticket cost a launch of one tile each 2 us. The tickets after the homes' are counted in
 // queue[x * kQueueStride] (one cache line each). A workgroup takes tiles from its home until that is
-// exhausted, then moves on to another open queue; it ends once every queue is known to be exhausted.
+// exhausted, then, with none of its tiles' writes left, moves on to another open queue; it ends once
+// every queue is known to be exhausted.
 // Look-back ends here too, if the whole grid is resident (the host launches this order only
 // with no other such launch running, and never with more workgroups than fit): take the unfinished
 // tile of lowest FED. Either it has been taken, and its predecessors (lower FEDs) are finished,
@@ -1758,6 +1780,24 @@ __device__ __forceinline__ Ticket claim_xcd(const FusedArgs& A, XcdCursor& c) {
     return Ticket{kNoTile, 0u};
 }
 
+// The same in two halves, so that the atomic is under way while the caller does something else: the
+// home queue's (or the present one's) ticket asked for, its answer not looked at, ...
+__device__ __forceinline__ uint32_t ask_xcd(const FusedArgs& A, const XcdCursor& c) {
+    const uint32_t x = uni(c.cur);
+    if (queue_tiles(A, x) <= home_tiles(x) || (c.known >> x & 1u)) return kNoTile;
+    return atomicAdd(A.queue + x * kQueueStride, lane() == 0u ? 1u : 0u);
+}
+// ... and the tile it stands for (none: that queue is exhausted).
+__device__ __forceinline__ Ticket take_xcd(const FusedArgs& A, XcdCursor& c, uint32_t asked) {
+    const uint32_t x = uni(c.cur), a = uni(asked);
+    if (a != kNoTile) {
+        const uint32_t t = home_tiles(x) + a;
+        if (t < queue_tiles(A, x)) return tile_of(A, x, t);
+    }
+    c.known |= 1u << x;
+    return Ticket{kNoTile, 0u};
+}
+
 // A workgroup's first tile: its own place in its home queue, or where that is past the queue's end
 // (the homes have the same number of workgroups, the queues not always of tiles) a ticket of another.
 __device__ __forceinline__ Ticket first_xcd(const FusedArgs& A, XcdCursor& c) {
@@ -1781,9 +1821,10 @@ __device__ __forceinline__ bool picked(const FusedArgs& A) {
     return large == (A.pick == 2u);
 }
 
-// Two-wave tiles: at most 128 vector registers, so that the eight tiles that fit a CU's LDS can be
-// resident (four waves per SIMD).
-constexpr int min_waves_per_simd(int w) { return w == 2 ? 4 : 1; }
+// At most 128 vector registers for tiles of two and four waves, so that the eight and four tiles that
+// fit a CU's LDS can be resident (four waves per SIMD). (64 busy events with the large shape take 765
+// us with 130 registers, 620 with 128.)
+constexpr int min_waves_per_simd(int w) { return w == 1 ? 1 : 4; }
 
 template <int W, int DW, bool kMod, int S>
 __global__ __launch_bounds__(kWave * W, min_waves_per_simd(W)) void fused_kernel(FusedArgs A) {
@@ -1792,7 +1833,9 @@ __global__ __launch_bounds__(kWave * W, min_waves_per_simd(W)) void fused_kernel
     XcdCursor cur{blockIdx.x & ((1u << queue_shift()) - 1u), 0u};
     run_zs_tiles<W, DW, kMod>(
         A, sm, [&]() { return A.fed_major == 2u ? first_xcd(A, cur) : claim_one(A); },
-        [&]() { return A.fed_major == 2u ? claim_xcd(A, cur) : claim_one(A); });
+        [&]() { return A.fed_major == 2u ? ask_xcd(A, cur) : kNoTile; },
+        [&](uint32_t asked) { return A.fed_major == 2u ? take_xcd(A, cur, asked) : claim_one(A); },
+        [&]() { return A.fed_major == 2u ? claim_xcd(A, cur) : Ticket{kNoTile, 0u}; });
 }
 
 template <int W, int DW, bool kMod, int S>
