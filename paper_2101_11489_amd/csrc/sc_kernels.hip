@@ -21,10 +21,12 @@
 //    seeds) go along the four digis of a lane and from lane to lane, in the definition's order;
 //  * the waves exchange their groups' counts in LDS; the tile publishes the FED's counts and looks
 //    back over the earlier FEDs of its event, 64 per load (decoupled look-back), for its output
-//    offsets; records are written by the lane of each cluster's last strip, member ADCs
-//    (gain-corrected here) by the lane of their digi, again in windows of 256.
+//    offsets; forming leaves the list of cluster members, from which records are written by the
+//    lane of each cluster's last strip and member ADCs (gain-corrected here) four per lane, again
+//    in windows of 256; the writes of a tile come after the first half of the next.
 // No MFMA: nothing here is a dense contraction.
 
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
@@ -723,8 +725,9 @@ __device__ __forceinline__ uint32_t build_dense_group(TileSmem<W, DW, S>& sm, ui
 // order, then from lane to lane, once per further lane of the longest run (mostly once).
 // Bound by vector instruction issue. Two digis per lane with six-step lane scans of every sum, as
 // before, took 8758 vector instructions per tile of a 64-event batch (440 FEDs, 0.5 to 5 %
-// occupancy) and 0.471 ms for the launch; this takes 5551 and 0.376 ms. Four per lane rather than
-// more: a wave's share of a FED is 370 to 1700 digis, and a window costs the same however few it holds.
+// occupancy) and 0.471 ms for the launch, the windows 5551 and 0.376 ms (with what has been
+// shortened since, 3838 and 0.275). Four per lane rather than more: a wave's share of a FED is 370
+// to 1700 digis, and a window costs the same however few it holds.
 constexpr uint32_t kWindow = 4 * kWave;
 
 // The last slot whose mask bit is set (at least one is).
@@ -839,9 +842,9 @@ __device__ __forceinline__ bool passes_exactly(float q, float S, float t) {
 // Runs of one window; puts the words of its clusters' members down from slot n_adc on and counts its
 // clusters and member ADCs (uniform; n_adc counts from the list's start). A member's slot is at or
 // below its own, and later windows are read from slots above all of these.
-// Only members are kept: of the strips above twice their noise that a front end sends, most
-// belong to no cluster at low occupancy (45 % of the digis at 1.5 %), and the writes take that many
-// windows less.
+// Only members are kept: of the strips above twice their noise that a front end sends, many
+// belong to no cluster (46 % of the digis at 1.5 % occupancy, 37 % over 0.5 to 5 %), and the writes
+// take that many windows less. 64 events of 440 FEDs: 306 -> 283 us, 64 busy ones 690 -> 641.
 //  * cluster threshold: the sums S and Q are the definition's own (S in strip order), and the test
 //    q >= t sqrt(S) is taken on squares first: q q >= S t2_hi passes and q q < S t2_lo fails, with
 //    t2_hi and t2_lo = t^2 (1 +- 2^-19). Every rounding on either way is 2^-24 or less relative
@@ -1718,10 +1721,13 @@ __device__ __forceinline__ Ticket claim_one(const FusedArgs& A) {
 }
 
 // Tile order 2: G = 8 queues (one in a grid of fewer workgroups); queue x holds the FEDs f = x
-// (mod G), FED-major. A workgroup's home queue is blockIdx mod G, and its first tile is its own
-// place there (blockIdx / G), without an atomic: as many workgroups asking at once for their first
-// ticket cost a launch of one tile each 2 us. The tickets after the homes' are counted in
-// queue[x * kQueueStride] (one cache line each). A workgroup takes tiles from its home until that is
+// (mod G), FED-major, its tickets counted in queue[x * kQueueStride] (one cache line each). A
+// workgroup's home queue is blockIdx mod G. In a launch with a workgroup for every tile (one_each) it
+// takes its own place there (blockIdx / G), without an atomic: as many workgroups asking at once
+// for a ticket cost such a launch 2 us. Its look-backs wait for workgroups of lower index only, which
+// start first. (Places for the first tiles of larger launches would hang where a grid is not resident
+// as a whole: tiles taken later would wait for places whose workgroups cannot start.)
+// Else a workgroup takes tickets from its home until that is
 // exhausted, then, with none of its tiles' writes left, moves on to another open queue; it ends once
 // every queue is known to be exhausted.
 // Look-back ends here too, if the whole grid is resident (the host launches this order only
@@ -1737,14 +1743,10 @@ struct XcdCursor {
 
 __device__ __forceinline__ uint32_t queue_shift() { return gridDim.x < kXcds ? 0u : kXcdShift; }
 
-// Tiles of queue x, and those that are some workgroup's first.
+// Tiles of queue x.
 __device__ __forceinline__ uint32_t queue_tiles(const FusedArgs& A, uint32_t x) {
     const uint32_t s = queue_shift(), n_fed = A.cal.n_fed;
     return x < n_fed ? ((n_fed - x + (1u << s) - 1u) >> s) * A.n_ev : 0u;
-}
-__device__ __forceinline__ uint32_t home_tiles(uint32_t x) {
-    const uint32_t s = queue_shift();
-    return (gridDim.x - x + (1u << s) - 1u) >> s;
 }
 __device__ __forceinline__ Ticket tile_of(const FusedArgs& A, uint32_t x, uint32_t t) {
     const uint32_t j = div_events(A, t);
@@ -1756,9 +1758,9 @@ __device__ __forceinline__ Ticket claim_xcd(const FusedArgs& A, XcdCursor& c) {
     // each pass either returns a tile or adds a queue to `known`: at most groups + 1 passes
     for (uint32_t k = 0; k <= groups && c.known != all; ++k) {
         const uint32_t x = uni(c.cur);   // a scalar address: one atomic per wave, not per lane
-        const uint32_t size = queue_tiles(A, x), home = home_tiles(x);
-        if (size > home && !(c.known >> x & 1u)) {
-            const uint32_t t = home + uni(atomicAdd(A.queue + x * kQueueStride, lane() == 0u ? 1u : 0u));
+        const uint32_t size = queue_tiles(A, x);
+        if (size && !(c.known >> x & 1u)) {
+            const uint32_t t = uni(atomicAdd(A.queue + x * kQueueStride, lane() == 0u ? 1u : 0u));
             if (t < size) return tile_of(A, x, t);
         }
         c.known |= 1u << x;
@@ -1769,7 +1771,7 @@ __device__ __forceinline__ Ticket claim_xcd(const FusedArgs& A, XcdCursor& c) {
         if (lane() < groups && !(c.known >> lane() & 1u)) {
             const uint32_t v = __hip_atomic_load(A.queue + lane() * kQueueStride, __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT);
-            open = home_tiles(lane()) + v < queue_tiles(A, lane());
+            open = v < queue_tiles(A, lane());
         }
         const uint32_t m = (uint32_t)__ballot(open);
         c.known = uni(c.known | (all & ~m));
@@ -1784,27 +1786,24 @@ __device__ __forceinline__ Ticket claim_xcd(const FusedArgs& A, XcdCursor& c) {
 // home queue's (or the present one's) ticket asked for, its answer not looked at, ...
 __device__ __forceinline__ uint32_t ask_xcd(const FusedArgs& A, const XcdCursor& c) {
     const uint32_t x = uni(c.cur);
-    if (queue_tiles(A, x) <= home_tiles(x) || (c.known >> x & 1u)) return kNoTile;
+    if (c.known >> x & 1u) return kNoTile;
     return atomicAdd(A.queue + x * kQueueStride, lane() == 0u ? 1u : 0u);
 }
 // ... and the tile it stands for (none: that queue is exhausted).
 __device__ __forceinline__ Ticket take_xcd(const FusedArgs& A, XcdCursor& c, uint32_t asked) {
     const uint32_t x = uni(c.cur), a = uni(asked);
-    if (a != kNoTile) {
-        const uint32_t t = home_tiles(x) + a;
-        if (t < queue_tiles(A, x)) return tile_of(A, x, t);
-    }
+    if (a != kNoTile && a < queue_tiles(A, x)) return tile_of(A, x, a);
     c.known |= 1u << x;
     return Ticket{kNoTile, 0u};
 }
 
-// A workgroup's first tile: its own place in its home queue, or where that is past the queue's end
-// (the homes have the same number of workgroups, the queues not always of tiles) a ticket of another.
+// A workgroup's first tile: a ticket, or its own place in its home queue (none if that is past the
+// queue's end: the homes have the same number of workgroups, the queues not always of tiles).
 __device__ __forceinline__ Ticket first_xcd(const FusedArgs& A, XcdCursor& c) {
+    if (!A.one_each) return claim_xcd(A, c);
     const uint32_t s = queue_shift();
     const uint32_t x = blockIdx.x & ((1u << s) - 1u), t = blockIdx.x >> s;
-    if (t < queue_tiles(A, x)) return tile_of(A, x, t);
-    return A.one_each ? Ticket{kNoTile, 0u} : claim_xcd(A, c);
+    return t < queue_tiles(A, x) ? tile_of(A, x, t) : Ticket{kNoTile, 0u};
 }
 
 // Whether this launch's shape is the one for its events, where two are enqueued for the same events
@@ -1835,7 +1834,7 @@ __global__ __launch_bounds__(kWave * W, min_waves_per_simd(W)) void fused_kernel
         A, sm, [&]() { return A.fed_major == 2u ? first_xcd(A, cur) : claim_one(A); },
         [&]() { return A.fed_major == 2u ? ask_xcd(A, cur) : kNoTile; },
         [&](uint32_t asked) { return A.fed_major == 2u ? take_xcd(A, cur, asked) : claim_one(A); },
-        [&]() { return A.fed_major == 2u ? claim_xcd(A, cur) : Ticket{kNoTile, 0u}; });
+        [&]() { return A.fed_major == 2u && !A.one_each ? claim_xcd(A, cur) : Ticket{kNoTile, 0u}; });
 }
 
 template <int W, int DW, bool kMod, int S>
@@ -1968,6 +1967,10 @@ int blocks_per_cu_for(bool dense) {
     hipError_t e = dense ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, cluster_dense_kernel<W, DW, kMod, S>, kWave * W, 0)
                          : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fused_kernel<W, DW, kMod, S>, kWave * W, 0);
     if (e != hipSuccess || nb < 1) return 1;
+    // (LDS is given out in pieces of 1280 bytes, which that count may take for smaller ones: it said 12
+    // for single-wave tiles of 13008 bytes, of which a CU holds 11)
+    constexpr size_t lds = (sizeof(TileSmem<W, DW, S>) + 1279) / 1280 * 1280;
+    nb = std::min(nb, (int)(160 * 1024 / lds));
     known[dense].store(nb, std::memory_order_relaxed);
     return nb;
 }

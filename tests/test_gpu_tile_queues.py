@@ -43,3 +43,24 @@ def test_queues_of_unequal_work(tiles_per_cu, waves, chunk, n_fed):
         for k, r in zip(which, res):
             compare_clusters(r[0], r[1], refs[k], f"kind {k}")
             assert bary_bit_exact(r[0], refs[k])
+
+
+@pytest.mark.parametrize("waves,chunk,stage", [(1, 1024, 0), (1, 2048, 0), (2, 2048, 10240), (2, 2880, 0),
+                                               (4, 2048, 0), (4, 6144, 10240)])
+def test_many_tiles_of_every_queue(waves, chunk, stage):
+    """Several tiles per workgroup of the largest grid, from every queue, each event's FEDs in a row."""
+    n_fed = 440
+    noise, gain, bad = calib_arrays(n_fed)
+    rng = np.random.default_rng(2)
+    mask = rng.random((n_fed * NCH, NS)) < 0.001
+    dense = np.where(mask, rng.integers(40, 256, mask.shape), 0).astype(np.uint8)
+    zs, fo = fedgen.encode_dense(dense, mask, max_run=255)
+    ref = oracle.process_event(zs, fo, noise, gain, bad)
+    assert ref.cl.size > 5000
+    with make_ctx(noise, gain, bad) as ctx:
+        ctx.tuning = {"use_graph": 0, "tile_waves": waves, "chunk_digis": chunk, "stage_bytes": stage,
+                      "tiles_per_cu": 32, "fed_major": 2}
+        res, _, _, _ = run_fused(ctx, [(zs, fo)] * 24)
+        for r in res:
+            compare_clusters(r[0], r[1], ref)
+            assert bary_bit_exact(r[0], ref)
