@@ -341,9 +341,12 @@ __device__ __forceinline__ void walk_staged(TileSmem<W, DW, S>& sm, uint32_t del
         // CU's one scalar unit, shared by its four SIMDs, is busy with the other waves'
         // scalar work, and a scalar chain would wait for it at every step
         uint32_t lo = sm.stage[o - 2u], hi = sm.stage[o - 1u];
-        asm volatile("" : "+v"(lo), "+v"(hi));
+        // (what does not wait for the bytes goes before them: 20 events of 440 FEDs 97 -> 94.5 us, 64
+        // 283 -> 278. One 16-bit read at an odd address instead of two of a byte: 118 and 326.)
         vpos = __builtin_amdgcn_inverse_ballot_w64(1ull << (k & 63u)) ? pos : vpos;
-        pos = (hi << 8) + (pos + lo + 2u);
+        uint32_t next = pos + 2u;
+        asm volatile("" : "+v"(lo), "+v"(hi), "+v"(next), "+v"(vpos));
+        pos = (hi << 8) + lo + next;
     };
 #pragma unroll 8
     for (uint32_t k = 0; k < 64u; ++k) step(k, vpos0);
