@@ -177,7 +177,9 @@ typedef struct {
 typedef struct {
     uint64_t launches, events, graph_replays, graph_captures;
     uint64_t server_batches, server_events, server_rejected_again;
-    double last_kernel_ms;   /* device time of the last fused/cluster launch (HIP events) */
+    double last_kernel_ms;   /* device time of the last synchronous call's kernels (HIP events); -1
+                                after a graph replay, which is not timed. Pipelined and served
+                                launches are not timed either and leave it as it is */
     double kernel_ms_total;  /* sum of those device times over the timed launches */
     uint64_t kernels_timed;  /* number of launches summed in kernel_ms_total */
     uint64_t allocations;    /* device and pinned-host allocations the library has made, in this

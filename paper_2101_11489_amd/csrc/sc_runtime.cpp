@@ -678,7 +678,9 @@ sc_status run_batch(sc_ctx* c, const sc_event* ev, uint32_t n, sc_clusters* out,
     SC_HIP(c, hipEventRecord(c->done, c->stream));
     SC_HIP(c, enqueue_clean(c, c->ws, c->stream));
     SC_HIP(c, hipEventSynchronize(c->done));
-    record_kernel_ms(c);
+    // a replay records no timing events: they would still hold an earlier launch's interval
+    if (graph) c->stats.last_kernel_ms = -1.0;
+    else       record_kernel_ms(c);
     c->stats.launches++;
     c->stats.events += n;
     return finish_batch(c, c->ws, st, n, out, ev_status, c->stream);
