@@ -71,6 +71,17 @@ struct FusedArgs {
 // A FED from this size on counts as large: from about 3000 digis, which two wave lists of 1440 hold
 // no more, to 3800, by the hits' width.
 constexpr uint32_t kLargeFed = 5200;
+// The tiles by which a launch's workgroups choose (pick): number k of 64. Events and FEDs are spread
+// over the launch each by itself, the FEDs in the order of the multiples of 37 modulo 64, so that all
+// events (of more, 64) and all parts of the detector are among them whatever the two counts have in
+// common. (Every n_tiles / 64-th tile in FED-major order met one event alone where 64 divides n_fed.)
+struct SampledTile {
+    uint32_t e, f;
+};
+constexpr SampledTile sampled_tile(uint32_t k, uint32_t n_ev, uint32_t n_fed) {
+    return SampledTile{(uint32_t)((2ull * k + 1ull) * n_ev / 128ull),
+                       (uint32_t)((2ull * (k * 37u % 64u) + 1ull) * n_fed / 128ull)};
+}
 // Member ADCs per FED from which an event's output capacity leaves room for large FEDs.
 constexpr uint32_t kLargeFedMembers = 3600;
 

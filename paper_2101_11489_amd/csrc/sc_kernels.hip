@@ -1810,14 +1810,12 @@ __device__ __forceinline__ Ticket first_xcd(const FusedArgs& A, XcdCursor& c) {
 }
 
 // Whether this launch's shape is the one for its events, where two are enqueued for the same events
-// and each looks for itself (A.pick: 1 the ordinary shape, 2 the large one): 64 tiles spread over
-// the launch are sampled, the same ones by every workgroup, and the large shape is for launches
-// with 16 or more FEDs among them of kLargeFed bytes.
+// and each looks for itself (A.pick: 1 the ordinary shape, 2 the large one): a lane per sampled tile,
+// the same ones for every workgroup, and the large shape is for launches with 16 or more FEDs among
+// them of kLargeFed bytes.
 __device__ __forceinline__ bool picked(const FusedArgs& A) {
-    const uint32_t n_tiles = A.n_ev * A.cal.n_fed;
-    const uint32_t t = (uint32_t)((uint64_t)lane() * n_tiles / kWave) + n_tiles / (2u * kWave);
-    const uint32_t f = div_events(A, t), e = t - f * A.n_ev;
-    gconst<uint64_t>* off = gc(gc(A.ev)[e].fed_off) + f;
+    const SampledTile t = sampled_tile(lane(), A.n_ev, A.cal.n_fed);
+    gconst<uint64_t>* off = gc(gc(A.ev)[t.e].fed_off) + t.f;
     const uint64_t lo = off[0], hi = off[1];
     const bool large = popc(__ballot(hi > lo && hi - lo >= kLargeFed)) >= 16u;
     return large == (A.pick == 2u);
