@@ -82,8 +82,6 @@ constexpr SampledTile sampled_tile(uint32_t k, uint32_t n_ev, uint32_t n_fed) {
     return SampledTile{(uint32_t)((2ull * k + 1ull) * n_ev / 128ull),
                        (uint32_t)((2ull * (k * 37u % 64u) + 1ull) * n_fed / 128ull)};
 }
-// Member ADCs per FED from which an event's output capacity leaves room for large FEDs.
-constexpr uint32_t kLargeFedMembers = 3600;
 
 // Scratch of the allocation-free batch call (sc_process_events_static), a file-scope device
 // array of sc_kernels.hip: event descriptors, the tile queue and the look-back words, for at most

@@ -84,11 +84,11 @@ struct PinBuf {
     template <class T> T* as() const { return static_cast<T*>(p); }
 };
 
-// What the host knows of a batch's FED sizes: those of host events, and for events in device memory
-// whether their output capacities leave room for large ones.
+// What the host knows of a batch's FED sizes: those of host events. Those of events in device memory
+// only the device knows.
 struct FedMix {
-    uint64_t known = 0, large = 0;
-    bool maybe_large = false;
+    uint64_t large = 0;
+    bool unknown = false;
 };
 
 // Buffers of one batched launch. Grown on demand, never shrunk (a caching arena in the spirit of
@@ -245,7 +245,8 @@ Shape tuned_shape(const sc_ctx* c) {
     return Shape{c->tuning.tile_waves, c->tuning.chunk_digis, stage_bytes_of(c->tuning.stage_bytes)};
 }
 
-// The default tuning's shape stands for a choice between it and the large one.
+// The default tuning. Its shape stands for a choice between it and the large one.
+constexpr sc_tuning kDefaultTuning{2880, 2, 32, 2, 1, 6656};
 constexpr Shape kOrdinaryShape{2, 2880, 6656}, kLargeShape{4, 6144, 10240};
 bool adaptive(const sc_ctx* c) {
     const Shape s = tuned_shape(c);
@@ -266,10 +267,12 @@ struct Launch {
 //    events of 50 FEDs 23.2 us and 26.3, 20 of 440 FEDs 105 and 146);
 //  * batches whose FEDs are mostly large take it too: the ordinary shape's stage and lists do not
 //    hold such FEDs, which are then read from global memory and formed twice (64 events of 440
-//    FEDs of 8.2 KB: 1795 us against 687). The host counts the FEDs of host events. Of device
-//    events it knows the capacity of their outputs: room for as many member ADCs as a large FED may
-//    have, on average, enqueues both shapes, and the kernels themselves look which of them is for
-//    the events (an idle launch is 4 us of a batch of this size).
+//    FEDs of 8.2 KB: a call takes 1834 us, and 641 so). The host counts the FEDs of host events. Of events in
+//    device memory it knows no sizes (the capacity of their outputs says nothing of them: FEDs of 8.2
+//    KB have about 3000 members, and a caller may leave ordinary ones as much room): both shapes are
+//    enqueued, and the kernels themselves look which of them is for the events. The idle launch is
+//    2 to 4 us of a call (20 events of 50 FEDs 42 -> 44 us, of 440 FEDs 121 -> 124). The large shape
+//    goes first: a context's first call is shorter so (64 events 496 us against 563).
 std::vector<Launch> plan_launches(const sc_ctx* c, const FedMix& mix, uint32_t n, uint32_t order) {
     const uint64_t n_tiles = (uint64_t)n * c->n_fed;
     // workgroups for order 2 with one for every tile: eight queues of equal length
@@ -283,17 +286,16 @@ std::vector<Launch> plan_launches(const sc_ctx* c, const FedMix& mix, uint32_t n
     if (!adaptive(c)) return {launch(tuned_shape(c), 0u)};
     if ((order == 2u ? each : n_tiles) <= resident(c, kLargeShape, false))
         return {launch(kLargeShape, 0u)};
-    if (mix.maybe_large) return {launch(kOrdinaryShape, 1u), launch(kLargeShape, 2u)};
+    if (mix.unknown) return {launch(kLargeShape, 2u), launch(kOrdinaryShape, 1u)};
     return {launch(4u * mix.large >= n_tiles ? kLargeShape : kOrdinaryShape, 0u)};
 }
 
-// Adds an event to the mix: its FED offsets where the host has them, else its output capacity.
-void add_event(FedMix& mix, const uint64_t* fed_offset, uint32_t cap_adc, uint32_t n_fed) {
+// Adds an event to the mix, with its FED offsets if the host has them.
+void add_event(FedMix& mix, const uint64_t* fed_offset, uint32_t n_fed) {
     if (!fed_offset) {
-        mix.maybe_large |= cap_adc / n_fed >= kLargeFedMembers;
+        mix.unknown = true;
         return;
     }
-    mix.known += n_fed;
     for (uint32_t f = 0; f < n_fed; ++f)
         mix.large += fed_offset[f + 1] > fed_offset[f] && fed_offset[f + 1] - fed_offset[f] >= kLargeFed;
 }
@@ -433,7 +435,7 @@ sc_status stage_batch(sc_ctx* c, Workspace& ws, const sc_event* ev, uint32_t n,
     ws.mix = FedMix{};
     for (uint32_t i = 0; i < n; ++i) {
         EventDesc d{};
-        add_event(ws.mix, host_mem(ev[i].mem) ? ev[i].fed_offset : nullptr, out[i].cap_adc, n_fed);
+        add_event(ws.mix, host_mem(ev[i].mem) ? ev[i].fed_offset : nullptr, n_fed);
         if (host_mem(ev[i].mem)) {
             const uint64_t span = event_span(ev[i].fed_offset, n_fed);
             if (span && ev[i].mem == SC_MEM_HOST)
@@ -1117,7 +1119,7 @@ sc_status sc_create(const sc_calib* cal, const sc_options* opt_in, sc_ctx** out)
         return fail(nullptr, SC_ERR_DEVICE, "hipGetDeviceProperties");
     c->n_cu = prop.multiProcessorCount;
     c->device_name = prop.gcnArchName;
-    c->tuning = sc_tuning{2880, 2, 32, 2, 1, stage_bytes_of(0)};
+    c->tuning = kDefaultTuning;
     load_tuning(c.get());
     if (opt.stream) {
         c->stream = static_cast<hipStream_t>(opt.stream);
@@ -1581,7 +1583,7 @@ sc_status sc_process_events_static(sc_ctx* c, const sc_event* ev, uint32_t n, sc
     SC_HIP(c, launch_reset(a, n * c->n_fed, s));
     SC_HIP(c, hipEventRecord(c->ev0, s));
     FedMix mix;
-    for (uint32_t i = 0; i < n; ++i) add_event(mix, nullptr, out[i].cap_adc, c->n_fed);
+    add_event(mix, nullptr, c->n_fed);   // (all in device memory)
     for (const Launch& l : plan_launches(c, mix, n, a.fed_major)) {
         a.one_each = l.one_each;
         a.pick = l.pick;
