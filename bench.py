@@ -250,7 +250,8 @@ def plain_line(sc, torch, stream, cfg_id, n_events, workers, tuning):
     cal = fedgen.make_calibration(cfg)
     evs = fedgen.make_events(cfg, cal, range(n_events), workers=workers)
     ctx = sc.Context(cal.noise, cal.gain, cal.bad, device=0, stream=stream)
-    ctx.tuning = {k: tuning[k] for k in ("chunk_digis", "tile_waves", "tiles_per_cu", "fed_major")}
+    # (the tile shape is left to the library, which takes another for one event than for a batch)
+    ctx.tuning = {k: tuning[k] for k in ("tiles_per_cu", "fed_major")}
     ctx.tuning = {"use_graph": 0}
     d = [sc.Event(e.zs, e.fed_offset).to_device() for e in evs]
     o = [ctx.output(*sc.safe_caps(x)) for x in d]
@@ -440,8 +441,7 @@ def serving_sweep(sc, torch, stream, args, tuning, fracs):
     ctx3 = sc.Context(cal3.noise, cal3.gain, cal3.bad, device=0, stream=stream,
                       max_batch=64, n_streams=2)
     if tuning is not None:
-        ctx3.tuning = {k: tuning[k] for k in ("chunk_digis", "tile_waves", "tiles_per_cu",
-                                              "fed_major")}
+        ctx3.tuning = {k: tuning[k] for k in ("tiles_per_cu", "fed_major")}
     ctx3.tuning = {"use_graph": 0}
     p_dev = [sc.Event(x.zs, x.fed_offset).to_device() for x in pool]
     n_out = 256

@@ -146,10 +146,12 @@ typedef struct {
     sc_mem mem;
 } sc_clusters;
 
-/* Performance-relevant choices of the fused kernel (found by sc_autotune). With the default tile
- * shape (2 waves, 2880 digis, the small stage) the library takes 4 waves, 6144 digis and the large
- * stage instead for launches whose tiles can all have a resident workgroup of it, and for events
- * with mostly large FEDs; the results are the same. Every other shape is used as it is. */
+/* Performance-relevant choices of the fused kernel (found by sc_autotune). The default shape, 2
+ * waves and 2880 digis with stage_bytes 0, leaves the choice to the library: it takes 4 waves, 6144
+ * digis and the large stage instead for launches whose tiles can all have a resident workgroup of
+ * it, and for events with mostly large FEDs (in a launch with events in device memory the device
+ * looks); the results are the same. Every shape whose stage is named is used as it is, among them 2
+ * waves and 2880 digis with stage_bytes 6656, and so is what sc_autotune finds. */
 typedef struct {
     uint32_t chunk_digis;    /* digis a tile holds in LDS per pass: 2048, 3072, 4096; 1024 with 1
                                 wave, 2880 with 2, 6144 with 4 and the large stage */
@@ -166,11 +168,13 @@ typedef struct {
                                 until the look-back's wait bound reports SC_ERR_DEVICE. Other
                                 values are taken as 1. */
     uint32_t use_graph;      /* 1: replay the batched launch as a hipGraph */
-    uint32_t stage_bytes;    /* LDS bytes that stage a tile's FED: 0 or 6656 (FEDs of up to 6640
-                                bytes), or 10240 (up to 10224 bytes, with fewer resident tiles)
-                                for tile_waves 2 with chunk_digis 2048 or 2880, and tile_waves 4
-                                with 4096 or 6144 (6144 only with this stage). A larger FED is
-                                read from global memory instead: the same results, more slowly. */
+    uint32_t stage_bytes;    /* LDS bytes that stage a tile's FED: 6656 (FEDs of up to 6640 bytes),
+                                or 10240 (up to 10224 bytes, with fewer resident tiles) for
+                                tile_waves 2 with chunk_digis 2048 or 2880, and tile_waves 4 with
+                                4096 or 6144 (6144 only with this stage). 0: the library's choice
+                                with the default shape (above); with any other it stands for
+                                6656, and sc_get_tuning gives 6656. A larger FED is read from
+                                global memory instead: the same results, more slowly. */
 } sc_tuning;
 
 /* Counters of a context. */

@@ -25,6 +25,7 @@ SC_OK, SC_MALFORMED, SC_PENDING = 0, 1, 2
 SC_ERR_INVALID_ARG, SC_ERR_OVERFLOW, SC_ERR_BUDGET = -1, -2, -3
 SC_STATIC_MAX_EVENTS, SC_STATIC_MAX_TILES = 1024, 1024 * 440   # sc_process_events_static
 SC_ERR_AGAIN, SC_ERR_DEVICE, SC_ERR_NOMEM, SC_ERR_UNKNOWN_TICKET = -4, -5, -6, -7
+STAGE_BYTES_SMALL = 6656   # sc_tuning.stage_bytes
 SC_MEM_HOST, SC_MEM_DEVICE, SC_MEM_HOST_PINNED = 0, 1, 2
 CH_MALFORMED, CH_FED_TRAILING = 1, 2
 
@@ -500,7 +501,11 @@ class Context:
 
     @tuning.setter
     def tuning(self, d: dict):
+        """Fields to change. A shape that is named without its stage gets the small one where the
+        library has chosen so far (stage_bytes 0): it is then used as it is."""
         cur = self.tuning
+        if not cur["stage_bytes"] and ("chunk_digis" in d or "tile_waves" in d):
+            cur["stage_bytes"] = STAGE_BYTES_SMALL
         cur.update(d)
         t = ScTuning(*[cur[f] for f, _ in ScTuning._fields_])
         self._check(lib().sc_set_tuning(self._h, ctypes.byref(t)))

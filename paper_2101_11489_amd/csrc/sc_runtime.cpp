@@ -245,13 +245,14 @@ Shape tuned_shape(const sc_ctx* c) {
     return Shape{c->tuning.tile_waves, c->tuning.chunk_digis, stage_bytes_of(c->tuning.stage_bytes)};
 }
 
-// The default tuning. Its shape stands for a choice between it and the large one.
-constexpr sc_tuning kDefaultTuning{2880, 2, 32, 2, 1, 6656};
+// Stage 0 with the ordinary shape, as in the default tuning, leaves the choice between it and the large
+// one to the library; with its stage named it is used as it is, like every other shape (so that
+// what the autotuner timed is what its caller runs).
 constexpr Shape kOrdinaryShape{2, 2880, 6656}, kLargeShape{4, 6144, 10240};
-bool adaptive(const sc_ctx* c) {
-    const Shape s = tuned_shape(c);
-    return s.waves == kOrdinaryShape.waves && s.digis == kOrdinaryShape.digis &&
-           s.stage == kOrdinaryShape.stage;
+constexpr sc_tuning kDefaultTuning{kOrdinaryShape.digis, kOrdinaryShape.waves, 32, 2, 1, 0};
+bool leaves_shape_open(const sc_tuning& t) {
+    return t.tile_waves == kOrdinaryShape.waves && t.chunk_digis == kOrdinaryShape.digis &&
+           t.stage_bytes == 0u;
 }
 
 // The kernels of one batch: one launch, or two of which the device runs one (pick).
@@ -260,7 +261,7 @@ struct Launch {
     uint32_t grid, one_each, pick;
 };
 
-// A batch's launches. Where the default tuning leaves the shape open:
+// A batch's launches. Where the tuning leaves the shape open:
 //  * where every tile can have a resident workgroup of the large shape, they take it: four waves on
 //    a FED shorten its chain of passes (one 50-FED event 21.1 us with the ordinary shape and 18.5
 //    with the large one, one of 440 FEDs 26.2 and 23.4); beyond that the ordinary one is faster (20
@@ -283,7 +284,7 @@ std::vector<Launch> plan_launches(const sc_ctx* c, const FedMix& mix, uint32_t n
         return Launch{s, one_each ? (uint32_t)each : (uint32_t)std::min<uint64_t>(fit, n_tiles),
                       one_each ? 1u : 0u, pick};
     };
-    if (!adaptive(c)) return {launch(tuned_shape(c), 0u)};
+    if (!leaves_shape_open(c->tuning)) return {launch(tuned_shape(c), 0u)};
     if ((order == 2u ? each : n_tiles) <= resident(c, kLargeShape, false))
         return {launch(kLargeShape, 0u)};
     if (mix.unknown) return {launch(kLargeShape, 2u), launch(kOrdinaryShape, 1u)};
@@ -1283,7 +1284,7 @@ sc_status sc_cluster(sc_ctx* c, const uint8_t* adc_dense, sc_mem in_mem, sc_clus
     FusedArgs a = fused_args(c, ws, 1);
     SC_HIP(c, hipEventRecord(c->ev0, c->stream));
     // as for batches: four waves on a FED where each can have a resident workgroup
-    const bool small = adaptive(c) && c->n_fed <= resident(c, kLargeShape, true);
+    const bool small = leaves_shape_open(c->tuning) && c->n_fed <= resident(c, kLargeShape, true);
     const Shape shape = small ? kLargeShape : tuned_shape(c);
     SC_HIP(c, launch_cluster_dense(d_in, a, shape.waves, shape.digis, shape.stage,
                                    grid_for(c, shape, c->n_fed, true), c->stream));
@@ -1733,7 +1734,7 @@ sc_status sc_set_tuning(sc_ctx* c, const sc_tuning* t) {
     c->tuning = *t;
     c->tuning.fed_major = t->fed_major > 2u ? 1u : t->fed_major;
     c->tuning.use_graph = t->use_graph ? 1 : 0;
-    c->tuning.stage_bytes = stage_bytes_of(t->stage_bytes);
+    if (!leaves_shape_open(*t)) c->tuning.stage_bytes = stage_bytes_of(t->stage_bytes);
     return SC_OK;
 }
 

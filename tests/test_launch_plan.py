@@ -108,3 +108,12 @@ def test_other_shapes_are_used_as_they_are(plan):
     for chunk, waves, stage in ((3072, 2, 6656), (6144, 4, 10240), (1024, 1, 6656), (2880, 2, 10240)):
         for n_ev, feds in ((1, [DEVICE]), (64, [DEVICE]), (64, [8000])):
             assert plan(440, n_ev, feds, tuning=(chunk, waves, 32, stage))[0] == [((waves, chunk, stage), 0)]
+
+
+@pytest.mark.parametrize("order", [0, 1, 2])
+@pytest.mark.parametrize("n_fed,n_ev,feds", [(50, 1, [DEVICE]), (440, 2, [DEVICE]), (440, 64, [DEVICE]),
+                                             (440, 64, [8000]), (440, 64, [8000, DEVICE]), (50, 1, [8000])])
+def test_a_named_stage_pins_the_default_shape(plan, n_fed, n_ev, feds, order):
+    pinned = plan(n_fed, n_ev, feds, order, tuning=(2880, 2, 32, 6656))
+    assert pinned[0] == [(ORDINARY, 0)]
+    assert plan(n_fed, n_ev, feds, order, tuning=(2880, 2, 32, 0)) == plan(n_fed, n_ev, feds, order)
