@@ -3,38 +3,11 @@ side stubbed: 256 compute units, the residency that the shapes' LDS allows). The
 FEDs' sizes where the host has them, is left to the device where it has not, and never depends on the
 room in the outputs, which the plan is not told.
 """
-import os
-import subprocess
-
 import pytest
 
-from paper_2101_11489_amd import build
+from runtime_probe import compile_probe
 
-PROBE = r"""
-#include "sc_runtime.cpp"
-namespace sc {
-hipError_t static_scratch_address(void**) { return hipErrorUnknown; }
-hipError_t launch_derive_calib(const float*, const float*, const uint8_t*, uint32_t, float*, float*,
-                               hipStream_t) { return hipErrorUnknown; }
-hipError_t launch_reset(const FusedArgs&, uint32_t, hipStream_t) { return hipErrorUnknown; }
-hipError_t launch_fused(const FusedArgs&, uint32_t, uint32_t, uint32_t, uint32_t, hipStream_t) {
-    return hipErrorUnknown;
-}
-hipError_t add_fused(hipGraph_t, hipGraphNode_t*, const FusedArgs&, uint32_t, uint32_t, uint32_t,
-                     uint32_t) { return hipErrorUnknown; }
-hipError_t launch_cluster_dense(const uint8_t*, const FusedArgs&, uint32_t, uint32_t, uint32_t,
-                                uint32_t, hipStream_t) { return hipErrorUnknown; }
-hipError_t launch_unpack(const uint8_t*, const uint64_t*, uint32_t, uint8_t*, uint8_t*, EventResult*,
-                         hipStream_t) { return hipErrorUnknown; }
-hipError_t launch_hits(const HitDesc*, uint32_t, uint32_t, const uint32_t*, const float*, uint32_t,
-                       hipStream_t) { return hipErrorUnknown; }
-uint32_t stage_bytes_of(uint32_t stage) { return stage ? stage : 6656u; }
-bool tile_shape_supported(uint32_t, uint32_t, uint32_t) { return true; }
-bool tile_shape_supports_modules(uint32_t, uint32_t) { return true; }
-int fused_blocks_per_cu(uint32_t w, uint32_t d, bool, bool, uint32_t stage) {
-    return (int)(160 * 1024 / (4 * d + stage_bytes_of(stage) + 2400 + 16 * w));
-}
-}  // namespace sc
+MAIN = r"""
 // n_fed chunk waves tiles_per_cu stage | order n_ev host_bytes...: the FED bytes of each host event (all
 // FEDs alike), 0 for a device event; chunk 0: the default tuning
 int main(int argc, char** argv) {
@@ -66,17 +39,10 @@ DEVICE = 0
 
 @pytest.fixture(scope="module")
 def plan(tmp_path_factory):
-    d = tmp_path_factory.mktemp("launch_plan")
-    src, exe, lib = d / "probe.cpp", d / "probe", os.path.join(build.ROCM, "lib")
-    src.write_text(PROBE)
-    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(build.ROCM, "include"),
-                    "-I", build.INCLUDE, "-I", build.CSRC, str(src), "-o", str(exe), "-L", lib,
-                    "-lamdhip64", "-lpthread", "-Wl,-rpath," + lib], check=True)
+    probe = compile_probe(tmp_path_factory.mktemp("launch_plan"), MAIN)
 
     def run(n_fed, n_ev, feds, order=2, tuning=(0, 0, 0, 0)):
-        out = subprocess.run([str(exe), *(str(v) for v in (n_fed, *tuning, order, n_ev, *feds))], check=True,
-                             capture_output=True, text=True).stdout
-        rows = [tuple(int(v) for v in line.split()) for line in out.splitlines()]
+        rows = [tuple(int(v) for v in line) for line in probe(n_fed, *tuning, order, n_ev, *feds)]
         return [(r[:3], r[5]) for r in rows], [r[3] for r in rows], [r[4] for r in rows]
     return run
 
