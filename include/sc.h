@@ -149,8 +149,8 @@ typedef struct {
 /* Performance-relevant choices of the fused kernel (found by sc_autotune). The default shape, 2
  * waves and 2880 digis with stage_bytes 0, leaves the choice to the library: it takes 4 waves, 6144
  * digis and the large stage instead for launches whose tiles can all have a resident workgroup of
- * it, and for events with mostly large FEDs (in a launch with events in device memory the device
- * looks); the results are the same. Every shape whose stage is named is used as it is, among them 2
+ * it, and for batches with FEDs of more than 6640 bytes or with many just below that (in a launch
+ * with events in device memory the device looks); the results are the same. Every shape whose stage is named is used as it is, among them 2
  * waves and 2880 digis with stage_bytes 6656, and so is what sc_autotune finds. */
 typedef struct {
     uint32_t chunk_digis;    /* digis a tile holds in LDS per pass: 2048, 3072, 4096; 1024 with 1
@@ -249,9 +249,10 @@ sc_status sc_process_pipelined(sc_ctx *ctx, const sc_event *ev, uint32_t n, sc_c
  * and every output must be in device memory (SC_MEM_DEVICE; host kinds are SC_ERR_INVALID_ARG:
  * they need staging, use sc_process_events), 1 <= n <= SC_STATIC_MAX_EVENTS and
  * n * n_fed <= SC_STATIC_MAX_TILES, else SC_ERR_INVALID_ARG. The call's scratch (descriptors,
- * look-back words, tile queue, per-event results) is one fixed array per GPU, about 3.7 MB, held
- * from sc_create until the process ends and cleared by a fill kernel at the start of every call;
- * descriptors and results pass through pinned host memory that sc_create allocated. All contexts
+ * look-back words, tile queue) is one fixed array per GPU, about 3.7 MB, held from sc_create until
+ * the process ends; a fill kernel clears the words and the queue at the start of every call. The
+ * descriptors come from, and the events' results go to, pinned host memory that sc_create
+ * allocated for the context. All contexts
  * on one GPU share that array: calls that overlap on one GPU (from different threads or
  * contexts) race and must be serialised by the caller. Results, statuses and errors as for
  * sc_process_events. */

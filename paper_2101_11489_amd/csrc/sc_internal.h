@@ -53,6 +53,8 @@ constexpr size_t kNoisePad = 1024;
 // (order 2, at most 8).
 constexpr uint32_t kQueueStride = 32;
 constexpr size_t kQueueBytes = 8 * kQueueStride * sizeof(uint32_t);
+// Beside counter 0: whether the large shape was picked, for the second of two launches.
+constexpr uint32_t kPickedWord = 1;
 
 struct FusedArgs {
     const EventDesc* ev;
@@ -65,22 +67,35 @@ struct FusedArgs {
     uint32_t any_status;             // some event wants its channels' status
     uint32_t ev_magic;               // ceil(2^32 / n_ev), 0 for n_ev = 1
     uint32_t one_each;               // order 2 with a workgroup for every tile: no second tickets
-    uint32_t pick;                   // 0: run; 1, 2: run if the events' FEDs are mostly ordinary,
-                                     // or large (of two shapes enqueued for the same events)
+    uint32_t pick;                   // 0: run; of two shapes enqueued for the same events, the large
+                                     // one first: 2 look at the FEDs, say so and run if they are for
+                                     // it, 1 run if they were not
 };
-// A FED from this size on counts as large: from about 3000 digis, which two wave lists of 1440 hold
-// no more, to 3800, by the hits' width.
-constexpr uint32_t kLargeFed = 5200;
-// The tiles by which a launch's workgroups choose (pick): number k of 64. Events and FEDs are spread
-// over the launch each by itself, the FEDs in the order of the multiples of 37 modulo 64, so that all
-// events (of more, 64) and all parts of the detector are among them whatever the two counts have in
-// common. (Every n_tiles / 64-th tile in FED-major order met one event alone where 64 divides n_fed.)
+// The FEDs by which a launch's shape is chosen (plan_launches): those past the small stage, which the
+// ordinary shape reads from global memory byte by byte while all later FEDs of their event wait, and
+// long ones, of whose digis many wave groups have more than the 1440 that its lists hold.
+constexpr uint32_t kSmallStageFed = 6640, kLongFed = 6100;
+constexpr bool for_large_shape(uint64_t past, uint64_t past_per, uint64_t longs, uint64_t n) {
+    return past * past_per >= n || longs * 8u >= n;
+}
+// Where the workgroups choose by themselves (pick), they look at runs of four FEDs from these tiles on:
+// number k of n = 64, 128, 256 or 512. Events and FEDs are spread over the launch each by itself, the
+// FEDs in the order of the multiples of 37 modulo n, so that all events (of more, n) and all parts of
+// the detector are among them whatever the two counts have in common. (Every n_tiles / 64-th tile in
+// FED-major order met one event alone where 64 divides n_fed.)
 struct SampledTile {
     uint32_t e, f;
 };
-constexpr SampledTile sampled_tile(uint32_t k, uint32_t n_ev, uint32_t n_fed) {
-    return SampledTile{(uint32_t)((2ull * k + 1ull) * n_ev / 128ull),
-                       (uint32_t)((2ull * (k * 37u % 64u) + 1ull) * n_fed / 128ull)};
+constexpr uint32_t kSampledRun = 4;
+// log2(n / 64): every event of up to 512 has a run.
+constexpr uint32_t sampled_shift(uint32_t n_ev) {
+    return n_ev <= 64u ? 0u : n_ev <= 128u ? 1u : n_ev <= 256u ? 2u : 3u;
+}
+constexpr SampledTile sampled_tile(uint32_t k, uint32_t shift, uint32_t n_ev, uint32_t n_fed) {
+    const uint32_t bits = 6u + shift;
+    const uint32_t f = (k * 37u & ((1u << bits) - 1u)) * n_fed >> bits;
+    const uint32_t last = n_fed > kSampledRun ? n_fed - kSampledRun : 0u;   // a whole run, if there is one
+    return SampledTile{(uint32_t)((uint64_t)k * n_ev >> bits), f < last ? f : last};
 }
 
 // Scratch of the allocation-free batch call (sc_process_events_static), a file-scope device

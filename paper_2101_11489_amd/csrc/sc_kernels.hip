@@ -729,7 +729,7 @@ __device__ __forceinline__ uint32_t build_dense_group(TileSmem<W, DW, S>& sm, ui
 // Bound by vector instruction issue. Two digis per lane with six-step lane scans of every sum, as
 // before, took 8758 vector instructions per tile of a 64-event batch (440 FEDs, 0.5 to 5 %
 // occupancy) and 0.471 ms for the launch, the windows 5551 and 0.376 ms (with what has been
-// shortened since, 3838 and 0.275). Four per lane rather than more: a wave's share of a FED is 370
+// shortened since, 3951 and 0.279). Four per lane rather than more: a wave's share of a FED is 370
 // to 1700 digis, and a window costs the same however few it holds.
 constexpr uint32_t kWindow = 4 * kWave;
 
@@ -1547,10 +1547,11 @@ __device__ __forceinline__ Tile posted_tile(const TileSmem<W, DW, S>& sm) {
 // are taken only when the writes of the last of this one are done (other()).
 // Issue priorities (s_setprio): 3 in the walk, which a tile's other waves wait for, 2 in the other
 // phases that mostly wait for memory or LDS (ticket, staging, check, markers), 1 in forming, whose
-// counts later FEDs wait for, 0 in the writes. With it and the ticket's atomic beside the exchange,
-// 20 events of 440 FEDs took 104 -> 93 us, 64 ordinary ones 283 -> 275, 64 busy ones 642 -> 622.
-// 64 events of 440 FEDs: the wait for offsets fell from 6.3k to 2.9k cycles per tile, most of which
-// the other phases took up (vector issue is 70 % busy); one event: 30.3 -> 27.5 us.
+// counts later FEDs wait for, 0 in the writes: 64 ordinary events of 440 FEDs 288 -> 279 us, 64 busy
+// ones 642 -> 613, 13 with module rows 119 -> 110, 20 events and single ones the same. The ticket's
+// atomic beside the exchange: 20 events 96 -> 94 us, 64 busy ones 618 -> 613, module rows 109 -> 110.
+// The offsets asked for late: 64 events of 440 FEDs waited 2.9k cycles per tile for them instead of
+// 6.3k, most of which the other phases took up (vector issue is 70 % busy); one event: 30.3 -> 27.5 us.
 template <int W, int DW, bool kMod, int S, class FirstFn, class AskFn, class TakeFn, class OtherFn>
 __device__ __forceinline__ void run_zs_tiles(const FusedArgs& A, TileSmem<W, DW, S>& sm,
                                              FirstFn first, AskFn ask, TakeFn take,
@@ -1809,16 +1810,38 @@ __device__ __forceinline__ Ticket first_xcd(const FusedArgs& A, XcdCursor& c) {
     return t < queue_tiles(A, x) ? tile_of(A, x, t) : Ticket{kNoTile, 0u};
 }
 
-// Whether this launch's shape is the one for its events, where two are enqueued for the same events
-// and each looks for itself (A.pick: 1 the ordinary shape, 2 the large one): a lane per sampled tile,
-// the same ones for every workgroup, and the large shape is for launches with 16 or more FEDs among
-// them of kLargeFed bytes.
+// Whether the events are for the large shape: runs of four FEDs per sampled tile, the same ones for
+// every wave. It is for launches with a FED past the small stage among them (1 of 256 stands for about
+// 0.4 %; the shapes cross between 0.05 and 0.5 %), or with one in eight a long one.
+__device__ __forceinline__ bool for_large_shape(const FusedArgs& A) {
+    static_assert(kSmallStageFed == (uint32_t)kStageSmall - 16u, "what the small stage holds");
+    const uint32_t shift = sampled_shift(A.n_ev), n_fed = A.cal.n_fed;
+    uint32_t longs = 0u;
+    bool past = false;
+    for (uint32_t r = 0; r < 1u << shift; ++r) {
+        const SampledTile t = sampled_tile(r * kWave + lane(), shift, A.n_ev, n_fed);
+        gconst<uint64_t>* off = gc(gc(A.ev)[t.e].fed_off);
+        uint64_t at[kSampledRun + 1];
+#pragma unroll
+        for (uint32_t i = 0; i <= kSampledRun; ++i) at[i] = off[t.f + i < n_fed ? t.f + i : n_fed];
+#pragma unroll
+        for (uint32_t i = 0; i < kSampledRun; ++i) {
+            const uint64_t L = at[i + 1] > at[i] ? at[i + 1] - at[i] : 0u;
+            past |= L > kSmallStageFed;
+            longs += L >= kLongFed ? 1u : 0u;
+        }
+    }
+    const uint32_t n = kSampledRun * kWave << shift;
+    return sc::for_large_shape(popc(__ballot(past)), n, wave_sum(longs), n);
+}
+
+// Whether this launch is the one that runs, where two are enqueued for the same events. The first one
+// leaves its answer for the second, which reads a word where it would begin with two dependent loads.
 __device__ __forceinline__ bool picked(const FusedArgs& A) {
-    const SampledTile t = sampled_tile(lane(), A.n_ev, A.cal.n_fed);
-    gconst<uint64_t>* off = gc(gc(A.ev)[t.e].fed_off) + t.f;
-    const uint64_t lo = off[0], hi = off[1];
-    const bool large = popc(__ballot(hi > lo && hi - lo >= kLargeFed)) >= 16u;
-    return large == (A.pick == 2u);
+    if (A.pick == 1u) return gc(A.queue)[kPickedWord] == 0u;
+    const bool large = for_large_shape(A);
+    if (blockIdx.x == 0u) gm(A.queue)[kPickedWord] = large ? 1u : 0u;
+    return large;
 }
 
 // At most 128 vector registers for tiles of two and four waves, so that the eight and four tiles that

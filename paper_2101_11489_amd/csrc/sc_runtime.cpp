@@ -87,7 +87,7 @@ struct PinBuf {
 // What the host knows of a batch's FED sizes: those of host events. Those of events in device memory
 // only the device knows.
 struct FedMix {
-    uint64_t large = 0;
+    uint64_t past = 0, longs = 0;   // FEDs past the small stage, and long ones
     bool unknown = false;
 };
 
@@ -263,17 +263,23 @@ struct Launch {
 
 // A batch's launches. Where the tuning leaves the shape open:
 //  * where every tile can have a resident workgroup of the large shape, they take it: four waves on
-//    a FED shorten its chain of passes (one 50-FED event 21.1 us with the ordinary shape and 18.5
-//    with the large one, one of 440 FEDs 26.2 and 23.4); beyond that the ordinary one is faster (20
-//    events of 50 FEDs 23.2 us and 26.3, 20 of 440 FEDs 105 and 146);
-//  * batches whose FEDs are mostly large take it too: the ordinary shape's stage and lists do not
-//    hold such FEDs, which are then read from global memory and formed twice (64 events of 440
-//    FEDs of 8.2 KB: a call takes 1834 us, and 641 so). The host counts the FEDs of host events. Of events in
-//    device memory it knows no sizes (the capacity of their outputs says nothing of them: FEDs of 8.2
-//    KB have about 3000 members, and a caller may leave ordinary ones as much room): both shapes are
-//    enqueued, and the kernels themselves look which of them is for the events. The idle launch is
-//    2 to 4 us of a call (20 events of 50 FEDs 42 -> 44 us, of 440 FEDs 121 -> 124). The large shape
-//    goes first: a context's first call is shorter so (64 events 496 us against 563).
+//    a FED shorten its chain of passes (tile order 2, ordinary and large shape, us: one event of 50
+//    FEDs 18.1 and 16.6 at 1.5 % occupancy, 38 and 21 at 5 %; one of 440 FEDs 22.1 and 20.5, 42 and
+//    28). At 1024 workgroups, as many as are resident, the two are level (17.4 and 17.7 at 0.5 %, 20.2
+//    and 19.8 at 1.5 %); beyond, tiles wait for a workgroup (1120: 21.9 and 26.3; 16 events of 440
+//    FEDs 80 and 104);
+//  * batches with FEDs that the ordinary shape does not hold take it too. FEDs past its stage are read
+//    from global memory, while the later FEDs of their events wait (64 events of 440 FEDs at 0.5 %
+//    occupancy, ordinary and large shape, us, by how many of the 28160 FEDs are past the stage: none
+//    205 and 338, 18 378 and 330, 118 531 and 329, 1440 914 and 349, all of 8.2 KB about 1800 and 612):
+//    the line is at one in 1024. Long FEDs overflow its lists and are formed twice (uniform FEDs of
+//    5.7 KB 158 and 195, of 6.1 225 and 201): at one in eight, a mean, since their digis per byte
+//    differ. The host counts the FEDs of host events. Of events in device memory it knows no sizes (the
+//    capacity of their outputs says nothing of them: FEDs of 8.2 KB have about 3000 members, and a
+//    caller may leave ordinary ones as much room): both shapes are enqueued, and the kernels
+//    themselves look which of them is for the events. The idle launch is 2 to 4 us of a call (20
+//    events of 50 FEDs 42 -> 45 us, of 440 FEDs 122 -> 125). The large shape goes first: a context's
+//    first call is shorter so (64 events 496 us against 563).
 std::vector<Launch> plan_launches(const sc_ctx* c, const FedMix& mix, uint32_t n, uint32_t order) {
     const uint64_t n_tiles = (uint64_t)n * c->n_fed;
     // workgroups for order 2 with one for every tile: eight queues of equal length
@@ -288,7 +294,8 @@ std::vector<Launch> plan_launches(const sc_ctx* c, const FedMix& mix, uint32_t n
     if ((order == 2u ? each : n_tiles) <= resident(c, kLargeShape, false))
         return {launch(kLargeShape, 0u)};
     if (mix.unknown) return {launch(kLargeShape, 2u), launch(kOrdinaryShape, 1u)};
-    return {launch(4u * mix.large >= n_tiles ? kLargeShape : kOrdinaryShape, 0u)};
+    const bool large = for_large_shape(mix.past, 1024u, mix.longs, n_tiles);
+    return {launch(large ? kLargeShape : kOrdinaryShape, 0u)};
 }
 
 // Adds an event to the mix, with its FED offsets if the host has them.
@@ -297,8 +304,11 @@ void add_event(FedMix& mix, const uint64_t* fed_offset, uint32_t n_fed) {
         mix.unknown = true;
         return;
     }
-    for (uint32_t f = 0; f < n_fed; ++f)
-        mix.large += fed_offset[f + 1] > fed_offset[f] && fed_offset[f + 1] - fed_offset[f] >= kLargeFed;
+    for (uint32_t f = 0; f < n_fed; ++f) {
+        const uint64_t L = fed_offset[f + 1] > fed_offset[f] ? fed_offset[f + 1] - fed_offset[f] : 0u;
+        mix.past += L > kSmallStageFed;
+        mix.longs += L >= kLongFed;
+    }
 }
 
 // Largest byte offset an event references (its buffer must be at least this long).

@@ -60,3 +60,24 @@ def test_sizes(data, call, pattern, n):
                 compare_clusters(*o.to_numpy()[:2], refs[i], f"pass {rep} event {k}")
                 o.cl.zero_()
                 o.adc.zero_()
+
+
+def test_events_that_change_between_calls(data):
+    """One context and batch size, events of either kind in turn: each call's own events decide."""
+    cal, evs, refs = data
+    devs = [sc.Event(e.zs, e.fed_offset).to_device() for e in evs]
+    with make_ctx(cal.noise, cal.gain, cal.bad) as ctx:
+        for pattern in ((0, 1), (2, 3), (2, 3), (0, 1), (0, 1), (2, 3), 31 * (2,) + (0,), (3,)):
+            idx = [pattern[i % len(pattern)] for i in range(50)]
+            outs = [ctx.output(refs[i].cl.size, refs[i].adc.size) for i in idx]
+            for call in ("replay", "static"):
+                b = ctx.batch([devs[i] for i in idx], outs)
+                torch.cuda.synchronize()
+                if call == "static":
+                    assert sc.lib().sc_process_events_static(ctx._h, b.c_ev, b.n, b.c_out, b.c_st) == sc.SC_OK
+                else:
+                    assert ctx.process_batch(b)[0] == sc.SC_OK
+                for k, (i, o) in enumerate(zip(idx, outs)):
+                    compare_clusters(*o.to_numpy()[:2], refs[i], f"{call} {pattern} event {k}")
+                    o.cl.zero_()
+                    o.adc.zero_()

@@ -57,10 +57,13 @@ def test_device_events_are_judged_by_the_device(plan, n_fed, n_ev, order):
     assert set(plan(n_fed, n_ev, [8000, 8000, 8000, DEVICE], order)[0]) == both
 
 
-@pytest.mark.parametrize("feds,shape", [([5199], ORDINARY), ([5200], LARGE), ([5200, 1, 1, 1], LARGE),
-                                        ([5200, 1, 1, 1, 1], ORDINARY), ([1], ORDINARY)])
-def test_host_events_are_judged_by_their_feds(plan, feds, shape):
-    assert plan(440, 60, feds)[0] == [(shape, 0)]
+# FEDs past the small stage (6640 bytes) from one in 1024 on, long ones (6100 bytes) from one in eight
+@pytest.mark.parametrize("n_ev,feds,shape", [
+    (60, [6640] + 8 * [1], ORDINARY), (60, [6641], LARGE), (60, [6641] + 59 * [1], LARGE),
+    (1024, [6641] + 1023 * [1], LARGE), (1025, [6641] + 1024 * [1], ORDINARY), (60, [6099], ORDINARY),
+    (60, [6100], LARGE), (64, [6100] + 7 * [1], LARGE), (63, [6100] + 8 * [1], ORDINARY), (60, [1], ORDINARY)])
+def test_host_events_are_judged_by_their_feds(plan, n_ev, feds, shape):
+    assert plan(440, n_ev, feds)[0] == [(shape, 0)]
 
 
 @pytest.mark.parametrize("feds", [[DEVICE], [1000], [8000]])
